@@ -167,9 +167,9 @@ int lp_unwrap_solve(lp_unwrap_ctx* ctx, int M, int N, const double* psi, const f
  * tol and options; each map stops on its own (per-map convergence flags), and
  * every step of every iteration is one launch for all active maps.
  * Every preconditioner of lpu_preconditioner is supported.  The natural-order
- * ILU(0) / IC(0) / SSOR sweeps are sequential along each map, so each map's
- * sweep is walked by one workgroup; the other preconditioners are tiled over
- * the whole device.
+ * ILU(0) / IC(0) / SSOR sweeps are sequential along each map; each 64-row strip
+ * of a map is swept by one workgroup, the strips of all maps side by side; the
+ * other preconditioners are tiled over the whole device.
  * per_map: HOST array of n_maps lpu_stats, or NULL.
  * Returns the worst status over the maps (an error if any map failed). */
 int lp_unwrap_batch(lp_unwrap_ctx* ctx, int n_maps, const lpu_map* maps, double p, double eps,

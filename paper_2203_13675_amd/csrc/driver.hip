@@ -38,13 +38,14 @@ void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int ex
 int egrid(const Engine& e, int ntiles);
 int dct_grid_for(const Engine& e, int ndtiles);
 bool dct_wide_for(const Engine& e, int ndtiles, int kind);
-template <typename T> void e_pivots(hipStream_t, const Engine&, int, bool, double);
-void wf_shape(int M, int N, int* diags, int* len);
+template <typename T> void e_pivots(hipStream_t, const Engine&, int, bool, double, bool);
+int wf_strips(int M);
+int wf_grid(const Engine& e);
 template <typename T> void e_tc_pivots(hipStream_t, const Engine&, int, bool, double);
 template <typename T>
 void e_twocolor(hipStream_t, const Engine&, int, int, bool, double, int);
 template <typename T>
-void e_sweep(hipStream_t, const Engine&, int, int, bool, double, const void*, void*, void*);
+void e_sweep(hipStream_t, const Engine&, int, bool, double, const void*, void*, void*, int);
 
 enum { kIdle = 99 };
 enum FinOpH { kFinInitH = 0, kFinAlphaH = 1, kFinUpdateH = 2, kFinConfirmH = 3, kFinTailH = 4,
@@ -73,8 +74,8 @@ static double now_ms() {
 // engine set-up
 // ---------------------------------------------------------------------------
 static void engine_free(Engine& e) {
-  // counts, mact, act and dact live in one allocation that starts at counts
-  void* ptrs[] = {e.desc, e.ms, e.tile_map, e.dtile_map, e.fcnt, e.gcnt, e.gsum, e.eot, e.counts,
+  // counts, mact, slist, act and dact live in one allocation that starts at counts
+  void* ptrs[] = {e.desc, e.ms, e.tile_map, e.dtile_map, e.fcnt, e.gcnt, e.gsum, e.eot, e.counts, e.wctl, e.wedge,
                   e.dx, e.dy, e.phi_prev, e.r64, e.U, e.V, e.aux, e.x[0], e.x[1], e.d[0],
                   e.d[1], e.r, e.s, e.q, e.b, e.t1, e.t2, e.iso, e.P};
   for (void* p : ptrs)
@@ -148,7 +149,8 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
   Engine& e = ctx->eng;
   std::vector<MapDesc> hd(n);
   long long px = 0;
-  int tiles = 0, dtiles = 0, maxN = 1, groups = 0, wfd = 1, wfl = 1;
+  int tiles = 0, dtiles = 0, maxN = 1, groups = 0, strips = 0;
+  long long edges = 0;
   for (int m = 0; m < n; ++m) {
     MapDesc& d = hd[m];
     std::memset(&d, 0, sizeof(d));
@@ -175,10 +177,9 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     d.phi = maps[m].phi;
     d.use_iso = maps[m].mask != nullptr ? 1 : 0;
     maxN = std::max(maxN, d.N);
-    int dg = 1, ln = 1;
-    wf_shape(d.M, d.N, &dg, &ln);
-    wfd = std::max(wfd, dg);
-    wfl = std::max(wfl, ln);
+    d.edge0 = edges;
+    edges += 2LL * wf_strips(d.M) * d.N;
+    strips += wf_strips(d.M);
     if (need_dct) {
       int stt = 0;
       d.tabM = dct_dev(ctx, d.M, &stt);
@@ -187,7 +188,7 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     }
   }
   const bool grow = px > e.cap_px || tiles > e.cap_tiles || dtiles > e.cap_dtiles ||
-                    n > e.cap_maps || elem > e.elem;
+                    n > e.cap_maps || elem > e.elem || strips > e.cap_strips || edges > e.cap_edge;
   if (grow) {
     // captured graphs hold the buffers' addresses; every other argument they
     // capture is part of their key, and the layout itself is device data
@@ -209,14 +210,18 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     // pinned staging (counts, active maps, stencil tiles, the two DCT
     // lists), so the first three go up in one copy
     const long long dcap = (long long)dtiles + 8LL * (n + 1) * 256 + 64;
-    const size_t list_ints = kListHead + (size_t)n + (size_t)tiles + 4 * (size_t)dcap;
+    const size_t list_ints =
+        kListHead + (size_t)n + 2 * (size_t)strips + (size_t)tiles + 4 * (size_t)dcap;
     A((void**)&e.counts, 4 * list_ints);
     if (ok) {
       e.mact = e.counts + kListHead;
-      e.act = e.mact + n;
+      e.slist = e.mact + n;
+      e.act = e.slist + 2 * (size_t)strips;
       e.dact = e.act + tiles;
     }
     A((void**)&e.fcnt, 4 * (size_t)n);
+    A((void**)&e.wctl, 256);
+    A((void**)&e.wedge, 8 * (size_t)edges);
     // groups <= tiles / G + dtiles / G + 2 n for any layout within these capacities
     const long long gcap = (long long)(tiles + dtiles) / kArriveGroup + 2LL * n + 8;
     A((void**)&e.gcnt, 4 * (size_t)gcap);
@@ -241,24 +246,30 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     e.cap_tiles = tiles;
     e.cap_dtiles = dtiles;
     e.cap_maps = n;
+    e.cap_strips = strips;
+    e.cap_edge = edges;
     e.elem = elem;
     e.pstride = pst;
     e.gstride = gcap;
     if (hipMemset(e.iso, 0, (size_t)cpx) != hipSuccess)
       return set_error(ctx, LPU_ERR_HIP, "hipMemset");
+    // no launch's tag (launches count from 1) is in a fresh edge buffer
+    if (hipMemsetAsync(e.wctl, 0, 256, ctx->stream) != hipSuccess ||
+        hipMemsetAsync(e.wedge, 0, 8 * (size_t)edges, ctx->stream) != hipSuccess)
+      return set_error(ctx, LPU_ERR_HIP, "hipMemsetAsync");
   }
   // arrival counters start at zero (every launch leaves them so; cleared
   // here as well, outside any graph capture)
   if (hipMemsetAsync(e.fcnt, 0, 4 * (size_t)n, ctx->stream) != hipSuccess ||
-      hipMemsetAsync(e.gcnt, 0, 4 * (size_t)std::max(groups, 1), ctx->stream) != hipSuccess)
+      hipMemsetAsync(e.gcnt, 0, 4 * (size_t)std::max(groups, 1), ctx->stream) != hipSuccess ||
+      hipMemsetAsync(e.wctl, 0, 8, ctx->stream) != hipSuccess)
     return set_error(ctx, LPU_ERR_HIP, "hipMemsetAsync");
   e.n_maps = n;
   e.total_px = px;
   e.total_tiles = tiles;
   e.total_dtiles = dtiles;
   e.max_n = maxN;
-  e.wf_diags = wfd;
-  e.wf_len = wfl;
+  e.total_strips = strips;
   e.th = ctx->tune.tile_rows;
   e.grid = ctx->tune.grid;
   e.dct_grid = ctx->tune.dct_grid;
@@ -349,7 +360,8 @@ static int engine_activate(lp_unwrap_ctx* ctx, const std::vector<int>& set, int*
   // staging with the device layout: counts, maps, stencil tiles, DCT lists
   int* hc = e.hlist;
   int* hm = hc + kListHead;
-  int* h = hm + e.cap_maps;
+  int* hs = hm + e.cap_maps;
+  int* h = hs + 2 * (size_t)e.cap_strips;
   int* hd = h + e.cap_tiles;
   int nt = 0;
   for (int m : set)
@@ -411,15 +423,32 @@ static int engine_activate(lp_unwrap_ctx* ctx, const std::vector<int>& set, int*
   const int nd = std::max(ndl[0], ndl[1]);
   int nm = 0;
   for (int m : set) hm[nm++] = m;
+  // strips of the natural-order sweeps, the first of every map, then the
+  // second ...: a strip's predecessor in its map always comes earlier, and
+  // the maps' chains run side by side
+  int ns = 0;
+  for (int s = 0, left = 1; left; ++s) {
+    left = 0;
+    for (int m : set)
+      if (s < wf_strips(e.hdesc[m].M)) {
+        hs[2 * ns] = m;
+        hs[2 * ns + 1] = s;
+        ++ns;
+        left = 1;
+      }
+  }
+  e.act_strips = ns;
   std::fill(hc, hc + kListHead, 0);
   hc[0] = nt;
   hc[1] = ndl[0];
   hc[2] = nm;
   hc[3] = ndl[1];
+  hc[4] = ns;
   hc[5] = ndl[2];
   hc[7] = ndl[3];
-  // counts, maps and stencil tiles in one copy, then each DCT list
-  const size_t head = (size_t)kListHead + (size_t)e.cap_maps + (size_t)nt;
+  // counts, maps, strips and stencil tiles in one copy, then each DCT list
+  const size_t head =
+      (size_t)kListHead + (size_t)e.cap_maps + 2 * (size_t)e.cap_strips + (size_t)nt;
   LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.counts, hc, 4 * head, hipMemcpyHostToDevice, st));
   for (int li = 0; li < nlists; ++li)
     if (ndl[li])
@@ -461,9 +490,9 @@ struct Pcg {
 
   // Preconditioner apply s = M^-1 r for the maps in state `expect`, then the
   // per-map finisher of r^T s with FinishMode `mode` (inside the last DCT
-  // stage for the even/odd kernels and the second two-colour pass, as a
-  // launch of its own otherwise).
-  void tail(hipStream_t st, int nt, int ndt, int nmaps, int expect, int mode) {
+  // stage for the even/odd kernels, the second two-colour pass and the
+  // backward sweep, as a launch of its own otherwise).
+  void tail(hipStream_t st, int nt, int ndt, int expect, int mode) {
     Engine& e = ctx->eng;
     KTimer& kt = ctx->kt;
     bool fused = false;
@@ -483,21 +512,22 @@ struct Pcg {
       }
     } else {
       const int ev = kt.begin(LPU_KC_SWEEP, st);
-      e_sweep<T>(st, e, nmaps, expect, pc == kPcSsor, omega, e.r, e.s, e.t1);
+      e_sweep<T>(st, e, expect, pc == kPcSsor, omega, e.r, e.s, e.t1, mode);
       kt.end(ev, LPU_KC_SWEEP, st);
+      fused = true;
     }
     if (!fused) fin(st, kFinTailH, expect, mode);
   }
 
   void fin(hipStream_t st, int op, int expect, int mode = kFinishNone) {
-    // the preconditioner partials of r^T s: one per DCT or sweep tile
+    // the preconditioner partials of r^T s: one per DCT tile
     e_finish(st, ctx->eng, op, expect, mode, pointwise());
   }
 
   // One PCG iteration for every running map of the active set (Algorithm 1's
   // inner loop body): direction update + SpMV, alpha, x/r update, beta or
   // stop test, preconditioner.
-  void body(hipStream_t st, int nt, int nd, int nm) {
+  void body(hipStream_t st, int nt, int nd) {
     Engine& e = ctx->eng;
     KTimer& kt = ctx->kt;
     // the finishers of alpha and of the update run inside the two launches
@@ -507,7 +537,7 @@ struct Pcg {
     ev = kt.begin(LPU_KC_UPDATE, st);
     e_update<T>(st, e, nt, pc, true);
     kt.end(ev, LPU_KC_UPDATE, st);
-    if (!pointwise()) tail(st, nt, nd, nm, kRun, kFinishIter);
+    if (!pointwise()) tail(st, nt, nd, kRun, kFinishIter);
   }
 
   // Issue K iterations: as launches of captured graphs of 8, 4, 2 and 1
@@ -515,15 +545,15 @@ struct Pcg {
   // this engine layout; consecutive kernels of one graph start back to back,
   // while each graph launch costs a few microseconds), or launch by launch
   // while kernel timing is on.
-  int iterate(int nt, int nd, int nm, long long K) {
+  int iterate(int nt, int nd, long long K) {
     hipStream_t st = ctx->stream;
     if (!ctx->tune.use_graph || ctx->kt.mask != 0) {
-      for (long long k = 0; k < K; ++k) body(st, nt, nd, nm);
+      for (long long k = 0; k < K; ++k) body(st, nt, nd);
       return LPU_OK;
     }
     const Engine& e = ctx->eng;
-    // the natural-order sweeps launch one grid per tile anti-diagonal over the
-    // active maps; every other kernel's shape depends on the tile counts only
+    // the natural-order sweeps' grid depends on the strips of the active maps,
+    // every other kernel's on the tile counts only
     const bool sweep = !pointwise() && !two_colour(pc) && pc != kPcDct;
     // every launch argument that is not a fixed buffer address
     int om[2] = {0, 0};
@@ -532,8 +562,7 @@ struct Pcg {
       if (K < chunk) continue;
       const int key[kGraphKey] = {egrid(e, nt), pointwise() ? 0 : dct_grid_for(e, nd),
                                   pc == kPcDct && dct_wide_for(e, nd, dct_kind) ? 1 : 0,
-                                  sweep ? nm : 0, sweep ? (e.wf_diags << 16) | e.wf_len : 0,
-                                  pc, dct_kind,
+                                  sweep ? wf_grid(e) : 0, pc, dct_kind,
                                   (int)sizeof(T), e.th, om[0], om[1], chunk};
       hipGraphExec_t ex = nullptr;
       for (const GraphEntry& g : ctx->graphs)
@@ -541,7 +570,7 @@ struct Pcg {
       if (!ex) {
         hipStream_t cs = ctx->cap_stream;
         LPU_HIP_CHECK(ctx, hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-        for (int k = 0; k < chunk; ++k) body(cs, nt, nd, nm);
+        for (int k = 0; k < chunk; ++k) body(cs, nt, nd);
         hipGraph_t g = nullptr;
         LPU_HIP_CHECK(ctx, hipStreamEndCapture(cs, &g));
         const hipError_t ie = hipGraphInstantiate(&ex, g, nullptr, nullptr, 0);
@@ -594,20 +623,20 @@ struct Pcg {
     kt.end(ev, LPU_KC_INIT, st);
     fin(st, kFinInitH, kRun);
     if (!pw) {
-      tail(st, nt, nd, (int)set.size(), kInitPc, kFinishInit);
+      tail(st, nt, nd, kInitPc, kFinishInit);
     }
     long long K = 4;
     const long long Kcap = std::max(2, ctx->tune.max_batch_iters);
     std::vector<double> prev_metric(e.n_maps, -1.0);
     std::vector<long long> prev_l(e.n_maps, 0);
     for (;;) {
-      if ((rc = iterate(nt, nd, (int)set.size(), K))) return rc;
+      if ((rc = iterate(nt, nd, K))) return rc;
       ev = kt.begin(LPU_KC_CONFIRM, st);
       e_resid<T>(st, e, nt, pc, true);
       kt.end(ev, LPU_KC_CONFIRM, st);
       fin(st, kFinConfirmH, kConfirm);
       if (!pw) {
-        tail(st, nt, nd, (int)set.size(), kConfirmPc, kFinishConfirm);
+        tail(st, nt, nd, kConfirmPc, kFinishConfirm);
       }
       if ((rc = read_states(ctx))) return rc;
       std::vector<int> still;
@@ -667,7 +696,7 @@ static int run_maps(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, double p, do
   const double t_start = now_ms();
   hipStream_t st = ctx->stream;
   const bool mixed = sizeof(T) == 4;
-  // 64 x 64 DCT tiles double as the sweeps' tiles (one partial of r^T s each)
+  // the sweeps' strips put their partials of r^T s in the 64 x 64 DCT tiles' slots
   int rc = engine_setup(ctx, n, maps, (int)sizeof(T), pc == kPcDct,
                         pc == kPcDct && even_odd_ok(maps, n, mixed, o.dct_mode) ? 128 : kDT);
   if (rc) return rc;
@@ -779,7 +808,7 @@ static int run_maps(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, double p, do
     e_weights<T>(st, e, nt, p, tau);
     if (need_diag || any_mask) e_diag<T>(st, e, nt, need_diag);
     if (pc == kPcIlu || pc == kPcIc || pc == kPcSsor)
-      e_pivots<T>(st, e, (int)act.size(), pc == kPcSsor, o.ssor_omega);
+      e_pivots<T>(st, e, (int)act.size(), pc == kPcSsor, o.ssor_omega, true);
     else if (two_colour(pc))
       e_tc_pivots<T>(st, e, nt, pc == kPcSsorRb, o.ssor_omega);
     kt.end(ev, LPU_KC_SETUP, st);
@@ -1002,7 +1031,7 @@ int step_pivots(lp_unwrap_ctx* ctx, int M, int N, const T* U, const T* V, T* piv
   Engine& e = ctx->eng;
   const size_t b = (size_t)M * N * sizeof(T);
   if ((rc = copy_in(ctx, e.U, U, b)) || (rc = copy_in(ctx, e.V, V, b))) return rc;
-  e_pivots<T>(ctx->stream, e, 1, ssor, omega);
+  e_pivots<T>(ctx->stream, e, 1, ssor, omega, false);
   if ((rc = copy_in(ctx, piv, e.aux, b))) return rc;
   LPU_HIP_CHECK(ctx, hipStreamSynchronize(ctx->stream));
   return LPU_OK;
@@ -1056,8 +1085,8 @@ int step_precond(lp_unwrap_ctx* ctx, int M, int N, int pc, int dct_mode, double 
     ctx->kt.end(ev, LPU_KC_TWOCOLOR, st);
     if ((rc = copy_in(ctx, s, e.s, b))) return rc;
   } else {
-    e_pivots<T>(st, e, 1, pc == kPcSsor, omega);
-    e_sweep<T>(st, e, 1, kRun, pc == kPcSsor, omega, e.r, e.s, e.t1);
+    e_pivots<T>(st, e, 1, pc == kPcSsor, omega, true);
+    e_sweep<T>(st, e, kRun, pc == kPcSsor, omega, e.r, e.s, e.t1, 0);
     if ((rc = copy_in(ctx, s, e.s, b))) return rc;
   }
   LPU_HIP_CHECK(ctx, hipStreamSynchronize(st));

@@ -77,6 +77,7 @@ struct MapDesc {
   int gb, gbd;                 // first arrival-group counter of the stencil / DCT tiles
   int use_iso;                 // zero the preconditioner output on isolated pixels
   long long off;               // element offset of this map in the work vectors
+  long long edge0;             // first entry of this map in the sweeps' edge buffer
   const double* psi;           // caller's wrapped phase
   const float* mask;           // caller's quality mask or null
   double* phi;                 // caller's solution (FP64)
@@ -106,8 +107,9 @@ struct Engine {
   long long total_px = 0, cap_px = 0;
   int total_tiles = 0, total_dtiles = 0, cap_tiles = 0, cap_dtiles = 0;
   int max_n = 1;             // widest map
-  int wf_diags = 1, wf_len = 1;  // natural-order sweeps: most 64 x 64 tile anti-diagonals of a
-                                 // map, and most tiles on one anti-diagonal
+  int total_strips = 0, cap_strips = 0;  // 64-row strips of the natural-order sweeps
+  int act_strips = 0;                    // those of the active maps
+  long long cap_edge = 0;                // entries of wedge
   int th = kTH;              // stencil tile height (rows)
   int grid = kEngineGrid;    // cap on the blocks of the stencil tile kernels
   int dct_grid = kDctGrid;   // cap on the blocks of a DCT stage (multiple of 8)
@@ -123,15 +125,18 @@ struct Engine {
   long long dlist_cap = 0;   // capacity of each of the four DCT lists
   int dct_trows = kDT;       // DCT output tile rows (64 dense, 128 even/odd)
   int* mact = nullptr;       // active maps (sweep kernels)
+  int* slist = nullptr;      // (map, strip) pairs of the active maps' strips, strip by strip
+  unsigned int* wctl = nullptr;        // sweeps: ticket, workgroups done, launches so far
+  unsigned long long* wedge = nullptr; // sweeps: tagged last rows of the strips
   int* fcnt = nullptr;       // per-map arrival counters of the fused finishers (zero between launches)
   int* gcnt = nullptr;       // per-group arrival counters (groups of kArriveGroup tiles of one map)
   double* gsum = nullptr;    // group sums of the fused finishers: 2 rows of gstride
   long long gstride = 0;
   EoTile* eot = nullptr;     // even/odd DCT tile records, [parity][global DCT tile]
   int* counts = nullptr;     // [0] active tiles, [1] DCT list (even stages), [2] active
-                             // maps, [3] DCT list (odd stages), [5] and [7] the wide-tile
-                             // lists; kListHead ints, followed in the same allocation by
-                             // mact, act and dact
+                             // maps, [3] DCT list (odd stages), [4] active strips, [5] and
+                             // [7] the wide-tile lists; kListHead ints, followed in the same
+                             // allocation by mact, slist, act and dact
   int* hlist = nullptr;      // pinned staging for counts and the lists, same layout
   // FP64 arrays
   double* dx = nullptr;

@@ -6,23 +6,56 @@
 // P = D/omega), so s = M^{-1} r is
 //   forward : y_ij = (r_ij + V_{i-1,j} y_{i-1,j} + U_{i,j-1} y_{i,j-1}) / p_ij
 //   backward: z_ij = y_ij + (U_ij z_{i,j+1} + V_ij z_{i+1,j}) / p_ij,  s = c z
-// (the solves multiply by 1 / p_ij, formed once per tile before its wavefront)
 // (c = 2 - omega for SSOR, 1 otherwise), and the ILU(0) pivots are
 //   p_ij = a_ij - U_{i,j-1}^2 / p_{i,j-1} - V_{i-1,j}^2 / p_{i-1,j}
 // (a_ij the diagonal of A; below 1e-4 a_ij the pivot falls back to a_ij; an
-// isolated pixel, a_ij = 0, gets 1).  Each value depends on its west and north
-// neighbours (east and south for the backward solve), so the maps are cut into
-// 64 x 64 tiles, the tiles with I + J = d form anti-diagonal d, and the tiles
-// of one anti-diagonal are independent: one launch per anti-diagonal (tiles
-// of every active map with that many diagonals), in increasing d for the
-// forward solve and the pivots and from the bottom-right corner for the
-// backward solve.  Inside a tile one wave runs a skewed wavefront: lane t owns
-// row t and at step k handles column k - t, so the north neighbour is lane
-// t - 1's value of the previous step (a DPP lane shift) and the west one its
-// own; the tile's operands are staged in LDS first with coalesced row loads,
-// and its results leave the same way.  Boundary values come from the tiles of
-// the previous anti-diagonal.  Every kernel completes on its own (no waits
-// across blocks).
+// isolated pixel, a_ij = 0, gets 1).  The factorisation stores 1 / p_ij, once
+// per outer step, so the solves multiply.
+//
+// Each value depends on its west and north neighbours (east and south for the
+// backward solve, which is the forward recurrence on the map rotated by 180
+// degrees), so a solve is a chain of M + N - 1 dependent pixels and its time
+// is that chain's: the map is cut into strips of 64 rows, one workgroup each,
+// and a strip is swept from left to right by ONE wave, lane l on row l, in
+// steps: at step k lane l computes column k - l.  The north neighbour is lane
+// l - 1's value of the previous step (a DPP lane shift), the west one the
+// lane's own.  Everything else is kept off that wave:
+//  * four loader waves, each with a quarter of the rows, bring the operands of a
+//    chunk of steps at a time from memory, three to five chunks ahead, and write
+//    them into an LDS ring indexed by step, so the sweeping wave reads 64
+//    consecutive entries at an immediate offset, eight steps ahead of their use;
+//  * two storer waves take its results from LDS back to rows in memory (the
+//    backward ones form s and the partial of r^T s as they pass);
+//  * the strip's last row goes to the strip below as it is made: every value
+//    is published with a tag, the launch's epoch, in the same 8-byte word (two
+//    words for a double), so the one wave that waits for it in the next
+//    strip's workgroup polls the data itself and needs no flag or fence.
+// The eight waves meet at one barrier per chunk.  Strips run concurrently,
+// each some 150 to 200 steps behind the one above it.
+//
+// What one workgroup can bring from memory sets the pace (a compute unit gets
+// about 50 GB/s of misses), so nothing is fetched twice: a chunk is as many
+// steps as a 128-byte line has elements, and a row's share of it is one whole
+// aligned line, the one whose first element is due within the chunk's steps.
+// Its 16 bytes per lane make 8 rows per instruction.
+//
+// Progress: workgroups take strips from a ticket counter, in an order in which
+// a strip's predecessor always has the smaller ticket, so the strip a
+// workgroup waits for is finished or held by a workgroup that already runs,
+// whatever the number of resident workgroups.  The wait is bounded all the
+// same; a strip whose wait runs out goes on with NaN, which ends that map's
+// solve as a breakdown.
+//
+// Measured (960 x 1280 FP64; 840 x 1120 FP32): a forward solve 154 and 110 us,
+// a backward one 164 and 121 us, the pivots 284 and 213 us, where one launch
+// per anti-diagonal of 64 x 64 tiles took 34 x 14.7 us and 31 x 13.4 us for a
+// solve and 1290 and 1020 us for the pivots.  A chunk of 16 steps takes 0.6 us
+// (FP32) to 0.8 us (FP64), of which the sweeping wave computes 0.45 and 0.6, and
+// a strip starts 5.6 to 6.3 us after the one above it: 80 steps it must wait
+// (64 of skew and the chunk), two chunks of look-ahead, and the trip of the
+// last row's values through memory.
+
+#include <type_traits>
 
 #include "lpu_internal.h"
 #include "lpu_device.h"
@@ -30,85 +63,42 @@
 
 namespace lpu {
 
-constexpr int kWWaves = 4;               // waves per tile: all stage and store, wave 0 sweeps
-constexpr int kWThreads = 64 * kWWaves;
-constexpr int kWT = 64;  // tile side (rows = columns = lanes of a wave); LDS rows are kWT
-                         // elements apart, so the wavefront's reads (row t, column k - t)
-                         // fall in distinct banks
+constexpr int kWT = 64;                 // rows of a strip (lanes of the sweeping wave)
+constexpr int kWLoad = 4, kWStore = 2;  // loader and storer waves
+constexpr int kWThreads = 64 * (2 + kWLoad + kWStore);
+constexpr int kWRing = 4;    // chunks of operands in LDS: in use, next, and the two a write spans
+constexpr int kWOut = 3;     // chunks of results: in work, and the two a store spans
+constexpr int kWAhead = 8;   // steps between reading a step's operands and using them
+constexpr int kWHeld = 3;    // chunks a loader or storer wave holds in registers
+constexpr int kWPitch = kWT + 1;  // LDS entries per step (an element's row + 1 is a valid entry)
+constexpr int kWMaxGrid = 512;
+// polls of one wait before it is given up: about a second, where a wait on a
+// running predecessor takes microseconds
+constexpr int kWMaxPolls = 1 << 20;
+
+enum SweepMode : int { kWPivots = 0, kWForward = 1, kWBackward = 2 };
 
 struct WArgs {
   const MapDesc* desc;
   MapState* ms;
+  const int* slist;   // (map, strip) pairs of the active maps, predecessors first
   const int* mact;
-  int mact_cap;  // entries of mact (its capacity)
   const int* counts;
   double* P;
   long long pstride;
   const void *U, *V, *piv, *r;
   void *s, *y;
-  int expect;  // state of the maps to work on (-1: every active map)
-  int diag;    // anti-diagonal index (backward solve: counted from the bottom-right)
+  unsigned int* ctl;         // ticket, workgroups done, launches so far
+  unsigned long long* edge;  // tagged last rows of the strips
+  int *fcnt, *gcnt;          // arrival counters of the fused finisher
+  double* gsum;
+  long long gstride;
+  int expect;    // state of the maps to work on (-1: every active map)
+  int fin_mode;  // backward: FinishMode of the fused finisher of r^T s (0: none)
+  int recip;     // pivots: store 1 / p (what the solves read) instead of p
   double omega;
   int ssor;
 };
-
-// Tile of anti-diagonal a.diag of the map in slot blockIdx.y, position
-// blockIdx.x along the diagonal; false when there is none.
-struct WTile {
-  int m, M, N, i0, j0, local, tx;
-  long long off;
-};
-
-// The lookups form a chain of memory round trips ahead of the operands: the
-// active-map count, the block's map, the map's state and its descriptor.
-// The map is requested with the count (through an index clamped to the
-// list's capacity, used only when the slot is active) and the descriptor
-// with the state, so the chain is two round trips instead of four; the
-// empty asm statements keep the compiler from sinking the second load of
-// each pair below the branch that follows.
-template <bool REV>
-__device__ __forceinline__ bool wf_tile(const WArgs& a, WTile& w) {
-  const int nm = a.counts[2];
-  const int m = a.mact[min((int)blockIdx.y, max(a.mact_cap - 1, 0))];
-  __asm__ volatile("" ::"s"(nm), "s"(m));
-  if ((int)blockIdx.y >= nm) return false;
-  w.m = m;
-  const MapDesc& d = a.desc[m];
-  w.M = d.M;
-  w.N = d.N;
-  w.off = d.off;
-  const int st = a.ms[m].state;
-  __asm__ volatile("" ::"s"(w.M), "s"(w.N), "s"(w.off), "s"(st));
-  if (a.expect >= 0 && st != a.expect) return false;
-  const int ty = (d.M + kWT - 1) / kWT;
-  w.tx = (d.N + kWT - 1) / kWT;
-  if (a.diag >= ty + w.tx - 1) return false;
-  const int imin = max(0, a.diag - w.tx + 1), imax = min(a.diag, ty - 1);
-  const int I = imin + (int)blockIdx.x;
-  if (I > imax) return false;
-  int ti = I, tj = a.diag - I;
-  if (REV) {
-    ti = ty - 1 - ti;
-    tj = w.tx - 1 - tj;
-  }
-  w.i0 = ti * kWT;
-  w.j0 = tj * kWT;
-  w.local = ti * w.tx + tj;
-  return true;
-}
-
-// DPP whole-wave shift: lane l receives lane l-1's value (lane 0 receives 0).
-__device__ __forceinline__ int wshr(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xF, 0xF, true);
-}
-__device__ __forceinline__ float from_prev_lane(float v) {
-  return __builtin_bit_cast(float, wshr(__builtin_bit_cast(int, v)));
-}
-__device__ __forceinline__ double from_prev_lane(double v) {
-  const long long b = __builtin_bit_cast(long long, v);
-  const int lo = wshr((int)(b & 0xffffffffLL)), hi = wshr((int)(b >> 32));
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
-}
 
 // DPP whole-wave shift with a fill: lane l receives lane l-1's v, lane 0 keeps
 // its own value of fill.
@@ -125,242 +115,580 @@ __device__ __forceinline__ double from_prev_lane(double fill, double v) {
   return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
 }
 
-// Lane `src` (wave-uniform) of v, in every lane.
-__device__ __forceinline__ float lane_value(float v, int src) {
-  return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
-}
-__device__ __forceinline__ double lane_value(double v, int src) {
-  const long long b = __builtin_bit_cast(long long, v);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffLL), src);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), src);
-  return __builtin_bit_cast(double, ((long long)hi << 32) | (unsigned int)lo);
-}
-
 __device__ __forceinline__ double wf_wave_sum(double v) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
   return v;
 }
 
-template <typename T>
-using gptr = const __attribute__((address_space(1))) T*;
-using lptr = __attribute__((address_space(3))) void*;
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
-// In-grid element (i, j) of a map, clamped into it, and whether it is inside.
-__device__ __forceinline__ size_t wf_at(int i, int j, int M, int N, bool& ok) {
-  ok = (unsigned)i < (unsigned)M && (unsigned)j < (unsigned)N;
-  return (size_t)min(max(i, 0), M - 1) * N + min(max(j, 0), N - 1);
+// Quotients of the pivot recurrence.  Both a pivot's quotients (by the pivot
+// to its west and by the one to its north) divide by a value some lane formed
+// one step earlier, so that lane forms its reciprocal once, and the shift
+// brings it along with the pivot.  rcp_full: 1 / b to about an ulp of a double
+// (the hardware's estimate and two Newton steps).  quot: the correctly rounded
+// a / b, as the division operator gives it: for a double by Markstein's final
+// step (IBM J. Res. Dev. 34, 1990: q = a r, then q + r (a - b q)); for floats
+// the product in double, whose error of 2^-51 cannot reach across a rounding
+// boundary of a 24-bit quotient (2^-49 away at least).
+__device__ __forceinline__ double rcp_full(double b) {
+  double r = __builtin_amdgcn_rcp(b);
+  r = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+  return __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
+}
+__device__ __forceinline__ float quot(float a, float, double r) { return (float)((double)a * r); }
+__device__ __forceinline__ double quot(double a, double b, double r) {
+  const double q = a * r;
+  return __builtin_fma(__builtin_fma(-b, q, a), r, q);
 }
 
-template <typename T>
-__device__ __forceinline__ T wf_ld(gptr<T> a, int i, int j, int M, int N, T outside) {
-  bool ok;
-  const T v = a[wf_at(i, j, M, N, ok)];
-  return ok ? v : outside;
+// A value of a strip's last row with its launch's tag: one 8-byte word for a
+// float, two (low and high half) for a double.  Words are single agent-coherent
+// accesses, so a word whose tag matches holds its value.
+__device__ __forceinline__ void edge_put(unsigned long long* p, unsigned int tag, float v) {
+  const unsigned long long w = ((unsigned long long)tag << 32) | __builtin_bit_cast(unsigned int, v);
+  __hip_atomic_store(p, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-
-// One 64-element vector of array a along the tile's edge, staged like the
-// tile: element t at (i0 + t * di + oi, j0 + t * dj + oj), `outside` off the
-// map.
+__device__ __forceinline__ void edge_put(unsigned long long* p, unsigned int tag, double v) {
+  const unsigned long long b = __builtin_bit_cast(unsigned long long, v), t = (unsigned long long)tag << 32;
+  __hip_atomic_store(p, t | (b & 0xffffffffULL), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(p + 1, t | (b >> 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// The words of one value as read, and the value once every tag matches.
 template <typename T>
-struct WEdge {
-  T* dst;
-  gptr<T> src;
-  int di, dj, oi, oj;
-  T outside;
+struct Edge {
+  unsigned long long w[sizeof(T) / 4];
+  __device__ __forceinline__ void read(const unsigned long long* p) {
+#pragma unroll
+    for (int k = 0; k < (int)sizeof(T) / 4; ++k)
+      w[k] = __hip_atomic_load(p + k, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  __device__ __forceinline__ bool ready(unsigned int tag) const {
+    bool ok = true;
+#pragma unroll
+    for (int k = 0; k < (int)sizeof(T) / 4; ++k) ok = ok && (unsigned int)(w[k] >> 32) == tag;
+    return ok;
+  }
+  __device__ __forceinline__ T value() const {
+    if constexpr (sizeof(T) == 4) return __builtin_bit_cast(T, (unsigned int)w[0]);
+    else return __builtin_bit_cast(T, (w[1] << 32) | (w[0] & 0xffffffffULL));
+  }
 };
 
-// Stage NA arrays of the tile (dst[q][t][c] = src[q](i0 + t, j0 + c); the
-// rows of each dst contiguous) and NE edge vectors straight from memory into
-// LDS with LDS-direct loads, every load issued before one wait, no registers
-// held.  Lanes whose element lies off the map read a clamped in-map element
-// instead, and those entries are then overwritten with 0 (1 for array
-// q == one) or the edge's `outside`.
-template <typename T, int NA, int NE>
-__device__ __forceinline__ void wf_stage(T (*const (&dst)[NA])[kWT], const gptr<T> (&src)[NA],
-                                         int one, const WEdge<T> (&edge)[NE], const WTile& w) {
-  constexpr int kParts = sizeof(T) / 4;  // instructions per row
-  // one wave can keep at most 63 loads in flight, so every wave of the block
-  // takes its share of the rows (wave wv: rows wv, wv + kWWaves, ...)
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  using gbyte = const __attribute__((address_space(1))) unsigned char*;
+template <typename T>
+struct alignas(2 * sizeof(T)) Pair {
+  T a, b;
+};
+
+// The lane, opaque: what a role derives from it is formed in that role, not
+// ahead of the branch to it for every role at once.
+__device__ __forceinline__ int wf_lane() {
+  int l = threadIdx.x & 63;
+  __asm__ volatile("" : "+v"(l));
+  return l;
+}
+
+// A wave-uniform value read from memory, in scalar registers.
+__device__ __forceinline__ long long wf_uniform(long long v) {
+  const unsigned int lo = __builtin_amdgcn_readfirstlane((int)(v & 0xffffffffLL));
+  return ((long long)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32) | lo;
+}
+
+// Every wave of the workgroup, at whatever place in its own role's loop.
+__device__ __forceinline__ void wf_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+}
+
+// Sizes per element type: C steps of a chunk, V elements of 16 bytes, L lanes
+// for a row's share of a chunk, H rows per instruction (a group), GL and GS
+// groups per loader and storer wave, R steps of the operand ring.
+template <typename T>
+struct WSize {
+  static constexpr int C = 16, V = 16 / sizeof(T), L = C / V, H = 64 / L;
+  static constexpr int GL = kWT / H / kWLoad, GS = kWT / H / kWStore, R = kWRing * C;
+};
+template <typename T>
+using wvec = T __attribute__((ext_vector_type(16 / sizeof(T)), aligned(sizeof(T))));
+
+// The elements of chunk q that a lane of a loader or storer wave handles: in
+// group g of its G, the 16 bytes (l mod L) of row H (g0 + g) + l / L's run of C
+// elements.  Along the sweep
+// the run starts at column q C + dl - row, i.e. at step q C + dl with
+// dl = 0 .. C - 1 such that it is aligned in memory.  at[g]: offset of
+// the lane's 16 bytes at q = 0 from the strip's base; it moves C per chunk
+// with the sweep.  Rows past the map take row 0's place (and are dropped).
+template <typename T, bool REV, int G>
+struct WLanes {
+  int dl[G];
+  unsigned int at[G];
+  int lr, sub;  // row of group 0, first element within the run
+
+  __device__ __forceinline__ WLanes(int l, int g0, int rows, int N, long long base) {
+    constexpr int C = WSize<T>::C, V = WSize<T>::V, L = WSize<T>::L, H = WSize<T>::H;
+    lr = H * g0 + l / L;
+    sub = l % L * V;
+    // element index (mod C) of the strip's first pixel along the sweep
+    const int e0 = (int)((REV ? base + (long long)kWT * N - 1 : base) & (C - 1));
 #pragma unroll
-  for (int e = 0; e < NE; ++e) {
-    if (e % kWWaves != wv) continue;
-#pragma unroll
-    for (int h = 0; h < kParts; ++h) {
-      const int dw = h * 64 + l, t = dw / kParts, part = dw % kParts;
-      bool ok;
-      const size_t at = wf_at(w.i0 + t * edge[e].di + edge[e].oi, w.j0 + t * edge[e].dj + edge[e].oj,
-                              w.M, w.N, ok);
-      __builtin_amdgcn_global_load_lds((gbyte)edge[e].src + at * sizeof(T) + part * 4,
-                                       (lptr)((unsigned char*)edge[e].dst + h * 256), 4, 0, 0);
+    for (int g = 0; g < G; ++g) {
+      const int r = H * g + lr, row = r < rows ? r : 0;
+      dl[g] = (REV ? row + e0 - row * N + 1 : row - e0 - row * N) & (C - 1);
+      at[g] = REV ? (unsigned int)((kWT - row) * N + row - dl[g] - sub - V)
+                  : (unsigned int)(row * N - row + dl[g] + sub);
     }
   }
-  // A tile wholly inside the map whose rows start 16-byte aligned goes in
-  // 16-byte pieces, kVR rows per instruction (lane l: row l / (64 / kVR) of
-  // the group, piece l % (64 / kVR)); the rest dword by dword, clamped.
-  bool vec = w.i0 + kWT <= w.M && w.j0 + kWT <= w.N && (w.N * sizeof(T)) % 16 == 0;
+  __device__ __forceinline__ int row(int g) const { return WSize<T>::H * g + lr; }
+  // step (counted from chunk q's first) and column of the lane's element e
+  __device__ __forceinline__ int step(int g, int e) const { return dl[g] + sub + e; }
+  __device__ __forceinline__ int col(int q, int g, int e) const {
+    return q * WSize<T>::C + step(g, e) - row(g);
+  }
+  // Keeps what the accessors derive from being held in registers across the
+  // whole sweep (it is cheaper to form again per chunk than to spill).
+  __device__ __forceinline__ void fresh() { __asm__ volatile("" : "+v"(lr), "+v"(sub)); }
+  // element e of a vector in memory order
+  static __device__ __forceinline__ int mem(int e) { return REV ? WSize<T>::V - 1 - e : e; }
+};
+
+// Whether every lane's 16 bytes of chunk q lie in the map's array (they may
+// reach into neighbouring rows): all but chunk -1 of the first strip and the
+// last few chunks of the last strip (or strips, on maps a few pixels wide).
+// wf_last: the last such chunk.
+template <typename T>
+__device__ __forceinline__ int wf_last(int strip, int rows, int M, int N) {
+  constexpr int C = WSize<T>::C;
+  const long long room = (long long)(M - strip * kWT - rows + 1) * N + (rows - 1) - 2 * C;
+  return room < 0 ? -2 : (int)min(room / C, (long long)1 << 20);
+}
+
+// Whether every element of chunk q and its east neighbour lie in the map's
+// strip.
+template <typename T>
+__device__ __forceinline__ bool wf_inner(int q, int rows, int N) {
+  constexpr int C = WSize<T>::C;
+  return rows == kWT && q * C >= kWT - 1 && (q + 2) * C < N;
+}
+
+// ---------------------------------------------------------------------------
+// The pivots, the forward solve (P + L) y = r or the backward solve
+// (P + L^T) z = P y with s = c z and the strips' partials of r^T s.
+//   Operands of a step, as two pairs per lane:
+//     pivots   {U, V}, {U_west, V_north}
+//     forward  {r, 1 / p}, {U_west, V_north}
+//     backward {y, 1 / p}, {U, V}
+// (a loader writes an element's U as its row's west coupling of the next step
+// and its V as the next row's north coupling of that step).  Off the map they are 0 (1 / p:
+// 1), which keeps every value there from reaching a pixel of the map, so the
+// sweeping wave has no conditions.
+// ---------------------------------------------------------------------------
+template <typename T, int MODE>
+__global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(WArgs a) {
+  using W = WSize<T>;
+  constexpr int C = W::C, V16 = W::V, kGL = W::GL, kGS = W::GS;
+  __shared__ Pair<T> pa[W::R][kWPitch], pb[W::R][kWPitch];
+  __shared__ T yo[kWOut * C][kWPitch];  // results
+  __shared__ T yb[W::R];                // the row above the strip
+  __shared__ double yr[MODE == kWPivots ? W::R : 1];  // pivots: its reciprocals
+  __shared__ double red[kWThreads / 64 * 3];
+  __shared__ int sh_ticket, fflag;
+  constexpr T kOff = MODE == kWPivots ? T(1) : T(0);  // value off the map
+  constexpr bool kRev = MODE == kWBackward;           // the sweep runs from the map's last pixel
+  constexpr int kWords = sizeof(T) / 4;               // words of an edge entry
+  const int tid = threadIdx.x;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n_strips = a.counts[4];
+  const unsigned int tag = a.ctl[2] + 1u;
+  const bool one_each = (int)gridDim.x >= n_strips;
+  for (;;) {
+    if (tid == 0)
+      sh_ticket = (int)__hip_atomic_fetch_add(a.ctl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    const int tk = __builtin_amdgcn_readfirstlane(sh_ticket);
+    if (tk >= n_strips) break;
+    const int m = __builtin_amdgcn_readfirstlane(a.slist[2 * tk]);
+    const int strip = __builtin_amdgcn_readfirstlane(a.slist[2 * tk + 1]);
+    const MapDesc& d = a.desc[m];
+    const int M = __builtin_amdgcn_readfirstlane(d.M), N = __builtin_amdgcn_readfirstlane(d.N);
+    const int state = a.ms[m].state;
+    if (a.expect < 0 || state == a.expect) {
+      const int n_map = (M + kWT - 1) / kWT;  // strips of this map
+      const int rows = min(kWT, M - strip * kWT);
+      const int nc = (N + kWT - 1 + C - 1) / C;
+      // the strip's base: offsets are row * N + column (backward: counted from
+      // the first pixel of the strip's 64 rows in memory; the base may lie
+      // before the map, no accessed element does)
+      const long long base =
+          wf_uniform(d.off) + (kRev ? (long long)(M - (strip + 1) * kWT) : (long long)strip * kWT) * N;
+      const int q_last = wf_last<T>(strip, rows, M, N);
+      auto in_array = [&](int q) { return (q >= 0 || strip > 0) && q <= q_last; };
+      unsigned long long* edge = a.edge + wf_uniform(d.edge0) + (size_t)strip * N * 2;
+      double part = 0.0;
+
+      // Roles: wave 0 sweeps, waves 1..3 and 5 load, wave 4 polls (it shares
+      // wave 0's SIMD and has the least to issue), waves 6 and 7 store.  At
+      // iteration n chunk n is swept, chunk n + 2 written to LDS (its lines
+      // reach into chunk n + 3's steps) and the lines that end in chunk n - 1
+      // stored.
+      if (wv == 0) {
+        const int l = wf_lane();
+        wf_barrier();
+        __builtin_amdgcn_s_setprio(3);
+        T own = kOff;
+        Pair<T> oa[kWAhead], ob[kWAhead];
+        T of[kWAhead];
+        double rown = 1.0, orf[kWAhead];  // pivots: 1 / own, and of the row above
 #pragma unroll
-  for (int q = 0; q < NA; ++q) vec = vec && ((size_t)src[q] & 15) == 0;
-  if (vec) {
-    constexpr int kVR = 64 * 16 / (kWT * (int)sizeof(T));  // rows per instruction
-    const int sub = l / (64 / kVR), piece = l % (64 / kVR);
+        for (int u = 0; u < kWAhead; ++u) {
+          oa[u] = pa[u][l], ob[u] = pb[u][l], of[u] = yb[u];
+          if (MODE == kWPivots) orf[u] = yr[u];
+        }
+        int b = 0, ob3 = 0;
+        for (int n = 0; n < nc; ++n) {
+          const int bn = (b + C) & (W::R - 1);
 #pragma unroll
-    for (int q = 0; q < NA; ++q) {
-      for (int g = wv; g < kWT / kVR; g += kWWaves) {
-        const int t = g * kVR + sub;
-        const size_t at = (size_t)(w.i0 + t) * w.N + w.j0;
-        __builtin_amdgcn_global_load_lds((gbyte)src[q] + at * sizeof(T) + piece * 16,
-                                         (lptr)&dst[q][g * kVR][0], 16, 0, 0);
+          for (int u = 0; u < C; ++u) {
+            const int k = u % kWAhead;
+            const T up = from_prev_lane(of[k], own);  // lane 0: the row above the strip
+            T v;
+            if (MODE == kWPivots) {
+              const T uw = ob[k].a, vn = ob[k].b;
+              const T av = uw + oa[k].a + vn + oa[k].b;
+              v = av;
+              const double rup = from_prev_lane(orf[k], rown);
+              const T qw = quot(uw * uw, own, rown), qn = quot(vn * vn, up, rup);
+              v = uw != T(0) ? v - qw : v;
+              v = vn != T(0) ? v - qn : v;
+              if (v < (T)kPivotFloor * av) v = av;
+              if (av == T(0)) v = T(1);
+              rown = rcp_full((double)v);
+            } else if (MODE == kWForward) {
+              v = fma_t(ob[k].a, own, fma_t(ob[k].b, up, oa[k].a)) * oa[k].b;
+            } else {
+              v = fma_t(fma_t(ob[k].a, own, ob[k].b * up), oa[k].b, oa[k].a);
+            }
+            yo[ob3 + u][l] = v;
+            own = v;
+            const int f = (u + kWAhead) % C, fb = u + kWAhead < C ? b : bn;
+            oa[k] = pa[fb + f][l];
+            ob[k] = pb[fb + f][l];
+            of[k] = yb[fb + f];
+            if (MODE == kWPivots) orf[k] = yr[fb + f];
+          }
+          b = bn;
+          ob3 = ob3 == (kWOut - 1) * C ? 0 : ob3 + C;
+          wf_barrier();
+        }
+        __builtin_amdgcn_s_setprio(0);
+        wf_barrier();
+        wf_barrier();
+      } else if (wv < 4 || wv == 5) {
+        const int l = wf_lane();
+        // raw operands of a chunk, held from the load to the write
+        struct Held {
+          wvec<T> f[4][kGL];
+        };
+        Held h0{}, h1{}, h2{};
+        const T* U = reinterpret_cast<const T*>(a.U) + base;
+        const T* V = reinterpret_cast<const T*>(a.V) + base;
+        const T* P = reinterpret_cast<const T*>(a.piv) + base;
+        const T* R = reinterpret_cast<const T*>(kRev ? a.y : a.r) + base;
+        WLanes<T, kRev, kGL> ln(l, (wv == 5 ? 3 : wv - 1) * kGL, rows, N, base);
+        // (past the last chunk the last one is loaded again: every iteration
+        // issues as many loads, or the wait for a chunk's would have to cover
+        // the chunks requested after it as well)
+        auto load = [&](auto fast, int q, Held& h) {
+          q = min(q, nc - 1);
+          ln.fresh();
+          const long long qo = kRev ? -(long long)q * C : (long long)q * C;
+          if (decltype(fast)::value || in_array(q)) {
+#pragma unroll
+            for (int g = 0; g < kGL; ++g) {
+              h.f[2][g] = *reinterpret_cast<const wvec<T>*>(U + qo + ln.at[g]);
+              h.f[3][g] = *reinterpret_cast<const wvec<T>*>(V + qo + ln.at[g]);
+              if (MODE != kWPivots) {
+                h.f[0][g] = *reinterpret_cast<const wvec<T>*>(R + qo + ln.at[g]);
+                h.f[1][g] = *reinterpret_cast<const wvec<T>*>(P + qo + ln.at[g]);
+              }
+            }
+            return;
+          }
+#pragma unroll
+          for (int g = 0; g < kGL; ++g) {
+#pragma unroll
+            for (int e = 0; e < V16; ++e) {
+              const int row = ln.row(g), c = ln.col(q, g, e), x = ln.mem(e);
+              const bool ok = row < rows && (unsigned)c < (unsigned)N;
+              // row 0 column 0 of the strip for the elements off the map
+              const int rw = ok ? row : 0, cl = ok ? c : 0;
+              const unsigned int o = kRev ? (kWT - 1 - rw) * N + (N - 1 - cl) : rw * N + cl;
+              h.f[2][g][x] = U[o];
+              h.f[3][g][x] = V[o];
+              if (MODE != kWPivots) {
+                h.f[0][g][x] = R[o];
+                h.f[1][g][x] = P[o];
+              }
+            }
+          }
+        };
+        auto stash = [&](int q, const Held& h) {
+          if (q >= nc) return;
+          ln.fresh();
+          const bool inner = wf_inner<T>(q, rows, N);
+#pragma unroll
+          for (int g = 0; g < kGL; ++g) {
+#pragma unroll
+            for (int e = 0; e < V16; ++e) {
+              const int row = ln.row(g), c = ln.col(q, g, e), x = ln.mem(e);
+              const int at = (q * C + ln.step(g, e)) & (W::R - 1);
+              T u = h.f[2][g][x], v = h.f[3][g][x], w = u;
+              Pair<T> p;
+              if (MODE != kWPivots) p = {h.f[0][g][x], h.f[1][g][x]};
+              if (!inner) {
+                const bool ok = row < rows && (unsigned)c < (unsigned)N;
+                u = ok ? u : T(0);
+                v = ok ? v : T(0);
+                w = c < N - 1 ? u : T(0);
+                p = {ok ? p.a : T(0), ok ? p.b : T(1)};
+              }
+              if (kRev) {
+                pa[at][row] = p;
+                pb[at][row] = {u, v};
+              } else {
+                pa[at][row] = MODE == kWPivots ? Pair<T>{u, v} : p;
+                const int next = (at + 1) & (W::R - 1);
+                pb[next][row].a = w;
+                pb[next][row + 1].b = v;
+              }
+            }
+          }
+        };
+        // lines of chunk -1 reach into chunk 0's steps
+        const std::false_type any{};
+        load(any, -1, h0);
+        load(any, 0, h1);
+        load(any, 1, h2);
+        stash(-1, h0);
+        load(any, 2, h0);
+        stash(0, h1);
+        load(any, 3, h1);
+        stash(1, h2);
+        load(any, 4, h2);
+        wf_barrier();
+        int n = 0;
+        auto iteration = [&](auto fast, Held& h) {
+          stash(n + 2, h);
+          load(fast, n + 2 + kWHeld, h);
+          wf_barrier();
+          return n++ < nc + 1;
+        };
+        // with no other form of load in the loop, the wait for a chunk leaves
+        // the two requested after it in flight
+        const std::true_type fast{};
+        const int n_fast = q_last >= nc - 1 ? nc + 2 : q_last - (2 + kWHeld) + 1;
+        while (n + kWHeld <= n_fast) {
+          iteration(fast, h0);
+          iteration(fast, h1);
+          iteration(fast, h2);
+        }
+        while (n <= nc + 1 && iteration(any, h0) && iteration(any, h1) && iteration(any, h2)) {
+        }
+      } else if (wv == 4) {
+        const int l = wf_lane();
+        // the strip above's last row: its values, and the couplings to it.  A
+        // chunk's are requested an iteration before they are looked at (a
+        // round trip), and asked for again until they are there.
+        const unsigned long long* above = edge - (size_t)N * 2;
+        const T* Va = reinterpret_cast<const T*>(a.V) + base - N;
+        bool lost = false;
+        Edge<T> ew;
+        T vn = T(0);
+        // the column of this lane in chunk q, or a valid one (whose values are
+        // not used) for lanes without any
+        auto column = [&](int q) { return min(q * C + min(l, C - 1), N - 1); };
+        auto request = [&](int q) {
+          if (strip == 0) return;
+          ew.read(above + (size_t)column(q) * kWords);
+          if (!kRev) vn = Va[column(q)];
+        };
+        auto take = [&](int q) {
+          const int c = q * C + l;
+          const bool mine = strip > 0 && l < C && c < N;
+          T v = kOff;
+          if (strip > 0) {
+            bool need = mine;
+            for (int k = 0;; ++k) {
+              if (need && ew.ready(tag)) v = ew.value(), need = false;
+              if (__builtin_amdgcn_ballot_w64(need) == 0) break;
+              if (lost || k >= kWMaxPolls) {
+                if (need) v = T(__builtin_nanf(""));
+                lost = true;
+                break;
+              }
+              ew.read(above + (size_t)column(q) * kWords);
+            }
+          }
+          if (l < C) {
+            yb[c & (W::R - 1)] = v;
+            if (MODE == kWPivots) yr[c & (W::R - 1)] = rcp_full((double)v);
+            if (!kRev) pb[c & (W::R - 1)][0].b = mine ? vn : T(0);
+          }
+        };
+        request(0);
+        take(0);
+        request(1);
+        take(1);
+        request(2);
+        wf_barrier();
+        for (int n = 0; n <= nc + 1; ++n) {
+          if (n + 2 < nc) {
+            take(n + 2);
+            request(n + 3);
+          }
+          wf_barrier();
+        }
+      } else {
+        const int l = wf_lane(), st = wv - 6;
+        struct Held {
+          wvec<T> r[kGS];
+        };
+        Held h0{}, h1{}, h2{};  // backward: r of the lines to store next
+        const T* R = reinterpret_cast<const T*>(a.r) + base;
+        T* out = reinterpret_cast<T*>(MODE == kWPivots ? const_cast<void*>(a.piv)
+                                                       : (kRev ? a.s : a.y)) + base;
+        const T scale = a.ssor ? (T)(2.0 - a.omega) : T(1);
+        WLanes<T, kRev, kGS> ln(l, st * kGS, rows, N, base);
+        auto load_r = [&](auto fast, int q, Held& h) {
+          if (!kRev) return;
+          q = min(q, nc - 1);  // every iteration issues as many loads
+          ln.fresh();
+          const long long qo = -(long long)q * C;
+          if (decltype(fast)::value || in_array(q)) {
+#pragma unroll
+            for (int g = 0; g < kGS; ++g)
+              h.r[g] = *reinterpret_cast<const wvec<T>*>(R + qo + ln.at[g]);
+            return;
+          }
+#pragma unroll
+          for (int g = 0; g < kGS; ++g) {
+#pragma unroll
+            for (int e = 0; e < V16; ++e) {
+              const int row = ln.row(g), c = ln.col(q, g, e);
+              const bool ok = row < rows && (unsigned)c < (unsigned)N;
+              const int rw = ok ? row : 0, cl = ok ? c : 0;
+              h.r[g][ln.mem(e)] = R[(unsigned int)((kWT - 1 - rw) * N + (N - 1 - cl))];
+            }
+          }
+        };
+        auto store = [&](int q, const Held& h) {
+          ln.fresh();
+          const long long qo = kRev ? -(long long)q * C : (long long)q * C;
+          const bool inner = wf_inner<T>(q, rows, N);
+          const int first = (q + kWOut) % kWOut * C;  // ring place of chunk q's first step
+          wvec<T> w[kGS];  // all reads before the first store
+#pragma unroll
+          for (int g = 0; g < kGS; ++g) {
+#pragma unroll
+            for (int e = 0; e < V16; ++e) {
+              int at = first + ln.step(g, e);
+              at -= at >= kWOut * C ? kWOut * C : 0;
+              w[g][ln.mem(e)] = yo[at][ln.row(g)];
+            }
+          }
+#pragma unroll
+          for (int g = 0; g < kGS; ++g) {
+            if (MODE == kWPivots && a.recip) w[g] = T(1) / w[g];
+            if (kRev) w[g] *= scale;
+          }
+          if (inner) {
+#pragma unroll
+            for (int g = 0; g < kGS; ++g) {
+              *reinterpret_cast<wvec<T>*>(out + qo + ln.at[g]) = w[g];
+              if (kRev)
+#pragma unroll
+                for (int e = 0; e < V16; ++e) part += (double)h.r[g][ln.mem(e)] * (double)w[g][ln.mem(e)];
+            }
+            return;
+          }
+#pragma unroll
+          for (int g = 0; g < kGS; ++g) {
+#pragma unroll
+            for (int e = 0; e < V16; ++e) {
+              const int row = ln.row(g), c = ln.col(q, g, e);
+              if (row < rows && (unsigned)c < (unsigned)N) {
+                out[(unsigned int)(kRev ? (kWT - 1 - row) * N + (N - 1 - c) : row * N + c)] =
+                    w[g][ln.mem(e)];
+                if (kRev) part += (double)h.r[g][ln.mem(e)] * (double)w[g][ln.mem(e)];
+              }
+            }
+          }
+        };
+        const std::false_type any{};
+        load_r(any, -1, h0);
+        load_r(any, 0, h1);
+        load_r(any, 1, h2);
+        wf_barrier();  // the preamble's
+        wf_barrier();  // iteration 0: nothing swept yet
+        int n = 1;
+        auto iteration = [&](auto fast, Held& h) {
+          // chunk n - 1 is swept: its last row first, then the lines that end in it
+          if (st == 0 && n - 1 < nc && strip + 1 < n_map && l < C) {
+            const int c = (n - 1) * C + l - (kWT - 1);
+            if ((unsigned)c < (unsigned)N)
+              edge_put(edge + (size_t)c * kWords, tag, yo[(n - 1) % kWOut * C + l][kWT - 1]);
+          }
+          store(n - 2, h);
+          load_r(fast, n - 2 + kWHeld, h);
+          wf_barrier();
+          return n++ < nc + 1;
+        };
+        const std::true_type fast{};
+        const int n_fast = q_last >= nc - 1 ? nc + 2 : q_last + 2 - kWHeld + 1;
+        while (n + kWHeld <= n_fast) {
+          iteration(fast, h0);
+          iteration(fast, h1);
+          iteration(fast, h2);
+        }
+        while (n <= nc + 1 && iteration(any, h0) && iteration(any, h1) && iteration(any, h2)) {
+        }
       }
-    }
-  } else {
+      if (kRev) {
+        part = wf_wave_sum(part);
+        if ((tid & 63) == 0) red[wv] = part;
+        __syncthreads();
+        if (tid == 0) {
+          double tot = 0.0;
 #pragma unroll
-    for (int q = 0; q < NA; ++q) {
-      for (int t = wv; t < kWT; t += kWWaves) {
-#pragma unroll
-        for (int h = 0; h < kParts; ++h) {
-          // dword h * 64 + l of row t's kWT elements
-          const int dw = h * 64 + l, c = dw / kParts, part = dw % kParts;
-          bool ok;
-          const size_t at = wf_at(w.i0 + t, w.j0 + c, w.M, w.N, ok);
-          __builtin_amdgcn_global_load_lds((gbyte)src[q] + at * sizeof(T) + part * 4,
-                                           (lptr)((unsigned char*)&dst[q][t][0] + h * 256), 4, 0,
-                                           0);
+          for (int k = 0; k < kWStore; ++k) tot += red[6 + k];
+          store_partial(a.P + 1 * a.pstride + d.dtile0 + strip, tot);
+        }
+        if (a.fin_mode) {
+          const int sl[1] = {1};
+          __syncthreads();  // red is the finisher's scratch next
+          fused_finish<kFinTailW, 1>(Arrival{a.fcnt, a.gcnt, a.gsum, a.gstride, a.P, a.pstride}, sl,
+                                     d.dtile0, strip, n_map, d.gbd, a.desc, a.ms, m, a.fin_mode, 0,
+                                     &fflag, red);
         }
       }
     }
+    if (one_each) break;
+    __syncthreads();  // the ticket has been read by every wave
   }
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < NE; ++e) {
-    if (e % kWWaves != wv) continue;
-    bool ok;
-    (void)wf_at(w.i0 + l * edge[e].di + edge[e].oi, w.j0 + l * edge[e].dj + edge[e].oj, w.M, w.N, ok);
-    if (!ok) edge[e].dst[l] = edge[e].outside;
-  }
-  if (w.i0 + kWT > w.M || w.j0 + kWT > w.N) {
-    const int j = w.j0 + l;
-    for (int t = wv; t < kWT; t += kWWaves) {
-      if (w.i0 + t < w.M && j < w.N) continue;
-#pragma unroll
-      for (int q = 0; q < NA; ++q) dst[q][t][l] = q == one ? T(1) : T(0);
-    }
-  }
-  __syncthreads();
-}
-
-constexpr int kWR = 8;  // steps between reading a column's operands and using them
-                        // (4: 16.0 us per 1280 x 960 FP64 launch, 6: 15.1, 8: 14.9, 10: 15.0)
-constexpr int kWSteps = (2 * kWT - 1 + kWR - 1) / kWR * kWR;  // wavefront steps, rounded up
-
-// The staged pivots and U of the tile (two 64 x 64 arrays, pivots first, in
-// pu's space) rewritten in place as {1 / p, U} pairs, so the solves multiply
-// (no division on the wavefront's chain) and read both with one instruction.
-// Every thread reads its elements before any is written.
-template <typename T>
-__device__ __forceinline__ void wf_pivot_pairs(T (*pu)[kWT][2]) {
-  constexpr int kPer = kWT / kWWaves;
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const T* staged = &pu[0][0][0];
-  T pv[kPer], uv[kPer];
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    const int t = wv + kWWaves * i;
-    pv[i] = staged[t * kWT + l];
-    uv[i] = staged[kWT * kWT + t * kWT + l];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kPer; ++i) {
-    const int t = wv + kWWaves * i;
-    pu[t][l][0] = T(1) / pv[i];
-    pu[t][l][1] = uv[i];
-  }
-  __syncthreads();
-}
-
-// Rows of the tile back to memory, every wave taking its share.
-template <typename T>
-__device__ __forceinline__ void wf_store(T* out, const T (*src)[kWT], const WTile& w) {
-  const int l = threadIdx.x & 63, wv = threadIdx.x >> 6, j = w.j0 + l;
-  for (int t = wv; t < kWT; t += kWWaves) {
-    const int i = w.i0 + t;
-    if (i < w.M && j < w.N) out[(size_t)i * w.N + j] = src[t][l];
+  // the last workgroup to leave rearms the counters and ends the epoch (every
+  // workgroup read it before it left)
+  if (tid == 0 && __hip_atomic_fetch_add(a.ctl + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                      gridDim.x - 1) {
+    __hip_atomic_store(a.ctl, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(a.ctl + 1, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_add(a.ctl + 2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
-// ---------------------------------------------------------------------------
-// ILU(0) pivots, one anti-diagonal of tiles.  Lane l walks row l; the west
-// coupling U(i, j-1) is the U it read one step earlier, the north coupling
-// V(i-1, j) and pivot come from lane l-1's previous step.
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(kWThreads) k_wf_pivots(WArgs a) {
-  __shared__ __attribute__((aligned(16))) T Us[kWT][kWT], Vs[kWT][kWT];
-  __shared__ T left[kWT], top[kWT], ul[kWT], vt[kWT];
-  WTile w;
-  if (!wf_tile<false>(a, w)) return;
-  const gptr<T> U = (gptr<T>)(reinterpret_cast<const T*>(a.U) + w.off);
-  const gptr<T> V = (gptr<T>)(reinterpret_cast<const T*>(a.V) + w.off);
-  T* piv = reinterpret_cast<T*>(const_cast<void*>(a.piv)) + w.off;
-  const int l = threadIdx.x & 63;
-  {
-    T (*const dst[2])[kWT] = {Us, Vs};
-    const gptr<T> src[2] = {U, V};
-    const WEdge<T> edge[4] = {{left, (gptr<T>)piv, 1, 0, 0, -1, T(1)},
-                              {top, (gptr<T>)piv, 0, 1, -1, 0, T(1)},
-                              {ul, U, 1, 0, 0, -1, T(0)},
-                              {vt, V, 0, 1, -1, 0, T(0)}};
-    wf_stage<T, 2, 4>(dst, src, -1, edge, w);
-  }
-  // wave 0, lane l owns tile row l; at step k it computes column k - l (the
-  // pivot overwrites Us there, whose value it has read)
-  // Row 0's north neighbours (the tile above) are held one per lane and
-  // broadcast by lane index, so no LDS read sits on the chain.
-  if (threadIdx.x < 64) {
-  const T top_l = top[l], vt_l = vt[l];
-  T pw = left[l], pn = T(1), vn_own = T(0), uwest = ul[l];
-  T nu = T(0), nv = T(0);
-  if (l == 0) nu = Us[0][0], nv = Vs[0][0];
-  for (int k = 0; k < 2 * kWT - 1; ++k) {
-    const int c = k - l;
-    const T ue = nu, vs = nv;
-    const int cn = (c + 1) & (kWT - 1);  // wrapped for idle steps, as in the forward solve
-    nu = Us[l][cn], nv = Vs[l][cn];
-    const T p_above = from_prev_lane(pn);
-    const T v_above = from_prev_lane(vn_own);
-    const int k0 = min(k, kWT - 1);
-    const T top_k = lane_value(top_l, k0), vt_k = lane_value(vt_l, k0);
-    if (c >= 0 && c < kWT) {
-      const T uw = uwest, vn = l == 0 ? vt_k : v_above;
-      const T pup = l == 0 ? top_k : p_above;
-      const T av = uw + ue + vn + vs;
-      T pv;
-      if (av == T(0)) {
-        pv = T(1);
-      } else {
-        T v = av;
-        if (uw != T(0)) v -= uw * uw / pw;
-        if (vn != T(0)) v -= vn * vn / pup;
-        if (v < (T)kPivotFloor * av) v = av;
-        pv = v;
-      }
-      Us[l][c] = pv;
-      pw = pv;
-      pn = pv;
-      vn_own = vs;
-      uwest = ue;
-    }
-  }
-  }
-  __syncthreads();
-  wf_store<T>(piv, Us, w);
-}
-
-// SSOR "pivots" D / omega are pointwise: every active map, grid-stride.
+// SSOR "pivots" D / omega are pointwise (stored as 1 / p like the ILU ones):
+// every active map, grid-stride.
 template <typename T>
 __global__ void __launch_bounds__(256) k_wf_ssor_diag(WArgs a) {
   if ((int)blockIdx.y >= a.counts[2]) return;
@@ -374,181 +702,7 @@ __global__ void __launch_bounds__(256) k_wf_ssor_diag(WArgs a) {
        p += (long long)gridDim.x * blockDim.x) {
     const int i = (int)(p / N), j = (int)(p % N);
     const T dg = (j > 0 ? U[p - 1] : T(0)) + U[p] + (i > 0 ? V[p - N] : T(0)) + V[p];
-    piv[p] = dg == T(0) ? T(1) : dg / (T)a.omega;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Forward solve (P + L) y = r, one anti-diagonal of tiles
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(kWThreads) k_wf_forward(WArgs a) {
-  // sm[0]: r, overwritten by y; sm[1]: V.  Row 0 of each holds the row
-  // above the tile (its y and V), rows 1..64 the tile, so one instruction
-  // reads a lane's operand and the value above it, and both arrays are read
-  // from one address.  pu: {1 / p, U} pairs of the tile.
-  __shared__ __attribute__((aligned(16))) T sm[2][kWT + 1][kWT];
-  __shared__ __attribute__((aligned(16))) T pu[kWT][kWT][2];
-  __shared__ T left[kWT], ul[kWT];
-  WTile w;
-  if (!wf_tile<false>(a, w)) return;
-  const gptr<T> U = (gptr<T>)(reinterpret_cast<const T*>(a.U) + w.off);
-  const gptr<T> V = (gptr<T>)(reinterpret_cast<const T*>(a.V) + w.off);
-  const gptr<T> piv = (gptr<T>)(reinterpret_cast<const T*>(a.piv) + w.off);
-  const gptr<T> r = (gptr<T>)(reinterpret_cast<const T*>(a.r) + w.off);
-  T* y = reinterpret_cast<T*>(a.y) + w.off;
-  const int l = threadIdx.x & 63;
-  {
-    T* const stg = &pu[0][0][0];
-    T (*const dst[4])[kWT] = {&sm[0][1], reinterpret_cast<T (*)[kWT]>(stg),
-                              reinterpret_cast<T (*)[kWT]>(stg + kWT * kWT), &sm[1][1]};
-    const gptr<T> src[4] = {r, piv, U, V};
-    const WEdge<T> e[4] = {{left, (gptr<T>)y, 1, 0, 0, -1, T(0)},
-                           {&sm[0][0][0], (gptr<T>)y, 0, 1, -1, 0, T(0)},
-                           {ul, U, 1, 0, 0, -1, T(0)},
-                           {&sm[1][0][0], V, 0, 1, -1, 0, T(0)}};
-    wf_stage<T, 4, 4>(dst, src, 1, e, w);
-  }
-  wf_pivot_pairs<T>(pu);
-  // Wave 0 runs the wavefront, lane l on tile row l.  The operands of
-  // column c + kWR are read kWR steps ahead into a ring of registers (each
-  // slot refilled after its step used it), so the recurrence never waits for
-  // LDS.  A lane with no column at a step reads column c mod 64 of its row
-  // and ignores the value: a wrapped column keeps the wave's reads in
-  // distinct banks (lane l reads word 63 l + const of the tile), where a
-  // clamped one would put every such lane on one column, a single bank.  The
-  // north neighbours come from lane l - 1's previous step by a DPP shift;
-  // lane 0 keeps the values above the tile, which its reads of the row above
-  // its own fetched.
-  if (threadIdx.x < 64) {
-  T y_own = left[l], uwest = ul[l];
-  T ra[kWR], rr[kWR], va[kWR], vv[kWR], pp[kWR], uu[kWR];
-  auto fetch = [&](int u, int col) {
-    ra[u] = sm[0][l][col], rr[u] = sm[0][l + 1][col];
-    va[u] = sm[1][l][col], vv[u] = sm[1][l + 1][col];
-    pp[u] = pu[l][col][0], uu[u] = pu[l][col][1];
-  };
-#pragma unroll
-  for (int u = 0; u < kWR; ++u) fetch(u, (u - l) & (kWT - 1));
-  // The north coupling V(l - 1, c) a lane uses at a step is lane l - 1's
-  // own operand of the previous step, shifted at the end of that step before
-  // its slot is refilled (lane 0: the row above's, from the next slot).
-  T vn = va[0];
-  for (int k0 = 0; k0 < kWSteps; k0 += kWR) {
-#pragma unroll
-    for (int u = 0; u < kWR; ++u) {
-      const int c = k0 + u - l;
-      const T yup = from_prev_lane(ra[u], y_own);  // lane 0: y of the row above, column k
-      if (c >= 0 && c < kWT) {
-        const T v = (rr[u] + vn * yup + uwest * y_own) * pp[u];  // pp = 1 / p
-        sm[0][l + 1][c] = v;
-        y_own = v;
-        uwest = uu[u];
-      }
-      vn = from_prev_lane(va[(u + 1) % kWR], vv[u]);
-      fetch(u, (c + kWR) & (kWT - 1));
-    }
-  }
-  }
-  __syncthreads();
-  wf_store<T>(y, &sm[0][1], w);
-}
-
-// ---------------------------------------------------------------------------
-// Backward solve (P + L^T) z = P y (z overwrites y), s = c z, and the tile's
-// FP64 partial of r^T s; one anti-diagonal of tiles from the bottom-right
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ void __launch_bounds__(kWThreads) k_wf_backward(WArgs a) {
-  // sm rows 0..63: y of the tile, overwritten by z; row 64: z of the row
-  // below the tile; rows 65..128: V of the tile (so a lane's operand, the
-  // value below it and its V are read from one address).  pu: {1 / p, U}.
-  __shared__ __attribute__((aligned(16))) T sm[2 * kWT + 1][kWT];
-  __shared__ __attribute__((aligned(16))) T pu[kWT][kWT][2];
-  __shared__ T right[kWT];
-  __shared__ double red[kWWaves];
-  T (*const Yz)[kWT] = sm;
-  WTile w;
-  if (!wf_tile<true>(a, w)) return;
-  const gptr<T> U = (gptr<T>)(reinterpret_cast<const T*>(a.U) + w.off);
-  const gptr<T> V = (gptr<T>)(reinterpret_cast<const T*>(a.V) + w.off);
-  const gptr<T> piv = (gptr<T>)(reinterpret_cast<const T*>(a.piv) + w.off);
-  const gptr<T> r = (gptr<T>)(reinterpret_cast<const T*>(a.r) + w.off);
-  T* s = reinterpret_cast<T*>(a.s) + w.off;
-  T* y = reinterpret_cast<T*>(a.y) + w.off;
-  const int M = w.M, N = w.N, l = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  {
-    T* const stg = &pu[0][0][0];
-    T (*const dst[4])[kWT] = {&sm[0], reinterpret_cast<T (*)[kWT]>(stg),
-                              reinterpret_cast<T (*)[kWT]>(stg + kWT * kWT), &sm[kWT + 1]};
-    const gptr<T> src[4] = {(gptr<T>)y, piv, U, V};
-    const WEdge<T> edge[2] = {{right, (gptr<T>)y, 1, 0, 0, kWT, T(0)},
-                              {&sm[kWT][0], (gptr<T>)y, 0, 1, kWT, 0, T(0)}};
-    wf_stage<T, 4, 2>(dst, src, 1, edge, w);
-  }
-  wf_pivot_pairs<T>(pu);
-  // r for the closing r^T s (wave wv: rows wv, wv + kWWaves, ...), requested
-  // before the wavefront so its latency hides behind the chain
-  constexpr int kRows = kWT / kWWaves;
-  const int j = w.j0 + l;
-  const int dt0 = a.desc[w.m].dtile0;
-  T rv[kRows];
-#pragma unroll
-  for (int u = 0; u < kRows; ++u) rv[u] = wf_ld<T>(r, w.i0 + wv + u * kWWaves, j, M, N, T(0));
-  // wave 0, lane l owns tile row 63 - l; at step k it computes column
-  // 63 - (k - l); operands read kWR steps ahead, and lane 0's south
-  // neighbours (the row below the tile) carried as in the forward solve
-  if (threadIdx.x < 64) {
-  const int row = kWT - 1 - l;
-  T z_own = right[row];
-  T yy[kWR], yb[kWR], vv[kWR], pp[kWR], uu[kWR];
-  auto fetch = [&](int u, int col) {
-    yy[u] = sm[row][col], yb[u] = sm[row + 1][col], vv[u] = sm[kWT + 1 + row][col];
-    pp[u] = pu[row][col][0], uu[u] = pu[row][col][1];
-  };
-#pragma unroll
-  for (int u = 0; u < kWR; ++u) fetch(u, (kWT - 1 - (u - l)) & (kWT - 1));  // wrapped as forward
-  for (int k0 = 0; k0 < kWSteps; k0 += kWR) {
-#pragma unroll
-    for (int u = 0; u < kWR; ++u) {
-      const int c = kWT - 1 - (k0 + u - l);
-      const T zdown = from_prev_lane(yb[u], z_own);  // lane 0: z of the row below, column 63 - k
-      if (c >= 0 && c < kWT) {
-        const T v = yy[u] + (uu[u] * z_own + vv[u] * zdown) * pp[u];  // pp = 1 / p
-        Yz[row][c] = v;
-        z_own = v;
-      }
-      fetch(u, (c - kWR) & (kWT - 1));
-    }
-  }
-  }
-  __syncthreads();
-  // z back to y, s = c z, and the tile's partial of r^T s (wave wv: rows wv,
-  // wv + kWWaves, ...; the waves' sums added in a fixed order)
-  const T scale = a.ssor ? (T)(2.0 - a.omega) : T(1);
-  double part = 0.0;
-  T z[kRows];
-#pragma unroll
-  for (int u = 0; u < kRows; ++u) z[u] = Yz[wv + u * kWWaves][l];
-#pragma unroll
-  for (int u = 0; u < kRows; ++u) {
-    const int i = w.i0 + wv + u * kWWaves;
-    if (i < M && j < N) {
-      const size_t p = (size_t)i * N + j;
-      const T sv = scale * z[u];
-      y[p] = z[u];
-      s[p] = sv;
-      part += (double)rv[u] * (double)sv;
-    }
-  }
-  part = wf_wave_sum(part);
-  if (l == 0) red[wv] = part;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    double tot = 0.0;
-#pragma unroll
-    for (int k = 0; k < kWWaves; ++k) tot += red[k];
-    store_partial(a.P + 1 * a.pstride + dt0 + w.local, tot);
+    piv[p] = T(1) / (dg == T(0) ? T(1) : dg / (T)a.omega);
   }
 }
 
@@ -560,8 +714,8 @@ static WArgs make_wargs(const Engine& e, int expect, bool ssor, double omega, co
   WArgs a;
   a.desc = e.desc;
   a.ms = e.ms;
+  a.slist = e.slist;
   a.mact = e.mact;
-  a.mact_cap = e.cap_maps;
   a.counts = e.counts;
   a.P = e.P;
   a.pstride = e.pstride;
@@ -571,55 +725,60 @@ static WArgs make_wargs(const Engine& e, int expect, bool ssor, double omega, co
   a.r = r;
   a.s = s;
   a.y = y;
+  a.ctl = e.wctl;
+  a.edge = e.wedge;
+  a.fcnt = e.fcnt;
+  a.gcnt = e.gcnt;
+  a.gsum = e.gsum;
+  a.gstride = e.gstride;
   a.expect = expect;
-  a.diag = 0;
+  a.fin_mode = 0;
+  a.recip = 1;
   a.omega = omega;
   a.ssor = ssor ? 1 : 0;
   return a;
 }
 
-// Launches per solve: e.wf_diags anti-diagonals (the most any map has), each a
-// grid of (longest diagonal, active maps) one-wave blocks.
+// Strips of a map and entries of its edge buffer.
+int wf_strips(int M) { return (M + kWT - 1) / kWT; }
+
+// Grid of a sweep: the next power of two >= the active strips (few distinct
+// shapes keep captured graphs reusable), capped: workgroups take further
+// strips by ticket.
+int wf_grid(const Engine& e) {
+  int g = 1;
+  while (g < e.act_strips && g < kWMaxGrid) g <<= 1;
+  return g;
+}
+
 template <typename T>
-void e_pivots(hipStream_t st, const Engine& e, int nmaps, bool ssor, double omega) {
+void e_pivots(hipStream_t st, const Engine& e, int nmaps, bool ssor, double omega, bool recip) {
   WArgs a = make_wargs(e, -1, ssor, omega, nullptr, nullptr, nullptr);
-  const int nm = std::max(1, nmaps);
+  a.recip = recip ? 1 : 0;
   if (ssor) {
-    hipLaunchKernelGGL(k_wf_ssor_diag<T>, dim3(64, nm), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(k_wf_ssor_diag<T>, dim3(64, std::max(1, nmaps)), dim3(256), 0, st, a);
     return;
   }
-  for (int d = 0; d < e.wf_diags; ++d) {
-    a.diag = d;
-    hipLaunchKernelGGL(k_wf_pivots<T>, dim3(std::max(1, e.wf_len), nm), dim3(kWThreads), 0, st, a);
-  }
+  hipLaunchKernelGGL((k_wf_sweep<T, kWPivots>), dim3(wf_grid(e)), dim3(kWThreads), 0, st, a);
 }
 
+// s = M^-1 r for the maps in state `expect`; fin_mode != 0 runs the per-map
+// finisher of r^T s in the workgroup that completes the map
 template <typename T>
-void e_sweep(hipStream_t st, const Engine& e, int nmaps, int expect, bool ssor, double omega,
-             const void* r, void* s, void* y) {
+void e_sweep(hipStream_t st, const Engine& e, int expect, bool ssor, double omega, const void* r,
+             void* s, void* y, int fin_mode) {
   WArgs a = make_wargs(e, expect, ssor, omega, r, s, y);
-  const dim3 g(std::max(1, e.wf_len), std::max(1, nmaps));
-  for (int d = 0; d < e.wf_diags; ++d) {
-    a.diag = d;
-    hipLaunchKernelGGL(k_wf_forward<T>, g, dim3(kWThreads), 0, st, a);
-  }
-  for (int d = 0; d < e.wf_diags; ++d) {
-    a.diag = d;
-    hipLaunchKernelGGL(k_wf_backward<T>, g, dim3(kWThreads), 0, st, a);
-  }
+  const dim3 g(wf_grid(e));
+  hipLaunchKernelGGL((k_wf_sweep<T, kWForward>), g, dim3(kWThreads), 0, st, a);
+  a.fin_mode = fin_mode;
+  hipLaunchKernelGGL((k_wf_sweep<T, kWBackward>), g, dim3(kWThreads), 0, st, a);
 }
 
-void wf_shape(int M, int N, int* diags, int* len) {
-  const int ty = (M + kWT - 1) / kWT, tx = (N + kWT - 1) / kWT;
-  *diags = ty + tx - 1;
-  *len = std::min(ty, tx);
-}
-
-template void e_pivots<float>(hipStream_t, const Engine&, int, bool, double);
-template void e_pivots<double>(hipStream_t, const Engine&, int, bool, double);
-template void e_sweep<float>(hipStream_t, const Engine&, int, int, bool, double, const void*, void*,
-                             void*);
-template void e_sweep<double>(hipStream_t, const Engine&, int, int, bool, double, const void*, void*,
-                              void*);
+template void e_pivots<float>(hipStream_t, const Engine&, int, bool, double, bool);
+template void e_pivots<double>(hipStream_t, const Engine&, int, bool, double, bool);
+template void e_sweep<float>(hipStream_t, const Engine&, int, bool, double, const void*, void*, void*,
+                             int);
+template void e_sweep<double>(hipStream_t, const Engine&, int, bool, double, const void*, void*,
+                              void*, int);
 
 }  // namespace lpu

@@ -15,9 +15,10 @@ enum FinOp : int {
   kFinAlpha = 1,    // slot 0: d^T q
   kFinUpdate = 2,   // slots 0,1: r.r, r.s
   kFinConfirm = 3,  // slots 0,1: r.r, r.s
-  kFinTail = 4,     // slot 1 over DCT tiles (or one sweep partial): r.s
+  kFinTail = 4,     // slot 1 over DCT tiles : r.s
   kFinSum2 = 5,     // slots 0,1 over stencil tiles -> rr, bb (no state change)
-  kFinTailS = 6     // slot 1 over stencil tiles (two-colour preconditioners): r.s
+  kFinTailS = 6,    // slot 1 over stencil tiles (two-colour preconditioners): r.s
+  kFinTailW = 7     // slot 1 over the 64-row strips of the natural-order sweeps: r.s
 };
 
 __device__ inline void map_finish(MapState& s, int mode, double rs) {
@@ -214,6 +215,11 @@ __device__ inline void finish_map(const MapDesc* __restrict__ desc, MapState* ms
     double w[1];
     fin_sums<GROUPS, 1>(src, d.dtile0, d.ndt, d.gbd, sl, w, smem);
     v[0] = w[0];
+  } else if (op == kFinTailW) {
+    const int sl[1] = {1};
+    double w[1];
+    fin_sums<GROUPS, 1>(src, d.dtile0, (d.M + 63) / 64, d.gbd, sl, w, smem);
+    v[0] = w[0];
   } else if (op == kFinTailS) {
     const int sl[1] = {1};
     double w[1];
@@ -277,6 +283,7 @@ __device__ inline void finish_map(const MapDesc* __restrict__ desc, MapState* ms
       break;
     case kFinTail:
     case kFinTailS:
+    case kFinTailW:
       s.rs = v[0];
       s.amax[1] = s.amax[2] = s.amax[3] = 0.0f;  // scaled-fp16 maxima of this application
       map_finish(s, mode, v[0]);

@@ -22,10 +22,10 @@ namespace lpu {
 
 // kernels shared with the rest of the library
 template <typename T> void e_diag(hipStream_t, const Engine&, int, bool);
-template <typename T> void e_pivots(hipStream_t, const Engine&, int, bool, double);
+template <typename T> void e_pivots(hipStream_t, const Engine&, int, bool, double, bool);
 template <typename T>
-void e_sweep(hipStream_t, const Engine&, int, int, bool, double, const void*, void*, void*);
-void wf_shape(int M, int N, int* diags, int* len);
+void e_sweep(hipStream_t, const Engine&, int, bool, double, const void*, void*, void*, int);
+int wf_strips(int M);
 template <typename T> void e_tc_pivots(hipStream_t, const Engine&, int, bool, double);
 template <typename T> void e_twocolor(hipStream_t, const Engine&, int, int, bool, double, int);
 
@@ -36,7 +36,11 @@ constexpr int kNoAllocMaxTiles = 1 << 16;
 constexpr size_t al256(size_t b) { return (b + 255) / 256 * 256; }
 constexpr size_t kOffDesc = 0;
 constexpr size_t kOffState = kOffDesc + al256(sizeof(MapDesc));
-constexpr size_t kListInts = kListHead + 1 + kNoAllocMaxTiles;  // counts, one active map, tiles
+constexpr int kNoAllocMaxStrips = (int)(kNoAllocMaxPixels / 64);  // a map one pixel wide
+// edge entries 2 ceil(M / 64) N of a map of at most 4096 columns
+constexpr size_t kNoAllocEdges = 2 * ((size_t)kNoAllocMaxPixels / 64 + 4096);
+// counts, one active map, its strips, tiles
+constexpr size_t kListInts = kListHead + 1 + 2 * (size_t)kNoAllocMaxStrips + kNoAllocMaxTiles;
 constexpr size_t kOffCounts = kOffState + al256(sizeof(MapState));
 constexpr size_t kOffTileMap = kOffCounts + al256(4 * kListInts);
 constexpr size_t kGroups = kNoAllocMaxTiles / kArriveGroup + 8;
@@ -47,7 +51,11 @@ constexpr size_t kOffP = kOffGcnt + al256(4 * kGroups);
 constexpr size_t kOffAux = kOffP + al256(8 * (size_t)kNumSlots * kPstride);
 constexpr size_t kOffT1 = kOffAux + al256(8 * (size_t)kNoAllocMaxPixels);
 constexpr size_t kOffIso = kOffT1 + al256(8 * (size_t)kNoAllocMaxPixels);
-constexpr size_t kScratchBytes = kOffIso + al256((size_t)kNoAllocMaxPixels);
+// the sweeps' launch count and tagged edge values: zero in the image, and kept
+// consistent by the sweeps from call to call
+constexpr size_t kOffCtl = kOffIso + al256((size_t)kNoAllocMaxPixels);
+constexpr size_t kOffEdge = kOffCtl + 256;
+constexpr size_t kScratchBytes = kOffEdge + al256(8 * kNoAllocEdges);
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -77,11 +85,17 @@ static void* scratch_of(int device) {
 // Descriptor, state and tile lists of one M x N map at element offset 0 with
 // `th`-row stencil tiles; clears the arrival counters.
 __global__ void k_na_layout(MapDesc* desc, MapState* ms, int* counts, int* tile_map, int* fcnt,
-                            int* gcnt, int M, int N, int th, int ntiles, int ngroups) {
+                            int* gcnt, unsigned int* wctl, int M, int N, int th, int ntiles, int ngroups,
+                            int nstrips) {
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
   const int nth = gridDim.x * blockDim.x;
   int* mact = counts + kListHead;
-  int* act = mact + 1;
+  int* slist = mact + 1;
+  int* act = slist + 2 * kNoAllocMaxStrips;
+  for (int t = tid; t < nstrips; t += nth) {
+    slist[2 * t] = 0;
+    slist[2 * t + 1] = t;
+  }
   for (int t = tid; t < ntiles; t += nth) {
     tile_map[t] = 0;
     act[t] = t;
@@ -95,12 +109,13 @@ __global__ void k_na_layout(MapDesc* desc, MapState* ms, int* counts, int* tile_
     d.tiles_x = (N + kTW - 1) / kTW;
     d.ntiles = ntiles;
     d.tile0 = 0;
-    d.ndt = ((M + 63) / 64) * ((N + 63) / 64);  // 64 x 64 sweep tiles, one partial each
+    d.ndt = ((M + 63) / 64) * ((N + 63) / 64);  // slots of the strips' partials
     d.dtile0 = 0;
     d.gb = 0;
     d.gbd = ngroups;
     d.use_iso = 1;
     d.off = 0;
+    d.edge0 = 0;
     d.psi = nullptr;
     d.mask = nullptr;
     d.phi = nullptr;
@@ -115,8 +130,10 @@ __global__ void k_na_layout(MapDesc* desc, MapState* ms, int* counts, int* tile_
     for (int k = 0; k < kListHead; ++k) counts[k] = 0;
     counts[0] = ntiles;
     counts[2] = 1;
+    counts[4] = nstrips;
     mact[0] = 0;
     fcnt[0] = 0;
+    wctl[0] = wctl[1] = 0;  // the launch count goes on
   }
 }
 
@@ -141,7 +158,7 @@ static int apply(lp_unwrap_ctx* ctx, int M, int N, int pc, double omega, const T
   e.total_px = e.cap_px = (long long)M * N;
   e.total_tiles = e.cap_tiles = ntiles;
   e.max_n = N;
-  wf_shape(M, N, &e.wf_diags, &e.wf_len);
+  e.total_strips = e.act_strips = wf_strips(M);
   e.th = th;
   e.grid = ctx->tune.grid;
   e.dct_grid = ctx->tune.dct_grid;
@@ -149,7 +166,8 @@ static int apply(lp_unwrap_ctx* ctx, int M, int N, int pc, double omega, const T
   e.ms = reinterpret_cast<MapState*>(base + kOffState);
   e.counts = reinterpret_cast<int*>(base + kOffCounts);
   e.mact = e.counts + kListHead;
-  e.act = e.mact + 1;
+  e.slist = e.mact + 1;
+  e.act = e.slist + 2 * kNoAllocMaxStrips;
   e.tile_map = reinterpret_cast<int*>(base + kOffTileMap);
   e.fcnt = reinterpret_cast<int*>(base + kOffFcnt);
   e.gcnt = reinterpret_cast<int*>(base + kOffGcnt);
@@ -158,13 +176,15 @@ static int apply(lp_unwrap_ctx* ctx, int M, int N, int pc, double omega, const T
   e.aux = base + kOffAux;
   e.t1 = base + kOffT1;
   e.iso = base + kOffIso;
+  e.wctl = reinterpret_cast<unsigned int*>(base + kOffCtl);
+  e.wedge = reinterpret_cast<unsigned long long*>(base + kOffEdge);
   e.U = const_cast<T*>(U);
   e.V = const_cast<T*>(V);
   e.r = const_cast<T*>(r);
   e.s = s;
   const int lg = std::max(1, std::min(1024, (ntiles + 255) / 256));
   hipLaunchKernelGGL(k_na_layout, dim3(lg), dim3(256), 0, st, e.desc, e.ms, e.counts, e.tile_map,
-                     e.fcnt, e.gcnt, M, N, th, ntiles, ngroups);
+                     e.fcnt, e.gcnt, e.wctl, M, N, th, ntiles, ngroups, e.total_strips);
   // as lpu_precond_apply: isolation flags (and the inverse diagonal for Jacobi)
   e_diag<T>(st, e, ntiles, pc == kPcJacobi);
   const size_t n = (size_t)M * N;
@@ -176,8 +196,8 @@ static int apply(lp_unwrap_ctx* ctx, int M, int N, int pc, double omega, const T
     e_tc_pivots<T>(st, e, ntiles, pc == kPcSsorRb, omega);
     e_twocolor<T>(st, e, ntiles, kRun, pc == kPcSsorRb, omega, 0);
   } else {
-    e_pivots<T>(st, e, 1, pc == kPcSsor, omega);
-    e_sweep<T>(st, e, 1, kRun, pc == kPcSsor, omega, e.r, e.s, e.t1);
+    e_pivots<T>(st, e, 1, pc == kPcSsor, omega, true);
+    e_sweep<T>(st, e, kRun, pc == kPcSsor, omega, e.r, e.s, e.t1, 0);
   }
   const hipError_t le = hipGetLastError();
   if (le != hipSuccess)
