@@ -38,6 +38,7 @@ void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int ex
 int egrid(const Engine& e, int ntiles);
 int dct_grid_for(const Engine& e, int ndtiles);
 bool dct_wide_for(const Engine& e, int ndtiles, int kind);
+int dct_f64_side(int M, int N);
 template <typename T> void e_pivots(hipStream_t, const Engine&, int, bool, double, bool);
 int wf_strips(int M);
 int wf_grid(const Engine& e);
@@ -53,7 +54,7 @@ enum FinOpH { kFinInitH = 0, kFinAlphaH = 1, kFinUpdateH = 2, kFinConfirmH = 3, 
 enum PassOp { kPassSavePhi = 0, kPassX0Phi = 1, kPassX0Zero = 2, kPassPhiAdd = 3,
               kPassDiffNorms = 4, kPassPhiSet = 5 };
 
-// Contraction kernel of the DCT stages: 0 FP64 FMA, 1 FP32 FMA, 2 split-bf16
+// Contraction kernel of the DCT stages: 0 FP64 MFMA, 1 FP32 FMA, 2 split-bf16
 // MFMA, 3 scaled-fp16 MFMA, 4/5 the even/odd MFMA versions of 2/3 (every map
 // side a multiple of 128).
 static int dct_kind_for(const Engine& e, bool mixed, int dct_mode) {
@@ -133,7 +134,8 @@ static const DctTabDev* dct_dev(lp_unwrap_ctx* ctx, int n, int* status) {
 }
 
 // Lay out n maps; (re)allocate grow-only; upload descriptors and tile maps.
-// DCT output tiles are 64 x 64 for the dense kernels; the even/odd kernels
+// DCT output tiles are 64 x 64 for the dense kernels (FP64: 64 x 64 or 32 x 32
+// by the map's size); the even/odd kernels
 // (used when every side is a multiple of 128 in the mixed path with MFMA
 // transforms) take 128 rows x 64 output pairs.  The count per map is the same
 // in all stages.
@@ -161,9 +163,9 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     d.ntiles = d.tiles_x * ((d.M + d.th - 1) / d.th);
     d.tile0 = tiles;
     tiles += d.ntiles;
-    // even/odd tiles (128 rows) cover 64 output pairs, i.e. 128 columns of n
-    const int ccols = dct_trows == 128 ? 128 : kDT;
-    d.ndt = ((d.M + dct_trows - 1) / dct_trows) * ((d.N + ccols - 1) / ccols);
+    // (even/odd tiles of 128 rows cover 64 output pairs, i.e. 128 columns of n)
+    d.dtr = need_dct && elem == 8 ? dct_f64_side(d.M, d.N) : dct_trows;
+    d.ndt = ((d.M + d.dtr - 1) / d.dtr) * ((d.N + d.dtr - 1) / d.dtr);
     d.dtile0 = dtiles;
     dtiles += d.ndt;
     d.gb = groups;
@@ -274,6 +276,8 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
   e.grid = ctx->tune.grid;
   e.dct_grid = ctx->tune.dct_grid;
   e.dct_trows = dct_trows;
+  e.f64_wide = false;
+  for (const MapDesc& d : hd) e.f64_wide = e.f64_wide || d.dtr == 64;
   e.hdesc = hd;
   hipStream_t st = ctx->stream;
   // descriptors and tile -> map tables (staged through the pinned list buffer)
@@ -286,7 +290,7 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
   LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.tile_map, tm.data(), 4 * (size_t)tiles, hipMemcpyHostToDevice, st));
   LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.dtile_map, dm.data(), 4 * (size_t)dtiles, hipMemcpyHostToDevice, st));
   std::vector<EoTile> eo;
-  if (need_dct && dct_trows == 128 && dtiles > 0) {
+  if (need_dct && (dct_trows == 128 || elem == 8) && dtiles > 0) {
     // even/odd tile records for both stage parities
     eo.resize(2 * (size_t)dtiles);
     const long double pi = 3.141592653589793238462643383279502884L;
@@ -301,7 +305,7 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
       for (int par = 0; par < 2; ++par) {
         const DctTables* tk = par ? tM : tN;  // the contracted side's tables
         const int R = par ? d.N : d.M, K = par ? d.M : d.N;
-        const int tiles_r = (R + 127) / 128;
+        const int tiles_r = (R + d.dtr - 1) / d.dtr;
         for (int local = 0; local < d.ndt; ++local) {
           EoTile& r = eo[(size_t)par * dtiles + d.dtile0 + local];
           r.off = d.off;
@@ -311,17 +315,19 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
           r.ti[0] = tk->eot_h;
           r.ti[1] = tk->eot_hi;
           r.ti[2] = tk->eot_lo;
-          r.lam_m = tM->lam_split;
-          r.lam_n = tN->lam_split;
+          r.lam_m = elem == 8 ? tM->lam : tM->lam_split;
+          r.lam_n = elem == 8 ? tN->lam : tN->lam_split;
+          r.c64 = tk->c64;
+          r.ct64 = tk->ct64;
           r.m = m;
           r.R = R;
           r.K = K;
-          r.r0 = (local % tiles_r) * 128;
-          r.c0 = (local / tiles_r) * kDT;
+          r.r0 = (local % tiles_r) * d.dtr;
+          r.c0 = (local / tiles_r) * (d.dtr / 2);  // first output pair
           r.local = local;
           r.ndt = d.ndt;
           r.gbd = d.gbd;
-          r.pad = 0;
+          r.side = d.dtr;
           r.lmin = (float)std::fmin(l1M, l1N);
         }
       }
@@ -392,8 +398,7 @@ static int engine_activate(lp_unwrap_ctx* ctx, const std::vector<int>& set, int*
     for (int m : set) {
       const MapDesc& d = e.hdesc[m];
       const int R = par ? d.N : d.M, K = par ? d.M : d.N;
-      const int ccols = e.dct_trows == 128 ? 128 : kDT;
-      const int tr = (R + e.dct_trows - 1) / e.dct_trows, tc = (K + ccols - 1) / ccols;
+      const int tr = (R + d.dtr - 1) / d.dtr, tc = (K + d.dtr - 1) / d.dtr;
       for (int rt = 0; rt < tr; ++rt) units.push_back({d.dtile0 + rt, tr, tc, (long long)tc * K});
     }
     std::stable_sort(units.begin(), units.end(),
@@ -490,7 +495,7 @@ struct Pcg {
 
   // Preconditioner apply s = M^-1 r for the maps in state `expect`, then the
   // per-map finisher of r^T s with FinishMode `mode` (inside the last DCT
-  // stage for the even/odd kernels, the second two-colour pass and the
+  // stage for the even/odd and FP64 kernels, the second two-colour pass and the
   // backward sweep, as a launch of its own otherwise).
   void tail(hipStream_t st, int nt, int ndt, int expect, int mode) {
     Engine& e = ctx->eng;
@@ -504,7 +509,7 @@ struct Pcg {
     } else if (pc == kPcDct) {
       const void* in[4] = {e.r, e.t1, e.t2, e.t1};
       void* out[4] = {e.t1, e.t2, e.t1, e.s};
-      fused = dct_kind >= 4;
+      fused = dct_kind >= 4 || dct_kind == 0;
       for (int s = 0; s < 4; ++s) {
         const int ev = kt.begin(LPU_KC_DCT, st);
         e_dct_stage(st, e, ndt, s, expect, dct_kind, in[s], out[s], e.r, mode);
@@ -561,7 +566,7 @@ struct Pcg {
     for (int chunk = 8; chunk >= 1; chunk >>= 1) {
       if (K < chunk) continue;
       const int key[kGraphKey] = {egrid(e, nt), pointwise() ? 0 : dct_grid_for(e, nd),
-                                  pc == kPcDct && dct_wide_for(e, nd, dct_kind) ? 1 : 0,
+                                  pc == kPcDct && (dct_wide_for(e, nd, dct_kind) || e.f64_wide) ? 1 : 0,
                                   sweep ? wf_grid(e) : 0, pc, dct_kind,
                                   (int)sizeof(T), e.th, om[0], om[1], chunk};
       hipGraphExec_t ex = nullptr;

@@ -53,20 +53,22 @@ struct DctTabDev {
   const double* lam_split;
 };
 
-// One tile of the even/odd DCT stages for one stage parity (rows of X are the
-// map's rows for parity 0, its columns for parity 1), with everything a block
-// reads to start the tile, so a tile costs one record load instead of a chain
-// of descriptor loads.
+// One tile of the even/odd DCT stages (MFMA in 16 bits, or FP64) for one stage
+// parity (rows of X are the map's rows for parity 0, its columns for parity 1),
+// with everything a block reads to start the tile, so a tile costs one record
+// load instead of a chain of descriptor loads.
 struct EoTile {
   long long off;          // element offset of the map
   const uint16_t* tf[3];  // forward tables EO of the contracted side: fp16, bf16 hi, bf16 lo
   const uint16_t* ti[3];  // inverse tables EOt: fp16, bf16 hi, bf16 lo
-  const double* lam_m;    // eigenvalues along M and along N, in split order
+  const double* lam_m;    // eigenvalues along M and along N, in split order (FP64: natural order)
   const double* lam_n;
+  const double* c64;      // C and C^T of the contracted side
+  const double* ct64;
   int m, R, K, r0, c0;    // map, rows and contraction length at this parity, tile origin
   int local, ndt, gbd;    // tile index within the map, the map's tile count, arrival group base
   float lmin;             // smallest nonzero eigenvalue of the map's Laplacian
-  int pad;
+  int side;               // tile side (MapDesc::dtr)
 };
 
 struct MapDesc {
@@ -74,6 +76,7 @@ struct MapDesc {
   int th;                     // stencil tile height (rows)
   int tiles_x, ntiles, tile0;  // stencil tiles
   int ndt, dtile0;             // DCT tiles (same count in every stage)
+  int dtr;                     // side of a DCT tile: 128 (even/odd MFMA), 64, or 32 (FP64)
   int gb, gbd;                 // first arrival-group counter of the stencil / DCT tiles
   int use_iso;                 // zero the preconditioner output on isolated pixels
   long long off;               // element offset of this map in the work vectors
@@ -123,7 +126,8 @@ struct Engine {
   int* dact = nullptr;       // active DCT tiles: XCD-ordered lists of narrow tiles for the
                              // two stage parities, then of wide tiles (see driver)
   long long dlist_cap = 0;   // capacity of each of the four DCT lists
-  int dct_trows = kDT;       // DCT output tile rows (64 dense, 128 even/odd)
+  int dct_trows = kDT;       // 128 when the even/odd MFMA kernels serve the maps, else 64
+  bool f64_wide = false;     // a map takes FP64 DCT tiles of 64 x 64
   int* mact = nullptr;       // active maps (sweep kernels)
   int* slist = nullptr;      // (map, strip) pairs of the active maps' strips, strip by strip
   unsigned int* wctl = nullptr;        // sweeps: ticket, workgroups done, launches so far

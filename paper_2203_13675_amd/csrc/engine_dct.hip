@@ -9,8 +9,11 @@
 //     stage 1: X = t1 (N x M), B = C_M   -> t2 (M x N), t2 ./= Lambda
 //     stage 2: X = t2 (M x N), B = C_N^T -> t1 (N x M)
 //     stage 3: X = t1 (N x M), B = C_M^T -> s  (M x N), zero on isolated pixels,
-//              FP64 partial of r^T s per 64 x 64 tile.
-// Every map contributes ceil(M/64) ceil(N/64) output tiles to every stage.
+//              FP64 partial of r^T s per tile.
+// Every map contributes ceil(M/t) ceil(N/t) output tiles to every stage, t its
+// tile side (MapDesc::dtr).
+
+#include <type_traits>
 
 #include "lpu_internal.h"
 #include "lpu_device.h"
@@ -37,7 +40,6 @@ struct DArgs {
   const void* rvec;
   const unsigned char* iso;
   int stage, expect;
-  int trows;  // output tile rows: 64 (dense kernels) or 128 (even/odd kernels)
   int cidx;   // counts[] slot holding the length of `dact`
   int dact_cap;  // entries of `dact` (its capacity)
   int *fcnt, *gcnt;  // arrival counters of the fused finisher
@@ -64,10 +66,10 @@ __device__ __forceinline__ DTile dtile(const DArgs& a, int g) {
   const bool rows_m = (a.stage & 1) == 0;
   t.R = rows_m ? d.M : d.N;
   t.K = rows_m ? d.N : d.M;
-  const int tiles_r = (t.R + a.trows - 1) / a.trows;
+  const int tiles_r = (t.R + d.dtr - 1) / d.dtr;
   const int local = g - d.dtile0;
-  t.r0 = (local % tiles_r) * a.trows;
-  t.c0 = (local / tiles_r) * kDT;
+  t.r0 = (local % tiles_r) * d.dtr;
+  t.c0 = (local / tiles_r) * d.dtr;
   t.off = d.off;
   t.tab = rows_m ? d.tabN : d.tabM;
   return t;
@@ -647,10 +649,364 @@ __global__ void __launch_bounds__(256, 2) k_e_dct_eo(DArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// FMA stage (FP64 path, FP32 option): 64 x 64 tile, 16 x 16 threads x 4 x 4.
+// FP64 stage: even/odd split on the FP64 matrix cores, any side length.
+//
+// With h = ceil(n/2) and h2 = floor(n/2) the fold of the even/odd kernel above
+// holds for every n (an odd n's middle element has no mirror and joins the
+// even outputs only):
+//   forward  X_2c = sum_{j<h} C[2c][j] a_j,  X_2c+1 = sum_{j<h2} C[2c+1][j] d_j,
+//            a_j = x_j + x_{n-1-j}, d_j = x_j - x_{n-1-j}  (middle: a = x);
+//   inverse  u_j = sum_{k<h} C[2k][j] X_2k,  v_j = sum_{k<h2} C[2k+1][j] X_2k+1,
+//            x_j = u_j + v_j, x_{n-1-j} = u_j - v_j,
+// half the multiply-adds of the plain product.  Spectra are kept in split
+// order (even k first).  Both halves' table rows are rows of C (forward) and
+// of C^T (inverse, even and odd entries side by side) as they are.
+//
+// A block (4 waves) owns TR rows of X and TR / 2 output pairs; wave w computes
+// half w >> 1 of rows (TR / 2)(w & 1) .., as MFMA tiles of 16 x 16 x 4 with the
+// table as the first operand, so that a lane's results lie along the rows and
+// the transposed store is contiguous over 16 lanes.  K steps of 32 are folded
+// on the way from registers to LDS (two buffers; rows of 34 doubles: the fragment reads, 16
+// rows of 4 consecutive values, touch every bank equally often); the next step's
+// loads are in flight during the current one's MFMAs.  The last, partial step
+// has its own guarded loads, ahead of the loop, which has none.
+//
+// Which tile: 64 x 64 (K steps of 16, two blocks on a CU) halves the traffic
+// per product of 32 x 32 (steps of 32, three blocks), which gives four times as
+// many tiles.  One PCG iteration, the four stages the larger part of it, with
+// tiles of 64 and of 32: 5.3 and 7.0 ms at 4096^2, 756 and 960 us at 2048^2,
+// 179 and 193 at 1024^2, 290 and 307 at 1000 x 1500 (384 tiles), but 156 and
+// 148 at 720 x 960 (180 tiles), 145 and 132 at 768^2, 134 and 113 at 509 x 733,
+// 66 and 58 at 64^2: so maps of at least kF64Wide tiles of 64 x 64 take those.
+// The choice is the map's alone: its results do not depend on its batch-mates.
+// The plain FMA product it replaces took 18.3 ms, 2288, 656, 949, 548, 503, 557
+// and 94 us.  Large maps run at 55 TFLOP/s of the 74 a large FP64 product
+// reaches here; small ones are bound by the latency of one tile's steps.
 // ---------------------------------------------------------------------------
-template <typename T>
+constexpr int kF64Wide = 224;
+
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2u __attribute__((ext_vector_type(2), aligned(8)));
+
+template <int INV, int TR>
+__device__ __forceinline__ void dct_f64_tile(const DArgs& a, const EoTile& t, bool use_iso, int g,
+                                             double* smem, double* red) {
+  constexpr int TP = TR / 2;             // output pairs
+  constexpr int KS = TR == 64 ? 16 : 32, P = KS + 2;  // K step, LDS row pitch
+  constexpr int NI = TR / 32, NJ = TP / 16;  // 16-row and 16-pair tiles per wave
+  constexpr int TPR = KS / 2, RP = 256 / TPR;  // staging: threads per row, rows per pass
+  constexpr int XP = TR / RP, QP = TP / RP;    // staging passes
+  constexpr int kBuf = 2 * (TR + TP) * P;  // doubles of one K step's operands
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int hf = w >> 1, wr = (w & 1) * (TR / 2), l16 = lane & 15, lq = lane >> 4;
+  const int R = t.R, n = t.K, h = (n + 1) >> 1, h2 = n >> 1, r0 = t.r0, c0 = t.c0;
+  const double* X = reinterpret_cast<const double*>(a.X) + t.off;
+  double* Out = reinterpret_cast<double*>(a.Out) + t.off;
+  const auto* T = as_global(INV ? t.ct64 : t.c64);
+  const int sr = tid / TPR, sk = tid % TPR * 2;  // staging: row of a pass, first of two k
+  // rows and pairs past the map repeat the last one (their results are dropped)
+  size_t xo[XP];
+  size_t to[QP], to1[QP];
+#pragma unroll
+  for (int p = 0; p < XP; ++p) xo[p] = (size_t)min(r0 + sr + RP * p, R - 1) * n;
+#pragma unroll
+  for (int p = 0; p < QP; ++p) {
+    const int c = min(c0 + sr + RP * p, h - 1);
+    to[p] = INV ? (size_t)c * n : (size_t)(2 * c) * n;
+    to1[p] = (size_t)min(2 * c + 1, n - 1) * n;  // forward: the odd output's row
+  }
+  struct Held {  // one K step's operands on the way to LDS
+    f64x2u xa[XP], xb[XP], ta[QP], tb[QP];
+  };
+  using gvec = const __attribute__((address_space(1))) f64x2u*;
+  auto fetch = [&](Held& v, int k0) {
+    const int k = k0 + sk;
+#pragma unroll
+    for (int p = 0; p < XP; ++p) {
+      v.xa[p] = *reinterpret_cast<const f64x2u*>(X + xo[p] + k);
+      v.xb[p] = *reinterpret_cast<const f64x2u*>(X + xo[p] + (INV ? h + k : n - 2 - k));
+    }
+#pragma unroll
+    for (int p = 0; p < QP; ++p) {
+      v.ta[p] = *(gvec)(INV ? T + to[p] + 2 * k : T + to[p] + k);
+      v.tb[p] = *(gvec)(INV ? T + to[p] + 2 * k + 2 : T + to1[p] + k);
+    }
+  };
+  // a buffer: X [half][TR][P], then the table [half][TP][P]
+  auto put = [&](double* base, int rows, int half, int row, double v0, double v1) {
+    double* q = base + (half * rows + row) * P + sk;
+    q[0] = v0;
+    q[1] = v1;
+  };
+  // one of the XP + QP pieces of a step's way into LDS
+  auto stash = [&](const Held& v, double* Xs, int p) {
+    double* Ts = Xs + 2 * TR * P;
+    if (p < XP) {
+      const int row = sr + RP * p;
+      if (INV) {
+        put(Xs, TR, 0, row, v.xa[p][0], v.xa[p][1]);
+        put(Xs, TR, 1, row, v.xb[p][0], v.xb[p][1]);
+      } else {
+        put(Xs, TR, 0, row, v.xa[p][0] + v.xb[p][1], v.xa[p][1] + v.xb[p][0]);
+        put(Xs, TR, 1, row, v.xa[p][0] - v.xb[p][1], v.xa[p][1] - v.xb[p][0]);
+      }
+    } else {
+      const int q = p - XP, row = sr + RP * q;
+      if (INV) {
+        put(Ts, TP, 0, row, v.ta[q][0], v.tb[q][0]);
+        put(Ts, TP, 1, row, v.ta[q][1], v.tb[q][1]);
+      } else {
+        put(Ts, TP, 0, row, v.ta[q][0], v.ta[q][1]);
+        put(Ts, TP, 1, row, v.tb[q][0], v.tb[q][1]);
+      }
+    }
+  };
+  // the last, partial step (from k = nf * KS), requested with the first one:
+  // X zero past its half's length, table indices clamped into the row (any
+  // finite value does there)
+  const int nf = h2 / KS, kt = nf * KS + sk;
+  const bool tail = nf * KS < h;
+  double ya[XP][2], yb[XP][2], ua[QP][2], ub[QP][2];
+  auto fetch_tail = [&]() {
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int k = kt + e;
+#pragma unroll
+      for (int p = 0; p < XP; ++p) {
+        ya[p][e] = X[xo[p] + min(k, h - 1)];
+        yb[p][e] = X[xo[p] + (INV ? min(h + k, n - 1) : max(n - 1 - k, 0))];
+      }
+#pragma unroll
+      for (int p = 0; p < QP; ++p) {
+        ua[p][e] = T[to[p] + min(INV ? 2 * k : k, n - 1)];
+        ub[p][e] = INV ? T[to[p] + min(2 * k + 1, n - 1)] : T[to1[p] + min(k, n - 1)];
+      }
+    }
+  };
+  auto stash_tail = [&](double* Xs) {
+    double* Ts = Xs + 2 * TR * P;
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int k = kt + e;
+#pragma unroll
+      for (int p = 0; p < XP; ++p) {
+        const int row = sr + RP * p;
+        const double a0 = INV ? ya[p][e] : (k < h2 ? ya[p][e] + yb[p][e] : ya[p][e]);
+        const double a1 = INV ? yb[p][e] : ya[p][e] - yb[p][e];
+        Xs[(0 * TR + row) * P + sk + e] = k < h ? a0 : 0.0;
+        Xs[(1 * TR + row) * P + sk + e] = k < h2 ? a1 : 0.0;
+      }
+#pragma unroll
+      for (int p = 0; p < QP; ++p) {
+        const int row = sr + RP * p;
+        Ts[(0 * TP + row) * P + sk + e] = ua[p][e];
+        Ts[(1 * TP + row) * P + sk + e] = ub[p][e];
+      }
+    }
+  };
+  f64x4 acc[NI][NJ];
+#pragma unroll
+  for (int i = 0; i < NI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  // the products of one K step from buffer Xs; with NEXT, the next step's
+  // pieces go to buffer Xn between them (a product occupies the matrix core
+  // for 64 cycles, in which the wave can issue them)
+  auto product = [&](const Held* next, const double* Xs, double* Xn) {
+    const double* Xw = Xs + (hf * TR + wr + l16) * P + lq;
+    const double* Tw = Xs + 2 * TR * P + (hf * TP + l16) * P + lq;
+#pragma unroll
+    for (int s = 0; s < KS; s += 4) {
+      double xv[NI], tv[NJ];
+#pragma unroll
+      for (int i = 0; i < NI; ++i) xv[i] = Xw[16 * i * P + s];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) tv[j] = Tw[16 * j * P + s];
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(tv[j], xv[i], acc[i][j], 0, 0, 0);
+      if (next && s / 4 < XP + QP) stash(*next, Xn, s / 4);
+    }
+  };
+  // two buffers, one barrier per step; a step's operands are requested two
+  // steps before its products
+  double* cur = smem;
+  double* nxt = smem + kBuf;
+  Held va, vb;
+  if (nf > 0) {
+    // (past the last step the last one is fetched again: with as many loads in
+    // flight on every path, the wait for one step's leaves the next one's alone)
+    fetch_tail();
+    fetch(va, 0);
+    fetch(vb, min(1, nf - 1) * KS);
+#pragma unroll
+    for (int p = 0; p < XP + QP; ++p) stash(va, cur, p);
+    fetch(va, min(2, nf - 1) * KS);
+  } else {
+    fetch_tail();
+    stash_tail(cur);
+  }
+  __syncthreads();
+  auto step = [&](int s, Held& v) {
+    product(&v, cur, nxt);
+    fetch(v, min(s + 3, nf - 1) * KS);
+    __syncthreads();
+    double* const c = cur;
+    cur = nxt;
+    nxt = c;
+  };
+  int s = 0;
+  for (; s + 2 < nf; s += 2) {
+    step(s, vb);
+    step(s + 1, va);
+  }
+  if (s + 1 < nf) step(s, vb);
+  if (nf > 0 && tail) {
+    product(nullptr, cur, nullptr);
+    stash_tail(nxt);
+    __syncthreads();
+    cur = nxt;
+  }
+  product(nullptr, cur, nullptr);
+  // a lane holds outputs of row l16 (of each 16) at pairs lq + 4 e (of each 16)
+  const double* rv = reinterpret_cast<const double*>(a.rvec) + t.off;
+  const unsigned char* iso = (a.iso && use_iso) ? a.iso + t.off : nullptr;
+  double y[NI][NJ][4];
+  if (!INV) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) y[i][j][e] = acc[i][j][e];
+  } else {
+    // u (half 0) and v (half 1) of the same rows meet through LDS
+    __syncthreads();
+    double* xg = smem + w * (NI * NJ * 4 * 64) + lane;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) xg[((i * NJ + j) * 4 + e) * 64] = acc[i][j][e];
+    __syncthreads();
+    const double* og = smem + (w ^ 2) * (NI * NJ * 4 * 64) + lane;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const double o = og[((i * NJ + j) * 4 + e) * 64];
+          const int pair = c0 + 16 * j + lq + 4 * e;
+          // the middle of an odd side: no v
+          y[i][j][e] = hf ? o - acc[i][j][e] : (pair < h2 ? acc[i][j][e] + o : acc[i][j][e]);
+        }
+  }
+  // output index of pair element (j, e), or -1; row of i
+  auto out_c = [&](int j, int e) {
+    const int pair = c0 + 16 * j + lq + 4 * e;
+    if (pair >= (hf ? h2 : h)) return -1;
+    return INV ? (hf ? n - 1 - pair : pair) : (hf ? h + pair : pair);
+  };
+  double part = 0.0;
+  if (!INV && a.stage == 1) {
+    // spectrum ./ Lambda, zero mode dropped; indices in split order
+    const auto* lm = as_global(t.lam_m);
+    const auto* ln = as_global(t.lam_n);
+    const int hR = (R + 1) >> 1;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int r = min(r0 + wr + 16 * i + l16, R - 1);
+      const double lr = ln[r < hR ? 2 * r : 2 * (r - hR) + 1];
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int k = min(2 * (c0 + 16 * j + lq + 4 * e) + hf, n - 1);
+          y[i][j][e] = k == 0 && r == 0 ? 0.0 : y[i][j][e] / (lm[k] + lr);
+        }
+    }
+  }
+  if (INV && a.stage == 3) {
+    // zero on isolated pixels; FP64 partial of r^T s
+    double rr[NI][NJ][4];
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int c = out_c(j, e), r = r0 + wr + 16 * i + l16;
+          const bool in = c >= 0 && r < R;
+          const size_t o = in ? (size_t)c * R + r : 0;
+          rr[i][j][e] = in ? rv[o] : 0.0;
+          if (iso && iso[o]) y[i][j][e] = 0.0;
+        }
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) part += rr[i][j][e] * y[i][j][e];
+  }
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int r = r0 + wr + 16 * i + l16;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = out_c(j, e);
+        if (c >= 0 && r < R) Out[(size_t)c * R + r] = y[i][j][e];
+      }
+  }
+  if (INV && a.stage == 3) {
+    double vv[1] = {part};
+    block_sum<1>(vv, red);
+    if (tid == 0) store_partial(a.P + 1 * a.pstride + g, vv[0]);
+  }
+}
+
+// TMAX: the larger of the tile sides in the launch.  Launches of small maps
+// only take the instance for side 32, whose LDS leaves room for two blocks on
+// a CU.
+template <int INV, int TMAX>
+__global__ void __launch_bounds__(256, 2) k_e_dct_f64(DArgs a) {
+  // two K steps' operands; the inverse's exchange fits in them
+  __shared__ __attribute__((aligned(16))) double smem[TMAX == 64 ? 2 * 2 * 96 * 18 : 2 * 2 * 48 * 34];
+  __shared__ double red[4];
+  __shared__ double fred[3 * 4];
+  __shared__ int fflag;
+  const int nact = a.counts[a.cidx];
+  // the block's first list entry is requested with the list's length
+  const int g_first = a.dact[min((int)blockIdx.x, max(a.dact_cap - 1, 0))];
+  __asm__ volatile("" ::"s"(nact), "s"(g_first));  // both loads issued before the loop test
+  for (int t_ = blockIdx.x; t_ < nact; t_ += gridDim.x) {
+    const int g = t_ == (int)blockIdx.x ? g_first : a.dact[t_];
+    if (g < 0) continue;  // padding slot of the XCD-ordered list
+    const EoTile t = a.eot[(size_t)(a.stage & 1) * a.eot_cap + g];
+    const bool use_iso = a.desc[t.m].use_iso != 0;
+    if (a.ms[t.m].state != a.expect) continue;  // uniform over the block
+    if (TMAX == 64 && t.side == 64) dct_f64_tile<INV, TMAX>(a, t, use_iso, g, smem, red);
+    else dct_f64_tile<INV, 32>(a, t, use_iso, g, smem, red);
+    if (INV && a.stage == 3 && a.fin_mode) {
+      const int sl[1] = {1};
+      fused_finish<kFinTail, 1>(Arrival{a.fcnt, a.gcnt, a.gsum, a.gstride, a.P, a.pstride}, sl,
+                                g - t.local, t.local, t.ndt, t.gbd, a.desc, a.ms, t.m, a.fin_mode, 0,
+                                &fflag, fred);
+    }
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------
+// FMA stage (FP32 option): 64 x 64 tile, 16 x 16 threads x 4 x 4.
+// ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_e_dct_fma(DArgs a) {
+  using T = float;
   __shared__ T Xs[16][64 + 4];
   __shared__ T Bs[16][64 + 4];
   __shared__ double red[4];
@@ -669,10 +1025,7 @@ __global__ void __launch_bounds__(256) k_e_dct_fma(DArgs a) {
     const T* X = reinterpret_cast<const T*>(a.X) + t.off;
     T* Out = reinterpret_cast<T*>(a.Out) + t.off;
     const T* B;
-    if (sizeof(T) == 8)
-      B = reinterpret_cast<const T*>(a.stage < 2 ? (const void*)t.tab->c64 : (const void*)t.tab->ct64);
-    else
-      B = reinterpret_cast<const T*>(a.stage < 2 ? (const void*)t.tab->c32 : (const void*)t.tab->ct32);
+    B = reinterpret_cast<const T*>(a.stage < 2 ? (const void*)t.tab->c32 : (const void*)t.tab->ct32);
     T acc[4][4];
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -731,6 +1084,12 @@ __global__ void __launch_bounds__(256) k_e_dct_fma(DArgs a) {
   }
 }
 
+// Tile side of the FP64 stages for an M x N map (a function of the map alone).
+int dct_f64_side(int M, int N) {
+  const long long t = (long long)((M + 63) / 64) * ((N + 63) / 64);
+  return t >= kF64Wide ? 64 : 32;
+}
+
 // Grid of a DCT stage: the next power of two >= the list length, capped; a
 // multiple of 8, so list position q always runs on XCD q mod 8.
 int dct_grid_for(const Engine& e, int ndtiles) {
@@ -762,8 +1121,8 @@ void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int ex
   a.gstride = e.gstride;
   a.eot = e.eot;
   a.eot_cap = e.cap_dtiles;
-  // the finisher rides on the last stage of the even/odd kernels only
-  a.fin_mode = (stage == 3 && kind >= 4) ? fin_mode : 0;
+  // the finisher rides on the last stage of the even/odd and FP64 kernels
+  a.fin_mode = (stage == 3 && (kind >= 4 || kind == 0)) ? fin_mode : 0;
   a.desc = e.desc;
   a.ms = e.ms;
   a.dtile_map = e.dtile_map;
@@ -780,11 +1139,17 @@ void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int ex
   a.iso = e.iso;
   a.stage = stage;
   a.expect = expect;
-  a.trows = kind >= 4 ? 128 : 64;
-  // kind: 0 FP64 FMA, 1 FP32 FMA, 2 split-bf16 MFMA, 3 scaled-fp16 MFMA;
+  // kind: 0 FP64 MFMA, 1 FP32 FMA, 2 split-bf16 MFMA, 3 scaled-fp16 MFMA;
   // +2 (kinds 4, 5): the even/odd MFMA kernels (every side a multiple of 128)
-  if (kind == 0) hipLaunchKernelGGL(k_e_dct_fma<double>, dim3(grid), dim3(256), 0, st, a);
-  else if (kind == 1) hipLaunchKernelGGL(k_e_dct_fma<float>, dim3(grid), dim3(256), 0, st, a);
+  // (FP64: the instance that takes tiles of 64 x 64 as well, if any map has them)
+  if (kind == 0 && e.f64_wide) {
+    if (stage < 2) hipLaunchKernelGGL((k_e_dct_f64<0, 64>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_e_dct_f64<1, 64>), dim3(grid), dim3(256), 0, st, a);
+  } else if (kind == 0) {
+    if (stage < 2) hipLaunchKernelGGL((k_e_dct_f64<0, 32>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_e_dct_f64<1, 32>), dim3(grid), dim3(256), 0, st, a);
+  }
+  else if (kind == 1) hipLaunchKernelGGL(k_e_dct_fma, dim3(grid), dim3(256), 0, st, a);
   else if (kind == 2) hipLaunchKernelGGL(k_e_dct_mfma<1>, dim3(grid), dim3(256), 0, st, a);
   else if (kind == 3) hipLaunchKernelGGL(k_e_dct_mfma<0>, dim3(grid), dim3(256), 0, st, a);
   // scaled fp16 even/odd: intermediates between the stages are stored as
