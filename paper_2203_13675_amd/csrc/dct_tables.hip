@@ -57,18 +57,21 @@ const DctTables* get_dct_tables(lp_unwrap_ctx* ctx, int n, int* status) {
     lam[k] = (double)(2.0L - 2.0L * std::cos(pi * k / n));
   }
   std::vector<float> c32(nn), ct32(nn);
-  std::vector<uint16_t> chi(nn), clo(nn), cthi(nn), ctlo(nn), ch(nn), cth(nn);
+  // rows of the dense 16-bit tables padded with zeros to whole K steps
+  const size_t np = ((size_t)n + 63) / 64 * 64, nnp = (size_t)n * np;
+  std::vector<uint16_t> chi(nnp), clo(nnp), cthi(nnp), ctlo(nnp), ch(nnp), cth(nnp);
   for (size_t q = 0; q < nn; ++q) {
+    const size_t o = q / n * np + q % n;
     c32[q] = (float)c[q];
     ct32[q] = (float)ct[q];
-    chi[q] = f32_to_bf16_rne(c32[q]);
-    clo[q] = f32_to_bf16_rne(c32[q] - bf16_to_f32(chi[q]));
-    cthi[q] = f32_to_bf16_rne(ct32[q]);
-    ctlo[q] = f32_to_bf16_rne(ct32[q] - bf16_to_f32(cthi[q]));
+    chi[o] = f32_to_bf16_rne(c32[q]);
+    clo[o] = f32_to_bf16_rne(c32[q] - bf16_to_f32(chi[o]));
+    cthi[o] = f32_to_bf16_rne(ct32[q]);
+    ctlo[o] = f32_to_bf16_rne(ct32[q] - bf16_to_f32(cthi[o]));
     const _Float16 h = (_Float16)c32[q];
     const _Float16 ht = (_Float16)ct32[q];
-    std::memcpy(&ch[q], &h, 2);
-    std::memcpy(&cth[q], &ht, 2);
+    std::memcpy(&ch[o], &h, 2);
+    std::memcpy(&cth[o], &ht, 2);
   }
   bool ok = true;
   auto up = [&](void** dst, const void* src, size_t bytes) {
@@ -80,12 +83,12 @@ const DctTables* get_dct_tables(lp_unwrap_ctx* ctx, int n, int* status) {
   up((void**)&t.ct64, ct.data(), nn * 8);
   up((void**)&t.c32, c32.data(), nn * 4);
   up((void**)&t.ct32, ct32.data(), nn * 4);
-  up((void**)&t.c_hi, chi.data(), nn * 2);
-  up((void**)&t.c_lo, clo.data(), nn * 2);
-  up((void**)&t.ct_hi, cthi.data(), nn * 2);
-  up((void**)&t.ct_lo, ctlo.data(), nn * 2);
-  up((void**)&t.c_h, ch.data(), nn * 2);
-  up((void**)&t.ct_h, cth.data(), nn * 2);
+  up((void**)&t.c_hi, chi.data(), nnp * 2);
+  up((void**)&t.c_lo, clo.data(), nnp * 2);
+  up((void**)&t.ct_hi, cthi.data(), nnp * 2);
+  up((void**)&t.ct_lo, ctlo.data(), nnp * 2);
+  up((void**)&t.c_h, ch.data(), nnp * 2);
+  up((void**)&t.ct_h, cth.data(), nnp * 2);
   up((void**)&t.lam, lam.data(), (size_t)n * 8);
   if (n % 128 == 0) {
     // even/odd split: C[k][n-1-j] = (-1)^k C[k][j]

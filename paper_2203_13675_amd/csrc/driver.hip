@@ -38,7 +38,7 @@ void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int ex
 int egrid(const Engine& e, int ntiles);
 int dct_grid_for(const Engine& e, int ndtiles);
 bool dct_wide_for(const Engine& e, int ndtiles, int kind);
-int dct_f64_side(int M, int N);
+int dct_side(int M, int N, bool fp64);
 template <typename T> void e_pivots(hipStream_t, const Engine&, int, bool, double, bool);
 int wf_strips(int M);
 int wf_grid(const Engine& e);
@@ -103,26 +103,9 @@ static const DctTabDev* dct_dev(lp_unwrap_ctx* ctx, int n, int* status) {
   for (auto& p : ctx->dct_dev)
     if (p.first == n) return p.second;
   DctTabDev h;
-  h.n = n;
-  h.pad = 0;
-  h.c64 = t->c64;
-  h.ct64 = t->ct64;
   h.c32 = t->c32;
   h.ct32 = t->ct32;
-  h.chi = t->c_hi;
-  h.clo = t->c_lo;
-  h.cthi = t->ct_hi;
-  h.ctlo = t->ct_lo;
-  h.ch = t->c_h;
-  h.cth = t->ct_h;
   h.lam = t->lam;
-  h.eo_hi = t->eo_hi;
-  h.eo_lo = t->eo_lo;
-  h.eo_h = t->eo_h;
-  h.eot_hi = t->eot_hi;
-  h.eot_lo = t->eot_lo;
-  h.eot_h = t->eot_h;
-  h.lam_split = t->lam_split;
   DctTabDev* d = nullptr;
   if (hipMalloc((void**)&d, sizeof(DctTabDev)) != hipSuccess ||
       hipMemcpy(d, &h, sizeof(DctTabDev), hipMemcpyHostToDevice) != hipSuccess) {
@@ -134,8 +117,8 @@ static const DctTabDev* dct_dev(lp_unwrap_ctx* ctx, int n, int* status) {
 }
 
 // Lay out n maps; (re)allocate grow-only; upload descriptors and tile maps.
-// DCT output tiles are 64 x 64 for the dense kernels (FP64: 64 x 64 or 32 x 32
-// by the map's size); the even/odd kernels
+// DCT output tiles are 64 x 64 for the FP32 FMA kernel and 64 x 64 or 32 x 32 by
+// the map's size for the FP64 and dense MFMA ones (dct_tile 0); the even/odd kernels
 // (used when every side is a multiple of 128 in the mixed path with MFMA
 // transforms) take 128 rows x 64 output pairs.  The count per map is the same
 // in all stages.
@@ -146,8 +129,14 @@ static bool even_odd_ok(const lpu_map* maps, int n, bool mixed, int dct_mode) {
   return true;
 }
 
+// Side of the DCT tiles: 128, 64, or 0 for the map's own rule.
+static int dct_tile_for(const lpu_map* maps, int n, bool mixed, int dct_mode) {
+  if (even_odd_ok(maps, n, mixed, dct_mode)) return 128;
+  return mixed && dct_mode == LPU_DCT_FP32 ? kDT : 0;
+}
+
 static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem, bool need_dct,
-                        int dct_trows = kDT) {
+                        int dct_tile = kDT) {
   Engine& e = ctx->eng;
   std::vector<MapDesc> hd(n);
   long long px = 0;
@@ -164,7 +153,7 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     d.tile0 = tiles;
     tiles += d.ntiles;
     // (even/odd tiles of 128 rows cover 64 output pairs, i.e. 128 columns of n)
-    d.dtr = need_dct && elem == 8 ? dct_f64_side(d.M, d.N) : dct_trows;
+    d.dtr = dct_tile ? dct_tile : dct_side(d.M, d.N, elem == 8);
     d.ndt = ((d.M + d.dtr - 1) / d.dtr) * ((d.N + d.dtr - 1) / d.dtr);
     d.dtile0 = dtiles;
     dtiles += d.ndt;
@@ -275,9 +264,9 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
   e.th = ctx->tune.tile_rows;
   e.grid = ctx->tune.grid;
   e.dct_grid = ctx->tune.dct_grid;
-  e.dct_trows = dct_trows;
-  e.f64_wide = false;
-  for (const MapDesc& d : hd) e.f64_wide = e.f64_wide || d.dtr == 64;
+  e.dct_trows = dct_tile == 128 ? 128 : kDT;
+  e.dct_tile64 = false;
+  for (const MapDesc& d : hd) e.dct_tile64 = e.dct_tile64 || d.dtr == 64;
   e.hdesc = hd;
   hipStream_t st = ctx->stream;
   // descriptors and tile -> map tables (staged through the pinned list buffer)
@@ -290,8 +279,8 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
   LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.tile_map, tm.data(), 4 * (size_t)tiles, hipMemcpyHostToDevice, st));
   LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.dtile_map, dm.data(), 4 * (size_t)dtiles, hipMemcpyHostToDevice, st));
   std::vector<EoTile> eo;
-  if (need_dct && (dct_trows == 128 || elem == 8) && dtiles > 0) {
-    // even/odd tile records for both stage parities
+  if (need_dct && dct_tile != kDT && dtiles > 0) {
+    // the MFMA kernels' tile records for both stage parities
     eo.resize(2 * (size_t)dtiles);
     const long double pi = 3.141592653589793238462643383279502884L;
     for (int m = 0; m < n; ++m) {
@@ -309,21 +298,23 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
         for (int local = 0; local < d.ndt; ++local) {
           EoTile& r = eo[(size_t)par * dtiles + d.dtile0 + local];
           r.off = d.off;
-          r.tf[0] = tk->eo_h;
-          r.tf[1] = tk->eo_hi;
-          r.tf[2] = tk->eo_lo;
-          r.ti[0] = tk->eot_h;
-          r.ti[1] = tk->eot_hi;
-          r.ti[2] = tk->eot_lo;
-          r.lam_m = elem == 8 ? tM->lam : tM->lam_split;
-          r.lam_n = elem == 8 ? tN->lam : tN->lam_split;
+          const bool eo16 = dct_tile == 128;
+          r.tf[0] = eo16 ? tk->eo_h : tk->c_h;
+          r.tf[1] = eo16 ? tk->eo_hi : tk->c_hi;
+          r.tf[2] = eo16 ? tk->eo_lo : tk->c_lo;
+          r.ti[0] = eo16 ? tk->eot_h : tk->ct_h;
+          r.ti[1] = eo16 ? tk->eot_hi : tk->ct_hi;
+          r.ti[2] = eo16 ? tk->eot_lo : tk->ct_lo;
+          r.lam_m = eo16 ? tM->lam_split : tM->lam;
+          r.lam_n = eo16 ? tN->lam_split : tN->lam;
           r.c64 = tk->c64;
           r.ct64 = tk->ct64;
           r.m = m;
           r.R = R;
           r.K = K;
           r.r0 = (local % tiles_r) * d.dtr;
-          r.c0 = (local / tiles_r) * (d.dtr / 2);  // first output pair
+          // first output pair (even/odd kernels), first output (dense)
+          r.c0 = (local / tiles_r) * (elem == 8 || eo16 ? d.dtr / 2 : d.dtr);
           r.local = local;
           r.ndt = d.ndt;
           r.gbd = d.gbd;
@@ -495,7 +486,7 @@ struct Pcg {
 
   // Preconditioner apply s = M^-1 r for the maps in state `expect`, then the
   // per-map finisher of r^T s with FinishMode `mode` (inside the last DCT
-  // stage for the even/odd and FP64 kernels, the second two-colour pass and the
+  // stage for the MFMA kernels, the second two-colour pass and the
   // backward sweep, as a launch of its own otherwise).
   void tail(hipStream_t st, int nt, int ndt, int expect, int mode) {
     Engine& e = ctx->eng;
@@ -509,7 +500,7 @@ struct Pcg {
     } else if (pc == kPcDct) {
       const void* in[4] = {e.r, e.t1, e.t2, e.t1};
       void* out[4] = {e.t1, e.t2, e.t1, e.s};
-      fused = dct_kind >= 4 || dct_kind == 0;
+      fused = dct_kind != 1;
       for (int s = 0; s < 4; ++s) {
         const int ev = kt.begin(LPU_KC_DCT, st);
         e_dct_stage(st, e, ndt, s, expect, dct_kind, in[s], out[s], e.r, mode);
@@ -566,7 +557,7 @@ struct Pcg {
     for (int chunk = 8; chunk >= 1; chunk >>= 1) {
       if (K < chunk) continue;
       const int key[kGraphKey] = {egrid(e, nt), pointwise() ? 0 : dct_grid_for(e, nd),
-                                  pc == kPcDct && (dct_wide_for(e, nd, dct_kind) || e.f64_wide) ? 1 : 0,
+                                  pc == kPcDct && (dct_wide_for(e, nd, dct_kind) || e.dct_tile64) ? 1 : 0,
                                   sweep ? wf_grid(e) : 0, pc, dct_kind,
                                   (int)sizeof(T), e.th, om[0], om[1], chunk};
       hipGraphExec_t ex = nullptr;
@@ -703,7 +694,7 @@ static int run_maps(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, double p, do
   const bool mixed = sizeof(T) == 4;
   // the sweeps' strips put their partials of r^T s in the 64 x 64 DCT tiles' slots
   int rc = engine_setup(ctx, n, maps, (int)sizeof(T), pc == kPcDct,
-                        pc == kPcDct && even_odd_ok(maps, n, mixed, o.dct_mode) ? 128 : kDT);
+                        pc == kPcDct ? dct_tile_for(maps, n, mixed, o.dct_mode) : kDT);
   if (rc) return rc;
   Engine& e = ctx->eng;
   KTimer& kt = ctx->kt;
@@ -959,8 +950,7 @@ static int step_setup(lp_unwrap_ctx* ctx, int M, int N, int elem, bool dct, cons
   mp.psi = psi;
   mp.mask = mask;
   mp.phi = phi;
-  const bool eo = dct && even_odd_ok(&mp, 1, elem == 4, dct_mode);
-  int rc = engine_setup(ctx, 1, &mp, elem, dct, eo ? 128 : kDT);
+  int rc = engine_setup(ctx, 1, &mp, elem, dct, dct ? dct_tile_for(&mp, 1, elem == 4, dct_mode) : kDT);
   if (rc) return rc;
   std::vector<int> one(1, 0);
   int nt, nd;

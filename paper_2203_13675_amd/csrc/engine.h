@@ -29,39 +29,22 @@ constexpr int kArriveGroup = 32;   // tiles per first-level arrival counter of t
 constexpr int kNumSlots = 4;       // partial-sum slots
 constexpr int kListHead = 16;      // ints of counts[] ahead of the active-map list
 
-// DCT tables of one size n as seen by the kernels.
+// DCT tables of one size n as seen by the FP32 FMA kernel.
 struct DctTabDev {
-  int n;
-  int pad;
-  const double* c64;
-  const double* ct64;
   const float* c32;
   const float* ct32;
-  const uint16_t* chi;
-  const uint16_t* clo;
-  const uint16_t* cthi;
-  const uint16_t* ctlo;
-  const uint16_t* ch;
-  const uint16_t* cth;
   const double* lam;
-  const uint16_t* eo_hi;   // even/odd split tables (null unless n % 128 == 0)
-  const uint16_t* eo_lo;
-  const uint16_t* eo_h;
-  const uint16_t* eot_hi;
-  const uint16_t* eot_lo;
-  const uint16_t* eot_h;
-  const double* lam_split;
 };
 
-// One tile of the even/odd DCT stages (MFMA in 16 bits, or FP64) for one stage
-// parity (rows of X are the map's rows for parity 0, its columns for parity 1),
-// with everything a block reads to start the tile, so a tile costs one record
+// One tile of the MFMA DCT stages for one stage parity (rows of X are the map's
+// rows for parity 0, its columns for parity 1), with everything a block reads to start the tile, so a tile costs one record
 // load instead of a chain of descriptor loads.
 struct EoTile {
   long long off;          // element offset of the map
-  const uint16_t* tf[3];  // forward tables EO of the contracted side: fp16, bf16 hi, bf16 lo
-  const uint16_t* ti[3];  // inverse tables EOt: fp16, bf16 hi, bf16 lo
-  const double* lam_m;    // eigenvalues along M and along N, in split order (FP64: natural order)
+  const uint16_t* tf[3];  // forward tables of the contracted side (EO, or the dense C with
+                          // padded rows): fp16, bf16 hi, bf16 lo
+  const uint16_t* ti[3];  // inverse tables (EOt, or C^T): fp16, bf16 hi, bf16 lo
+  const double* lam_m;    // eigenvalues along M and along N (even/odd in 16 bits: split order)
   const double* lam_n;
   const double* c64;      // C and C^T of the contracted side
   const double* ct64;
@@ -76,7 +59,7 @@ struct MapDesc {
   int th;                     // stencil tile height (rows)
   int tiles_x, ntiles, tile0;  // stencil tiles
   int ndt, dtile0;             // DCT tiles (same count in every stage)
-  int dtr;                     // side of a DCT tile: 128 (even/odd MFMA), 64, or 32 (FP64)
+  int dtr;                     // side of a DCT tile: 128 (even/odd MFMA), 64 or 32
   int gb, gbd;                 // first arrival-group counter of the stencil / DCT tiles
   int use_iso;                 // zero the preconditioner output on isolated pixels
   long long off;               // element offset of this map in the work vectors
@@ -127,7 +110,7 @@ struct Engine {
                              // two stage parities, then of wide tiles (see driver)
   long long dlist_cap = 0;   // capacity of each of the four DCT lists
   int dct_trows = kDT;       // 128 when the even/odd MFMA kernels serve the maps, else 64
-  bool f64_wide = false;     // a map takes FP64 DCT tiles of 64 x 64
+  bool dct_tile64 = false;   // a map takes FP64 or dense MFMA DCT tiles of 64 x 64
   int* mact = nullptr;       // active maps (sweep kernels)
   int* slist = nullptr;      // (map, strip) pairs of the active maps' strips, strip by strip
   unsigned int* wctl = nullptr;        // sweeps: ticket, workgroups done, launches so far

@@ -75,173 +75,11 @@ __device__ __forceinline__ DTile dtile(const DArgs& a, int g) {
   return t;
 }
 
-// ---------------------------------------------------------------------------
-// MFMA stage (mixed path): 4 waves, 32 x 32 outputs each, K step 32; lane l
-// supplies row (l mod 16) and K values 8*(l/16) .. +7 of the 16x16x32 ops.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ f32x8 load_x8(const float* __restrict__ X, int R, int K, int row, int k,
-                                         bool vec_ok) {
-  f32x8 v;
-  if (row < R && vec_ok && k + 7 < K) {
-    const float4* p = reinterpret_cast<const float4*>(X + (size_t)row * K + k);
-    const float4 a = p[0], b = p[1];
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-    v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (row < R && k + e < K) ? X[(size_t)row * K + k + e] : 0.0f;
-  }
-  return v;
-}
-
-__device__ __forceinline__ u16x8 load_t8(const uint16_t* __restrict__ B, int K, int row, int k,
-                                         bool vec_ok) {
-  u16x8 v;
-  if (row < K && vec_ok && k + 7 < K) {
-    v = *as_global(reinterpret_cast<const u16x8*>(B + (size_t)row * K + k));
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (row < K && k + e < K) ? as_global(B)[(size_t)row * K + k + e] : 0;
-  }
-  return v;
-}
-
 __device__ __forceinline__ float fp16_scale(float amax) {
   if (!(amax > 0.0f) || !isfinite(amax)) return 1.0f;
   int e;
   frexpf(amax, &e);
   return ldexpf(1.0f, 14 - e);
-}
-
-template <int SPLIT>
-__global__ void __launch_bounds__(256) k_e_dct_mfma(DArgs a) {
-  __shared__ double red[4];
-  const int nact = a.counts[a.cidx];
-  // the block's first list entry is requested with the list's length
-  const int g_first = a.dact[min((int)blockIdx.x, max(a.dact_cap - 1, 0))];
-  __asm__ volatile("" ::"s"(nact), "s"(g_first));  // both loads issued before the loop test
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int t_ = blockIdx.x; t_ < nact; t_ += gridDim.x) {
-    const int g = t_ == (int)blockIdx.x ? g_first : a.dact[t_];
-    if (g < 0) continue;  // padding slot of the XCD-ordered list
-    const DTile t = dtile(a, g);
-    if (!t.ok) continue;  // uniform over the block
-    const int R = t.R, K = t.K;
-    const float* X = reinterpret_cast<const float*>(a.X) + t.off;
-    float* Out = reinterpret_cast<float*>(a.Out) + t.off;
-    const uint16_t* Bh;
-    const uint16_t* Bl;
-    if (a.stage < 2) {
-      Bh = SPLIT ? t.tab->chi : t.tab->ch;
-      Bl = t.tab->clo;
-    } else {
-      Bh = SPLIT ? t.tab->cthi : t.tab->cth;
-      Bl = t.tab->ctlo;
-    }
-    const int r0 = t.r0 + (w & 1) * 32, c0 = t.c0 + (w >> 1) * 32;
-    const int lr = lane & 15, kg = (lane >> 4) * 8;
-    const bool vec_ok = (K % 8) == 0;
-    float xs = 1.0f, inv_xs = 1.0f;
-    MapState& st = a.ms[t.m];
-    if (!SPLIT) {
-      const float amax = a.stage == 0 ? (float)sqrt(st.rr) * 1.0000001f : st.amax[a.stage];
-      xs = fp16_scale(amax);
-      inv_xs = 1.0f / xs;
-    }
-    f32x4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < K; k0 += 32) {
-      u16x8 bh[2], bl[2];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        bh[j] = load_t8(Bh, K, c0 + j * 16 + lr, k0 + kg, vec_ok);
-        if (SPLIT) bl[j] = load_t8(Bl, K, c0 + j * 16 + lr, k0 + kg, vec_ok);
-      }
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const f32x8 xv = load_x8(X, R, K, r0 + i * 16 + lr, k0 + kg, vec_ok);
-        if (SPLIT) {
-          bf16x8 xh, xl;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const __bf16 h = (__bf16)xv[e];
-            xh[e] = h;
-            xl[e] = (__bf16)(xv[e] - (float)h);
-          }
-#pragma unroll
-          for (int j = 0; j < 2; ++j) {
-            const bf16x8 ch = __builtin_bit_cast(bf16x8, bh[j]);
-            const bf16x8 cl = __builtin_bit_cast(bf16x8, bl[j]);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, ch, acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, cl, acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, ch, acc[i][j], 0, 0, 0);
-          }
-        } else {
-          f16x8 xh;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) xh[e] = (_Float16)(xv[e] * xs);
-#pragma unroll
-          for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(xh, __builtin_bit_cast(f16x8, bh[j]),
-                                                               acc[i][j], 0, 0, 0);
-        }
-      }
-    }
-    // epilogue: lane holds D[row 4*(lane/16) + e][col lane mod 16] of each 16x16 tile
-    const MapDesc& d = a.desc[t.m];
-    const float* rv = reinterpret_cast<const float*>(a.rvec) + t.off;
-    const unsigned char* iso = (a.iso && d.use_iso) ? a.iso + t.off : nullptr;
-    double part = 0.0;
-    float vmax = 0.0f;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int c = c0 + j * 16 + lr;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int rb = r0 + i * 16 + (lane >> 4) * 4;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int r = rb + e;
-          float y = acc[i][j][e] * inv_xs;
-          const bool in = c < K && r < R;
-          if (a.stage == 1 && in)
-            y = (c == 0 && r == 0) ? 0.0f
-                                   : (float)((double)y / (as_global(d.tabM->lam)[c] + as_global(d.tabN->lam)[r]));
-          if (a.stage == 3 && in) {
-            const size_t o = (size_t)c * R + r;
-            if (iso && iso[o]) y = 0.0f;
-            part += (double)rv[o] * (double)y;
-          }
-          v[e] = y;
-          if (in) vmax = fmaxf(vmax, fabsf(y));
-        }
-        if (c < K) {
-          if (rb + 3 < R && (R % 4) == 0) {
-            *reinterpret_cast<float4*>(Out + (size_t)c * R + rb) = make_float4(v[0], v[1], v[2], v[3]);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-              if (rb + e < R) Out[(size_t)c * R + rb + e] = v[e];
-          }
-        }
-      }
-    }
-    if (!SPLIT && a.stage < 3) {
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) vmax = fmaxf(vmax, __shfl_down(vmax, off, 64));
-      if (lane == 0)
-        atomicMax(reinterpret_cast<unsigned int*>(&st.amax[a.stage + 1]), __float_as_uint(vmax));
-    }
-    if (a.stage == 3) {
-      double vv[1] = {part};
-      block_sum<1>(vv, red);
-      if (threadIdx.x == 0) a.P[1 * a.pstride + g] = vv[0];
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -645,6 +483,327 @@ __global__ void __launch_bounds__(256, 2) k_e_dct_eo(DArgs a) {
                                   a.fin_mode, 0, &fflag, fred);
       }
     }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Dense MFMA stage (mixed path, any side lengths): a block (4 waves) owns
+// TR x TR outputs, a wave a quarter of them as MFMA tiles of 16 x 16 x 32; lane
+// l supplies row l mod 16 and the 8 values of chunk l / 16 of an operand.  K
+// steps of 64 go through two LDS buffers, X converted once on the way (bf16 hi
+// and lo, or scaled fp16), every operand requested three steps before its
+// products; the tables' rows are padded with zeros to whole steps, so only X
+// needs guards, in the last, partial step, which is requested ahead of the
+// loop.  An output's products run over the K chunks in increasing order
+// whatever the tile, hi hi, hi lo, lo hi in each.
+//
+// What bounds it at the sizes of one image is the latency of a tile's steps
+// (the products of a step take some 100 cycles, the barrier and LDS around them
+// three times that), so small maps take tiles of 32 x 32, four times as many as
+// of 64 x 64, which re-read X and the tables half as often.  One PCG iteration
+// (split bf16 / fp16) with tiles of 64 and of 32: 53 / 53 and 45 / 48 us at
+// 64^2, 88 / 79 and 75 / 75 at 480 x 640, 110 / 97 and 106 / 101 at 720 x 960
+// (180 tiles of 64), 176 / 144 and 209 / 185 at 1000 x 1500 (384), 436 / 305 and
+// 662 / 485 at 2000^2, hence the rule's kDenseWide.  The kernel it replaces
+// (64 x 64, operands straight from memory, no step ahead, element by element
+// where a side is not a multiple of 8) took 62 / 62, 145 / 133, 192 / 185,
+// 887 / 632 and 824 / 679 us, and 353 / 267 at 509 x 733, now 83 / 84.
+// ---------------------------------------------------------------------------
+constexpr int kDenseWide = 192;
+
+template <int SPLIT, int TR>
+__device__ __forceinline__ void dct_dense_tile(const DArgs& a, const EoTile& t, bool use_iso, int g,
+                                               float xs, float* amax_out, uint16_t* smem, double* red,
+                                               float* fmx) {
+  constexpr int NP = SPLIT ? 2 : 1, KS = 64, NT = TR / 32, XP = TR / 32;
+  constexpr int kPlane = TR * KS, kBuf = 2 * NP * kPlane;  // 16-bit elements: X planes, table planes
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
+  const int lr = lane & 15, kq = lane >> 4;
+  const int R = t.R, K = t.K, Kp = (K + KS - 1) / KS * KS;
+  const float* X = reinterpret_cast<const float*>(a.X) + t.off;
+  float* Out = reinterpret_cast<float*>(a.Out) + t.off;
+  const bool fwd = a.stage < 2;
+  const auto* Th = as_global(fwd ? t.tf[SPLIT ? 1 : 0] : t.ti[SPLIT ? 1 : 0]);
+  const auto* Tl = as_global(fwd ? t.tf[2] : t.ti[2]);
+  const int sr = tid >> 3, sq = tid & 7;  // staging: row of a pass, 16-byte chunk (8 values)
+  // rows and columns past the map repeat the last one (their outputs are dropped)
+  size_t xo[XP], to[XP];
+#pragma unroll
+  for (int p = 0; p < XP; ++p) {
+    xo[p] = (size_t)min(t.r0 + sr + 32 * p, R - 1) * K + 8 * sq;
+    to[p] = (size_t)min(t.c0 + sr + 32 * p, K - 1) * Kp + 8 * sq;
+  }
+  typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+  using gtab = const __attribute__((address_space(1))) u16x8*;
+  struct Held {  // one K step's operands on the way to LDS
+    f32x4u x0[XP], x1[XP];
+    u16x8 th[XP], tl[XP];
+  };
+  auto fetch = [&](Held& v, int k0) {
+#pragma unroll
+    for (int p = 0; p < XP; ++p) {
+      v.x0[p] = *reinterpret_cast<const f32x4u*>(X + xo[p] + k0);
+      v.x1[p] = *reinterpret_cast<const f32x4u*>(X + xo[p] + k0 + 4);
+      v.th[p] = *(gtab)(Th + to[p] + k0);
+      if (SPLIT) v.tl[p] = *(gtab)(Tl + to[p] + k0);
+    }
+  };
+  const int nf = K / KS, kt = nf * KS;
+  const bool tail = kt < K;
+  Held vt;
+  auto fetch_tail = [&]() {
+#pragma unroll
+    for (int p = 0; p < XP; ++p) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int k = kt + 8 * sq + e;
+        const float x = X[xo[p] - 8 * sq + min(k, K - 1)];
+        if (e < 4) vt.x0[p][e & 3] = k < K ? x : 0.0f;
+        else vt.x1[p][e & 3] = k < K ? x : 0.0f;
+      }
+      vt.th[p] = *(gtab)(Th + to[p] + min(kt, Kp - KS));
+      if (SPLIT) vt.tl[p] = *(gtab)(Tl + to[p] + min(kt, Kp - KS));
+    }
+  };
+  // buffer: X planes, then table planes, each [TR][KS], chunks swizzled
+  auto stash = [&](const Held& v, uint16_t* buf) {
+#pragma unroll
+    for (int p = 0; p < XP; ++p) {
+      const int o = lds_at<8>(sr + 32 * p, sq);
+      const float xv[8] = {v.x0[p][0], v.x0[p][1], v.x0[p][2], v.x0[p][3],
+                           v.x1[p][0], v.x1[p][1], v.x1[p][2], v.x1[p][3]};
+      u16x8 h, l;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (SPLIT) {
+          const __bf16 b = (__bf16)xv[e];
+          h[e] = __builtin_bit_cast(uint16_t, b);
+          l[e] = __builtin_bit_cast(uint16_t, (__bf16)(xv[e] - (float)b));
+        } else {
+          h[e] = __builtin_bit_cast(uint16_t, (_Float16)(xv[e] * xs));
+        }
+      }
+      *reinterpret_cast<u16x8*>(buf + o) = h;
+      *reinterpret_cast<u16x8*>(buf + NP * kPlane + o) = v.th[p];
+      if (SPLIT) {
+        *reinterpret_cast<u16x8*>(buf + kPlane + o) = l;
+        *reinterpret_cast<u16x8*>(buf + NP * kPlane + kPlane + o) = v.tl[p];
+      }
+    }
+  };
+  const int wr = (w & 1) * (TR / 2), wc = (w >> 1) * (TR / 2);
+  f32x4 acc[NT][NT];
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto product = [&](const uint16_t* buf, int chunks) {
+    const uint16_t* A = buf;
+    const uint16_t* B = buf + NP * kPlane;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      if (ks >= chunks) break;  // uniform: the last step may hold one chunk of 32
+      const int q = 4 * ks + kq;
+      u16x8 bh[NT], bl[NT];
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        bh[j] = *reinterpret_cast<const u16x8*>(B + lds_at<8>(wc + 16 * j + lr, q));
+        if (SPLIT) bl[j] = *reinterpret_cast<const u16x8*>(B + kPlane + lds_at<8>(wc + 16 * j + lr, q));
+      }
+#pragma unroll
+      for (int i = 0; i < NT; ++i) {
+        const u16x8 ah = *reinterpret_cast<const u16x8*>(A + lds_at<8>(wr + 16 * i + lr, q));
+        u16x8 al;
+        if (SPLIT) al = *reinterpret_cast<const u16x8*>(A + kPlane + lds_at<8>(wr + 16 * i + lr, q));
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          if (SPLIT) {
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, ah), __builtin_bit_cast(bf16x8, bh[j]), acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, ah), __builtin_bit_cast(bf16x8, bl[j]), acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                __builtin_bit_cast(bf16x8, al), __builtin_bit_cast(bf16x8, bh[j]), acc[i][j], 0, 0, 0);
+          } else {
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                __builtin_bit_cast(f16x8, ah), __builtin_bit_cast(f16x8, bh[j]), acc[i][j], 0, 0, 0);
+          }
+        }
+      }
+    }
+  };
+  uint16_t* cur = smem;
+  uint16_t* nxt = smem + kBuf;
+  auto swap = [&]() {
+    uint16_t* const c = cur;
+    cur = nxt;
+    nxt = c;
+  };
+  // (past the last step the last one is fetched again: with as many loads in
+  // flight on every path, the wait for one step's leaves the later ones' alone)
+  Held va, vb;
+  if (tail) fetch_tail();
+  if (nf > 0) {
+    fetch(va, 0);
+    fetch(vb, min(1, nf - 1) * KS);
+    stash(va, cur);
+    fetch(va, min(2, nf - 1) * KS);
+  } else {
+    stash(vt, cur);
+  }
+  __syncthreads();
+  auto step = [&](int s, Held& v) {
+    stash(v, nxt);
+    fetch(v, min(s + 3, nf - 1) * KS);
+    product(cur, 2);
+    __syncthreads();
+    swap();
+  };
+  int s = 0;
+  for (; s + 2 < nf; s += 2) {
+    step(s, vb);
+    step(s + 1, va);
+  }
+  if (s + 1 < nf) step(s, vb);
+  if (nf > 0 && tail) {
+    stash(vt, nxt);
+    product(cur, 2);
+    __syncthreads();
+    swap();
+  }
+  product(cur, tail ? (K - kt + 31) / 32 : 2);
+  // epilogue: lane holds D[row 4*(lane/16) + e][col lane mod 16] of each 16x16
+  // tile; everything it reads is loaded before its first store
+  const float inv_xs = SPLIT ? 1.0f : 1.0f / xs;
+  const float* rv = reinterpret_cast<const float*>(a.rvec) + t.off;
+  const unsigned char* iso = (a.iso && use_iso) ? a.iso + t.off : nullptr;
+  float y[NT][NT][4];
+#pragma unroll
+  for (int i = 0; i < NT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[i][j][e] = acc[i][j][e] * inv_xs;
+  auto row = [&](int i, int e) { return t.r0 + wr + 16 * i + 4 * kq + e; };
+  auto col = [&](int j) { return t.c0 + wc + 16 * j + lr; };
+  if (a.stage == 1) {
+    const auto* lm = as_global(t.lam_m);
+    const auto* ln = as_global(t.lam_n);
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int c = col(j), r = row(i, e);
+          const double l = lm[min(c, K - 1)] + ln[min(r, R - 1)];
+          y[i][j][e] = (c == 0 && r == 0) ? 0.0f : (float)((double)y[i][j][e] / l);
+        }
+  }
+  double part = 0.0;
+  if (a.stage == 3) {
+    float rr[NT][NT][4];
+    bool z[NT][NT][4];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const bool in = col(j) < K && row(i, e) < R;
+          const size_t o = in ? (size_t)col(j) * R + row(i, e) : 0;
+          rr[i][j][e] = in ? rv[o] : 0.0f;
+          z[i][j][e] = iso && iso[o];
+        }
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          if (z[i][j][e]) y[i][j][e] = 0.0f;
+          part += (double)rr[i][j][e] * (double)y[i][j][e];
+        }
+  }
+  float vmax = 0.0f;
+#pragma unroll
+  for (int j = 0; j < NT; ++j) {
+    const int c = col(j);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const int rb = row(i, 0);
+      if (c >= K) continue;
+      if (rb + 3 < R) {
+        f32x4u v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = y[i][j][e];
+        *reinterpret_cast<f32x4u*>(Out + (size_t)c * R + rb) = v;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (rb + e < R) Out[(size_t)c * R + rb + e] = y[i][j][e];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (rb + e < R) vmax = fmaxf(vmax, fabsf(y[i][j][e]));
+    }
+  }
+  if (!SPLIT && a.stage < 3) {
+    // the next stage's scale: the largest output (an order-independent maximum)
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) vmax = fmaxf(vmax, __shfl_down(vmax, off, 64));
+    if (lane == 0) fmx[w] = vmax;
+    __syncthreads();
+    if (tid == 0) {
+      vmax = fmaxf(fmaxf(fmx[0], fmx[1]), fmaxf(fmx[2], fmx[3]));
+      // one address takes its atomics one at a time: only a block that raises
+      // the value it finds there adds one
+      if (vmax > __hip_atomic_load(amax_out, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+        atomicMax(reinterpret_cast<unsigned int*>(amax_out), __float_as_uint(vmax));
+    }
+  }
+  if (a.stage == 3) {
+    double vv[1] = {part};
+    block_sum<1>(vv, red);
+    if (tid == 0) store_partial(a.P + 1 * a.pstride + g, vv[0]);
+  }
+}
+
+// TMAX: the larger of the tile sides in the launch (launches of small maps only
+// take the instance for side 32, whose LDS and registers leave room for more
+// blocks on a CU).
+template <int SPLIT, int TMAX>
+__global__ void __launch_bounds__(256, TMAX == 64 ? 2 : 4) k_e_dct_dense(DArgs a) {
+  __shared__ __attribute__((aligned(16))) uint16_t smem[2 * 2 * (SPLIT ? 2 : 1) * TMAX * 64];
+  __shared__ double red[4];
+  __shared__ double fred[3 * 4];
+  __shared__ float fmx[4];
+  __shared__ int fflag;
+  const int nact = a.counts[a.cidx];
+  // the block's first list entry is requested with the list's length
+  const int g_first = a.dact[min((int)blockIdx.x, max(a.dact_cap - 1, 0))];
+  __asm__ volatile("" ::"s"(nact), "s"(g_first));  // both loads issued before the loop test
+  for (int t_ = blockIdx.x; t_ < nact; t_ += gridDim.x) {
+    const int g = t_ == (int)blockIdx.x ? g_first : a.dact[t_];
+    if (g < 0) continue;  // padding slot of the XCD-ordered list
+    const EoTile t = a.eot[(size_t)(a.stage & 1) * a.eot_cap + g];
+    const bool use_iso = a.desc[t.m].use_iso != 0;
+    MapState& st = a.ms[t.m];
+    float xs = 1.0f;
+    if (!SPLIT) xs = fp16_scale(a.stage == 0 ? (float)sqrt(st.rr) * 1.0000001f : st.amax[a.stage]);
+    if (st.state != a.expect) continue;  // uniform over the block
+    float* amax = a.stage < 3 ? &st.amax[a.stage + 1] : nullptr;
+    if (TMAX == 64 && t.side == 64)
+      dct_dense_tile<SPLIT, TMAX>(a, t, use_iso, g, xs, amax, smem, red, fmx);
+    else
+      dct_dense_tile<SPLIT, 32>(a, t, use_iso, g, xs, amax, smem, red, fmx);
+    if (a.stage == 3 && a.fin_mode) {
+      const int sl[1] = {1};
+      fused_finish<kFinTail, 1>(Arrival{a.fcnt, a.gcnt, a.gsum, a.gstride, a.P, a.pstride}, sl,
+                                g - t.local, t.local, t.ndt, t.gbd, a.desc, a.ms, t.m, a.fin_mode, 0,
+                                &fflag, fred);
+    }
+    __syncthreads();
   }
 }
 
@@ -1084,10 +1243,11 @@ __global__ void __launch_bounds__(256) k_e_dct_fma(DArgs a) {
   }
 }
 
-// Tile side of the FP64 stages for an M x N map (a function of the map alone).
-int dct_f64_side(int M, int N) {
+// Tile side of the FP64 and the dense MFMA stages for an M x N map (a function
+// of the map alone).
+int dct_side(int M, int N, bool fp64) {
   const long long t = (long long)((M + 63) / 64) * ((N + 63) / 64);
-  return t >= kF64Wide ? 64 : 32;
+  return t >= (fp64 ? kF64Wide : kDenseWide) ? 64 : 32;
 }
 
 // Grid of a DCT stage: the next power of two >= the list length, capped; a
@@ -1121,8 +1281,8 @@ void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int ex
   a.gstride = e.gstride;
   a.eot = e.eot;
   a.eot_cap = e.cap_dtiles;
-  // the finisher rides on the last stage of the even/odd and FP64 kernels
-  a.fin_mode = (stage == 3 && (kind >= 4 || kind == 0)) ? fin_mode : 0;
+  // the finisher rides on the last stage of every kernel but the FP32 FMA one
+  a.fin_mode = (stage == 3 && kind != 1) ? fin_mode : 0;
   a.desc = e.desc;
   a.ms = e.ms;
   a.dtile_map = e.dtile_map;
@@ -1141,8 +1301,8 @@ void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int ex
   a.expect = expect;
   // kind: 0 FP64 MFMA, 1 FP32 FMA, 2 split-bf16 MFMA, 3 scaled-fp16 MFMA;
   // +2 (kinds 4, 5): the even/odd MFMA kernels (every side a multiple of 128)
-  // (FP64: the instance that takes tiles of 64 x 64 as well, if any map has them)
-  if (kind == 0 && e.f64_wide) {
+  // (FP64 and dense: the instance that takes tiles of 64 x 64 as well, if any map has them)
+  if (kind == 0 && e.dct_tile64) {
     if (stage < 2) hipLaunchKernelGGL((k_e_dct_f64<0, 64>), dim3(grid), dim3(256), 0, st, a);
     else hipLaunchKernelGGL((k_e_dct_f64<1, 64>), dim3(grid), dim3(256), 0, st, a);
   } else if (kind == 0) {
@@ -1150,8 +1310,10 @@ void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int ex
     else hipLaunchKernelGGL((k_e_dct_f64<1, 32>), dim3(grid), dim3(256), 0, st, a);
   }
   else if (kind == 1) hipLaunchKernelGGL(k_e_dct_fma, dim3(grid), dim3(256), 0, st, a);
-  else if (kind == 2) hipLaunchKernelGGL(k_e_dct_mfma<1>, dim3(grid), dim3(256), 0, st, a);
-  else if (kind == 3) hipLaunchKernelGGL(k_e_dct_mfma<0>, dim3(grid), dim3(256), 0, st, a);
+  else if (kind == 2 && e.dct_tile64) hipLaunchKernelGGL((k_e_dct_dense<1, 64>), dim3(grid), dim3(256), 0, st, a);
+  else if (kind == 2) hipLaunchKernelGGL((k_e_dct_dense<1, 32>), dim3(grid), dim3(256), 0, st, a);
+  else if (kind == 3 && e.dct_tile64) hipLaunchKernelGGL((k_e_dct_dense<0, 64>), dim3(grid), dim3(256), 0, st, a);
+  else if (kind == 3) hipLaunchKernelGGL((k_e_dct_dense<0, 32>), dim3(grid), dim3(256), 0, st, a);
   // scaled fp16 even/odd: intermediates between the stages are stored as
   // scaled fp16 (first stage reads FP32 r, last stage writes FP32 s)
   else if (kind == 4 && stage < 2) hipLaunchKernelGGL((k_e_dct_eo<1, 0, 0, 0, 4>), dim3(grid), dim3(256), 0, st, a);

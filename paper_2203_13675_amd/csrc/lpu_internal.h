@@ -46,6 +46,7 @@ struct DctTables {
   double* ct64 = nullptr;   // C^T
   float* c32 = nullptr;
   float* ct32 = nullptr;
+  // dense 16-bit tables: n rows, each padded with zeros to a multiple of 64
   uint16_t* c_hi = nullptr;   // bf16 split of C
   uint16_t* c_lo = nullptr;
   uint16_t* ct_hi = nullptr;  // bf16 split of C^T
