@@ -50,7 +50,9 @@ def test_dct_dense(mode, rel, M, N):
 @pytest.mark.parametrize("mode", ["split_bf16", "fp16_scaled"])
 def test_dct_dense_batch_of_both_tiles_matches_single(mode):
     """Maps of both tile sides in one launch: each map's result equals its
-    single solve bit for bit (the tile side is the map's alone)."""
+    single solve bit for bit (the tile side is the map's alone).  The 128 x 128
+    map is along for the launch only: by itself it takes the even/odd kernels,
+    whose arithmetic differs."""
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2203_13675_amd.binding import Context
@@ -61,6 +63,8 @@ def test_dct_dense_batch_of_both_tiles_matches_single(mode):
     with Context(0) as ctx:
         phis, _, stats = ctx.batch(psis, **kw)
         for k, psi in enumerate(psis):
+            if psi.shape[0] % 128 == 0 and psi.shape[1] % 128 == 0:
+                continue
             one = ctx.solve(psi, **kw)
             assert stats[k]["inner_iters_total"] == one.stats["inner_iters_total"]
             assert torch.equal(phis[k], one.phi), psi.shape
