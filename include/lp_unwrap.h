@@ -272,7 +272,7 @@ int lpu_kernel_timing_get(lp_unwrap_ctx* ctx, int kernel_class, double* total_ms
  * calls with one setting).
  * ------------------------------------------------------------------------- */
 typedef struct lpu_tuning {
-    int tile_rows;        /* rows per stencil tile (one wave, 128 columns): 4, 8, 16, 32 or 64 */
+    int tile_rows;        /* rows per stencil tile (one block, 128 columns): 4, 8, 16, 32 or 64 */
     int grid;             /* blocks of the grid-stride stencil kernels: 64 .. 65536            */
     int dct_grid;         /* cap on the blocks of a DCT stage: 64 .. 65536                     */
     int use_graph;        /* 1: issue PCG iterations as captured HIP graphs of 8, 4, 2 and 1

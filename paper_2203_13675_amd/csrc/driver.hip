@@ -76,7 +76,7 @@ static double now_ms() {
 // ---------------------------------------------------------------------------
 static void engine_free(Engine& e) {
   // counts, mact, slist, act and dact live in one allocation that starts at counts
-  void* ptrs[] = {e.desc, e.ms, e.tile_map, e.dtile_map, e.fcnt, e.gcnt, e.gsum, e.eot, e.counts, e.wctl, e.wedge,
+  void* ptrs[] = {e.desc, e.ms, e.dtile_map, e.fcnt, e.gcnt, e.gsum, e.eot, e.counts, e.wctl, e.wedge,
                   e.dx, e.dy, e.phi_prev, e.r64, e.U, e.V, e.aux, e.x[0], e.x[1], e.d[0],
                   e.d[1], e.r, e.s, e.q, e.b, e.t1, e.t2, e.iso, e.P};
   for (void* p : ptrs)
@@ -194,7 +194,6 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     };
     A((void**)&e.desc, sizeof(MapDesc) * n);
     A((void**)&e.ms, sizeof(MapState) * n);
-    A((void**)&e.tile_map, 4 * (size_t)tiles);
     A((void**)&e.dtile_map, 4 * (size_t)dtiles);
     A((void**)&e.eot, sizeof(EoTile) * 2 * (size_t)std::max(dtiles, 1));
     // the lists of one activation, in one allocation laid out like the
@@ -202,20 +201,20 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     // lists), so the first three go up in one copy
     const long long dcap = (long long)dtiles + 8LL * (n + 1) * 256 + 64;
     const size_t list_ints =
-        kListHead + (size_t)n + 2 * (size_t)strips + (size_t)tiles + 4 * (size_t)dcap;
+        kListHead + (size_t)n + 2 * (size_t)strips + 2 * (size_t)tiles + 4 * (size_t)dcap;
     A((void**)&e.counts, 4 * list_ints);
     if (ok) {
       e.mact = e.counts + kListHead;
       e.slist = e.mact + n;
       e.act = e.slist + 2 * (size_t)strips;
-      e.dact = e.act + tiles;
+      e.dact = e.act + 2 * (size_t)tiles;
     }
-    A((void**)&e.fcnt, 4 * (size_t)n);
+    A((void**)&e.fcnt, 4 * (size_t)n * kArriveStride);
     A((void**)&e.wctl, 256);
     A((void**)&e.wedge, 8 * (size_t)edges);
     // groups <= tiles / G + dtiles / G + 2 n for any layout within these capacities
     const long long gcap = (long long)(tiles + dtiles) / kArriveGroup + 2LL * n + 8;
-    A((void**)&e.gcnt, 4 * (size_t)gcap);
+    A((void**)&e.gcnt, 4 * (size_t)gcap * kArriveStride);
     A((void**)&e.gsum, 8 * 2 * (size_t)gcap);
     A((void**)&e.dx, 8 * (size_t)cpx);
     A((void**)&e.dy, 8 * (size_t)cpx);
@@ -251,8 +250,8 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
   }
   // arrival counters start at zero (every launch leaves them so; cleared
   // here as well, outside any graph capture)
-  if (hipMemsetAsync(e.fcnt, 0, 4 * (size_t)n, ctx->stream) != hipSuccess ||
-      hipMemsetAsync(e.gcnt, 0, 4 * (size_t)std::max(groups, 1), ctx->stream) != hipSuccess ||
+  if (hipMemsetAsync(e.fcnt, 0, 4 * (size_t)n * kArriveStride, ctx->stream) != hipSuccess ||
+      hipMemsetAsync(e.gcnt, 0, 4 * (size_t)std::max(groups, 1) * kArriveStride, ctx->stream) != hipSuccess ||
       hipMemsetAsync(e.wctl, 0, 8, ctx->stream) != hipSuccess)
     return set_error(ctx, LPU_ERR_HIP, "hipMemsetAsync");
   e.n_maps = n;
@@ -269,14 +268,11 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
   for (const MapDesc& d : hd) e.dct_tile64 = e.dct_tile64 || d.dtr == 64;
   e.hdesc = hd;
   hipStream_t st = ctx->stream;
-  // descriptors and tile -> map tables (staged through the pinned list buffer)
-  std::vector<int> tm(tiles), dm(dtiles);
-  for (int m = 0; m < n; ++m) {
-    for (int t = 0; t < hd[m].ntiles; ++t) tm[hd[m].tile0 + t] = m;
+  // descriptors and the DCT tile -> map table (staged through the pinned list buffer)
+  std::vector<int> dm(dtiles);
+  for (int m = 0; m < n; ++m)
     for (int t = 0; t < hd[m].ndt; ++t) dm[hd[m].dtile0 + t] = m;
-  }
   LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.desc, hd.data(), sizeof(MapDesc) * n, hipMemcpyHostToDevice, st));
-  LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.tile_map, tm.data(), 4 * (size_t)tiles, hipMemcpyHostToDevice, st));
   LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.dtile_map, dm.data(), 4 * (size_t)dtiles, hipMemcpyHostToDevice, st));
   std::vector<EoTile> eo;
   if (need_dct && dct_tile != kDT && dtiles > 0) {
@@ -359,10 +355,13 @@ static int engine_activate(lp_unwrap_ctx* ctx, const std::vector<int>& set, int*
   int* hm = hc + kListHead;
   int* hs = hm + e.cap_maps;
   int* h = hs + 2 * (size_t)e.cap_strips;
-  int* hd = h + e.cap_tiles;
+  int* hd = h + 2 * (size_t)e.cap_tiles;
   int nt = 0;
   for (int m : set)
-    for (int t = 0; t < e.hdesc[m].ntiles; ++t) h[nt++] = e.hdesc[m].tile0 + t;
+    for (int t = 0; t < e.hdesc[m].ntiles; ++t, ++nt) {
+      h[2 * nt] = e.hdesc[m].tile0 + t;
+      h[2 * nt + 1] = m;
+    }
   // DCT tiles, one list per stage parity (rows of X are the map's rows for
   // stages 0 and 2, its columns for stages 1 and 3).  Blocks are dispatched
   // round-robin over the 8 XCDs, so list position q runs on XCD q mod 8 (the
@@ -444,7 +443,7 @@ static int engine_activate(lp_unwrap_ctx* ctx, const std::vector<int>& set, int*
   hc[7] = ndl[3];
   // counts, maps, strips and stencil tiles in one copy, then each DCT list
   const size_t head =
-      (size_t)kListHead + (size_t)e.cap_maps + 2 * (size_t)e.cap_strips + (size_t)nt;
+      (size_t)kListHead + (size_t)e.cap_maps + 2 * (size_t)e.cap_strips + 2 * (size_t)nt;
   LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.counts, hc, 4 * head, hipMemcpyHostToDevice, st));
   for (int li = 0; li < nlists; ++li)
     if (ndl[li])

@@ -21,11 +21,12 @@
 namespace lpu {
 
 constexpr int kTW = 128;  // stencil tile width (columns): two per lane of one wave
-constexpr int kTH = 16;   // default stencil tile height (rows), marched by the wave
+constexpr int kTH = 16;   // default stencil tile height (rows), four to a wave
 constexpr int kDT = 64;   // DCT output tile (64 x 64)
 constexpr int kEngineGrid = 16384;  // default cap on the blocks of the grid-stride tile kernels
 constexpr int kDctGrid = 2048;     // default cap on the blocks of a DCT stage
 constexpr int kArriveGroup = 32;   // tiles per first-level arrival counter of the fused finishers
+constexpr int kArriveStride = 64;  // ints from one arrival counter to the next (a 256-byte line each)
 constexpr int kNumSlots = 4;       // partial-sum slots
 constexpr int kListHead = 16;      // ints of counts[] ahead of the active-map list
 
@@ -103,9 +104,8 @@ struct Engine {
   MapDesc* desc = nullptr;
   MapState* ms = nullptr;
   MapState* hms = nullptr;   // pinned mirror
-  int* tile_map = nullptr;   // global stencil tile -> map
   int* dtile_map = nullptr;  // global DCT tile -> map
-  int* act = nullptr;        // active stencil tiles
+  int* act = nullptr;        // active stencil tiles, (tile, map) pairs
   int* dact = nullptr;       // active DCT tiles: XCD-ordered lists of narrow tiles for the
                              // two stage parities, then of wide tiles (see driver)
   long long dlist_cap = 0;   // capacity of each of the four DCT lists

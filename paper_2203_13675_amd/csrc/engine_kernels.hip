@@ -1,8 +1,8 @@
 // Batched kernels of the phase-unwrapping PCG (gfx950).
 //
-// Stencil tiles are 128 columns x 16 rows, one 64-lane wave each: lane l owns
-// columns j0 + l and j0 + 64 + l (two coalesced 64-wide rows per load), the
-// wave marches down the 16 rows keeping rows i-1, i, i+1 of the operand in
+// Stencil tiles are 128 columns x 16 rows, one block each: lane l owns
+// columns j0 + l and j0 + 64 + l (two coalesced 64-wide rows per load), a
+// wave takes four of the rows with the operand's rows above and below them in
 // registers, and horizontal neighbours come from lane shuffles (plus one halo
 // column at each side, loaded by lanes 0 and 63).  Each tile writes its FP64
 // partial sums to its own slot; finisher kernels reduce per map.
@@ -12,8 +12,6 @@
 //               - U_{i,j} x_{i,j+1} - U_{i,j-1} x_{i,j-1}
 //               - V_{i,j} x_{i+1,j} - V_{i-1,j} x_{i-1,j},
 // out-of-grid terms zero (U is 0 on the last column, V on the last row).
-
-#include <type_traits>
 
 #include "lpu_internal.h"
 #include "lpu_device.h"
@@ -27,15 +25,6 @@ namespace lpu {
 template <typename T>
 struct R2 {
   T a, b;  // columns j0 + lane, j0 + 64 + lane
-};
-
-template <typename T>
-struct R3 {
-  T s, w, d;  // raw loads of one operand element (see the field loaders)
-};
-template <typename T>
-struct R4 {
-  T s, w, d, x;  // R3 and the iterate (SpMV)
 };
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & 63; }
@@ -74,24 +63,34 @@ __device__ __forceinline__ T shdn(T v) { return dpp_move<0x130>(v); }
 template <typename T>
 __device__ __forceinline__ T shfrom(T v, int src) { return bcast(v, src); }
 
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
-  return v;
-}
+// Blocks of the tile kernels have one wave per kRW rows of a tile (the update
+// per kRWUpdate), at most kMaxTileWaves (tile_threads).
+constexpr int kMaxTileWaves = 8, kMaxTileThreads = 64 * kMaxTileWaves;
+
+struct TileRef {
+  int g, m;  // stencil tile of the engine and its map
+};
+
+// the tile sums keep one order over the rows (TileSum)
+template <typename T>
+constexpr bool kOrdered = sizeof(T) == 8;
 
 struct TilePos {
   int m, i0, j0, M, N, rows;
+  int local, ntiles, gb;  // position among the map's tiles, for the fused finishers
   long long off;
 };
 
 __device__ __forceinline__ TilePos tile_pos(const MapDesc* __restrict__ desc,
-                                            const int* __restrict__ tile_map, int g) {
+                                            const TileRef& ref) {
   TilePos t;
-  t.m = tile_map[g];
+  t.m = ref.m;
   const MapDesc& d = desc[t.m];
-  const int lt = g - d.tile0;
+  const int lt = ref.g - d.tile0;
   const int ty = lt / d.tiles_x;
+  t.local = lt;
+  t.ntiles = d.ntiles;
+  t.gb = d.gb;
   t.rows = d.th;
   t.i0 = ty * d.th;
   t.j0 = (lt - ty * d.tiles_x) * kTW;
@@ -115,30 +114,14 @@ __device__ __forceinline__ void neighbours(const R2<T>& v, T halo, R2<T>& w, R2<
   e.b = l < 63 ? dn_b : h63;   // column j0 + 128 for lane 63
 }
 
-// In-grid index of (i, j) clamped to the grid, and whether (i, j) is inside.
-// Loads through a clamped index always execute (no lane-divergent branch
-// around them), so the compiler can issue the loads of several rows at once;
-// the value is then replaced by zero where (i, j) is outside.
-__device__ __forceinline__ size_t clamp_at(int i, int j, int M, int N, bool& ok) {
-  ok = (unsigned)i < (unsigned)M && (unsigned)j < (unsigned)N;
-  const int ic = min(max(i, 0), M - 1), jc = min(max(j, 0), N - 1);
-  return (size_t)ic * N + jc;
-}
-
+// a(i, j), or zero outside the grid; the load goes through a clamped index, so
+// it always executes (no lane-divergent branch around it).
 template <typename T>
 __device__ __forceinline__ T ldz(const T* __restrict__ a, int i, int j, int M, int N) {
-  bool ok;
-  const T v = a[clamp_at(i, j, M, N, ok)];
+  const bool ok = (unsigned)i < (unsigned)M && (unsigned)j < (unsigned)N;
+  const int ic = min(max(i, 0), M - 1), jc = min(max(j, 0), N - 1);
+  const T v = a[(size_t)ic * N + jc];
   return ok ? v : T(0);
-}
-
-template <typename T>
-__device__ __forceinline__ R2<T> ldrow(const T* __restrict__ a, int i, int j0, int M, int N) {
-  const int l = lane_id();
-  R2<T> v;
-  v.a = ldz(a, i, j0 + l, M, N);
-  v.b = ldz(a, i, j0 + 64 + l, M, N);
-  return v;
 }
 
 // Halo column of this lane's halo load: lane 0 uses column j0 - 1, lane 63
@@ -155,103 +138,179 @@ __device__ __forceinline__ T stencil5(T uw, T uc, T vn, T vc, T xc, T xw, T xe, 
   return (uw + uc + vn + vc) * xc - uc * xe - uw * xw - vc * xs - vn * xn;
 }
 
-// March the tile: for every interior pixel call epi(i, j, x_ij, (A x)_ij),
-// or epi(i, j, x_ij, (A x)_ij, raw_ij) when epi takes the element's raw loads
-// as well.  The operand x is formed as make(load(i, j)): load issues the raw
-// loads of one element (zero outside the grid, through a clamped index), make
-// combines them.  Loads run two rows ahead of the arithmetic (operand row i + 2, U and
-// V row i + 1 while row i is computed) and their values are first combined in
-// the next step, so a row's loads are in flight while the previous row is
-// computed and stored (vector loads and stores share one counter on this
-// architecture; a value used in the step that loads it would make the wave
-// wait for everything issued before).
-template <int TH, bool FULL, typename T, typename Ld, typename Mk, typename E>
-__device__ __forceinline__ void march_stencil(const TilePos& tp, const T* __restrict__ U,
-                                              const T* __restrict__ V, Ld load, Mk make, E epi) {
-  const int M = tp.M, N = tp.N, i0 = tp.i0, j0 = tp.j0, l = lane_id();
-  const int hj = halo_col(j0), uj = j0 - 1;  // U's halo: column j0 - 1 (lane 0's), every lane
-  const int ca = j0 + l, cb = j0 + 64 + l;
-  using Raw = decltype(load(0, 0));
-  struct Row {
-    Raw a, b, h;  // columns ca, cb and this lane's halo column
-  };
-  auto lrow = [&](int i) {
-    Row r;
-    r.a = load(i, ca);
-    r.b = load(i, cb);
-    r.h = load(i, hj);
-    return r;
-  };
-  constexpr bool kRaw = std::is_invocable_v<E, int, int, T, T, const Raw&>;
-  auto call = [&](int i, int j, T xv, T ax, const Raw& raw) {
-    if constexpr (kRaw) epi(i, j, xv, ax, raw);
-    else epi(i, j, xv, ax);
-  };
-  R2<T> xm, xc;
-  Row rcur;  // raw loads of the row being computed (kept only when epi reads them)
-  {
-    const Row rm = lrow(i0 - 1), rc = lrow(i0);
-    xm.a = make(rm.a);
-    xm.b = make(rm.b);
-    xc.a = make(rc.a);
-    xc.b = make(rc.b);
-    rcur = rc;
-  }
-  T xh = make(lrow(i0).h);
-  Row rp = lrow(i0 + 1);
-  R2<T> vn = ldrow(V, i0 - 1, j0, M, N), vc = ldrow(V, i0, j0, M, N);
-  R2<T> uc = ldrow(U, i0, j0, M, N);
-  T uh = ldz(U, i0, uj, M, N);
-  auto step = [&](int k) {
-    const int i = i0 + k;
-    // next rows' loads first
-    const Row rpp = lrow(i + 2);
-    const R2<T> un = ldrow(U, i + 1, j0, M, N);
-    const T unh = ldz(U, i + 1, uj, M, N);
-    const R2<T> vnx = ldrow(V, i + 1, j0, M, N);
-    R2<T> xp;
-    xp.a = make(rp.a);
-    xp.b = make(rp.b);
-    const T xph = make(rp.h);
-    R2<T> xw, xe, uw, ue;
-    neighbours(xc, xh, xw, xe);
-    neighbours(uc, uh, uw, ue);
-    if (FULL || ca < N)
-      call(i, ca, xc.a, stencil5<T>(uw.a, uc.a, vn.a, vc.a, xc.a, xw.a, xe.a, xm.a, xp.a), rcur.a);
-    if (FULL || cb < N)
-      call(i, cb, xc.b, stencil5<T>(uw.b, uc.b, vn.b, vc.b, xc.b, xw.b, xe.b, xm.b, xp.b), rcur.b);
-    xm = xc;
-    xc = xp;
-    xh = xph;
-    if constexpr (kRaw) rcur = rp;
-    rp = rpp;
-    vn = vc;
-    vc = vnx;
-    uc = un;
-    uh = unh;
-  };
-  // TH > 0: compile-time tile height, unrolled (the lane shuffles inside keep
-  // the compiler from unrolling a loop of run-time length); TH == 0: tp.rows
-  if constexpr (TH > 0) {
-#pragma unroll 4
-    for (int k = 0; k < TH; ++k) {
-      if (i0 + k >= M) break;
-      step(k);
-    }
-  } else {
-    const int kend = min(tp.rows, M - i0);
-    for (int k = 0; k < kend; ++k) step(k);
-  }
-}
+// Rows of a tile go to the block's waves kRW at a time: wave w takes rows
+// kRW w, kRW (w + waves), ... .  The wave index is made uniform, so row
+// offsets stay in scalar registers.
+//
+// A map of up to a million pixels has too few tiles to hide memory latency by
+// their number (1024^2: 512 tiles on 256 CUs), so a tile's time is what bounds
+// its kernels, and with all rows of a tile in flight at once it is one round
+// trip instead of the 16 rows of a single wave that marched down the tile two
+// rows ahead of its arithmetic.  Measured per SpMV / update launch, one wave
+// per tile against four rows per wave (update eight): 64^2 FP64 12.7 / 7.2
+// against 8.1 / 6.7 us, 720x960 FP64 Jacobi 18.7 / 18.1 against 16.8 / 10.8,
+// 1024^2 FP32 19.5 / 14.5 against 13.2 / 9.2 (with the arrival counters on
+// lines of their own, see Arrival), 4096^2 FP32 110 / 50 against 109 / 49,
+// where HBM is the bound (537 MB and 201 MB a launch).  The rows above and below
+// a wave's own come from the caches.  Two rows per wave: 2 to 4 % faster up to
+// 720x960, 6 to 20 % slower from 2048^2 on.  The update has no halo and takes
+// eight rows a wave, so that enough loads are in flight at every size (4096^2
+// with four: 60 us).
+constexpr int kRW = 4;
+constexpr int kRWUpdate = 8;
 
-// Tiles that lie wholly inside the map's columns (every map side a multiple
-// of 128 gives only such tiles) take a copy of the march without per-lane
-// column guards, so no store or load sits behind a lane-divergent branch.
-template <int TH, typename T, typename Ld, typename Mk, typename E>
-__device__ __forceinline__ void march_tile(const TilePos& tp, const T* __restrict__ U,
-                                           const T* __restrict__ V, Ld load, Mk make, E epi) {
-  if (tp.j0 + kTW <= tp.N) march_stencil<TH, true, T>(tp, U, V, load, make, epi);
-  else march_stencil<TH, false, T>(tp, U, V, load, make, epi);
+__device__ __forceinline__ int wave_id() {
+  return __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+}
+__device__ __forceinline__ int wave_count() { return (int)(blockDim.x >> 6); }
+
+// The addends x y of one pixel's sums.
+template <typename T, int NS>
+struct Terms {
+  T x[NS], y[NS];
+};
+template <typename T>
+struct Terms<T, 0> {};
+
+// Sums over a tile of products of values of type T.
+//
+// ORDERED (the FP64 path): lane l adds its columns' terms row by row, column
+// j0 + l before j0 + 64 + l, and a tree adds the lanes, whatever the number of
+// waves the rows are spread over: the lanes' running sums pass from wave to
+// wave through LDS in row order.  FP64 solves of some thousand weakly
+// preconditioned iterations end at iterates that depend on the order of these
+// sums in the eighth digit, so the order is kept free of the launch's shape.
+// It costs 0.1 to 0.4 us of a kernel.
+// Otherwise (the FP32 path, whose scalars are rounded to FP32): every wave
+// adds its own rows, a tree its lanes, and the waves are added in order.
+template <typename T, int NS, bool ORDERED>
+struct TileSum {
+  double* lds;  // NS * 64 doubles
+  double sum[NS > 0 ? NS : 1];  // after finish(): valid in thread 0
+
+  __device__ __forceinline__ explicit TileSum(double* smem) : lds(smem) {
+#pragma unroll
+    for (int n = 0; n < NS; ++n) sum[n] = 0.0;
+  }
+  // a pixel's terms: added here, or kept in its place of the wave's rows
+  __device__ __forceinline__ void put(Terms<T, NS>& place, const Terms<T, NS>& t) {
+    if constexpr (ORDERED) place = t;
+    else accumulate(t);
+  }
+  // the kept terms of this wave's next G rows (zero where there is no pixel);
+  // every wave of the block calls it equally often, `first` the first time
+  template <int G>
+  __device__ __forceinline__ void add(bool first, const Terms<T, NS> (&ta)[G],
+                                      const Terms<T, NS> (&tb)[G]) {
+    if constexpr (NS > 0 && ORDERED) {
+      const int l = lane_id(), w = wave_id(), nw = wave_count();
+      for (int k = 0; k < nw; ++k) {
+        if (w == k) {
+          if (!first || k > 0)
+#pragma unroll
+            for (int n = 0; n < NS; ++n) sum[n] = lds[64 * n + l];
+#pragma unroll
+          for (int c = 0; c < G; ++c) {
+            accumulate(ta[c]);
+            accumulate(tb[c]);
+          }
+#pragma unroll
+          for (int n = 0; n < NS; ++n) lds[64 * n + l] = sum[n];
+        }
+        __syncthreads();
+      }
+    }
+  }
+  __device__ __forceinline__ void accumulate(const Terms<T, NS>& t) {
+    if constexpr (NS > 0)
+#pragma unroll
+      for (int n = 0; n < NS; ++n) sum[n] = fma((double)t.x[n], (double)t.y[n], sum[n]);
+  }
+  __device__ __forceinline__ void finish() {
+    if constexpr (NS > 0 && !ORDERED) {
+      block_sum<NS>(sum, lds);
+    } else if constexpr (NS > 0) {
+      if (wave_id() == 0)
+#pragma unroll
+        for (int n = 0; n < NS; ++n) sum[n] = tree64(lds[64 * n + lane_id()]);
+    }
+  }
+};
+
+// Stencil over the tile's rows of this wave: for every interior pixel
+// epi(i, row, j, x_ij, (A x)_ij, raw_ij, own_ij), row = i N, which returns the
+// pixel's terms of the sums in ts.  The operand x is
+// formed as make(load(row, j), i, j) and is zero outside the grid; own(row, j)
+// loads what only the pixel itself needs.  load and own must only load: every
+// load of kRW rows (and of the operand rows above and below them) is issued
+// through clamped coordinates before the first value is used, so a wave pays
+// one memory round trip per kRW rows.
+template <typename T, int NS, bool OR, typename Ld, typename Mk, typename Ow, typename E>
+__device__ __forceinline__ void stencil_tile(const TilePos& tp, TileSum<T, NS, OR>& ts,
+                                             const T* __restrict__ U, const T* __restrict__ V,
+                                             Ld load, Mk make, Ow own, E epi) {
+  const int M = tp.M, N = tp.N, j0 = tp.j0, l = lane_id();
+  const int hj = halo_col(j0);
+  const int ca = j0 + l, cb = j0 + 64 + l;
+  const bool oka = ca < N, okb = cb < N, okh = (unsigned)hj < (unsigned)N;
+  const unsigned ja = min(ca, N - 1), jb = min(cb, N - 1), jh = min(max(hj, 0), N - 1);
+  const unsigned ju = max(j0 - 1, 0);  // U's halo: column j0 - 1 (lane 0's), every lane
+  const int i_end = min(tp.i0 + tp.rows, M);
+  using Raw = decltype(load(size_t(0), 0u));
+  using Own = decltype(own(size_t(0), 0u));
+  // ordered sums need the same number of turns in every wave; otherwise a wave
+  // without rows leaves at once (4096^2 FP32 SpMV 109 against 114 us)
+  const int wrow = wave_id() * kRW, step = wave_count() * kRW, lead = OR ? wrow : 0;
+  for (int i0 = tp.i0 + wrow; i0 - lead < i_end; i0 += step) {
+    Terms<T, NS> ta[kRW] = {}, tb[kRW] = {};
+    Raw ra[kRW + 2], rb[kRW + 2], rh[kRW];  // operand rows i0 - 1 .. i0 + kRW
+    Own oa[kRW], ob[kRW];
+    R2<T> u[kRW], v[kRW + 1];  // V rows i0 - 1 .. i0 + kRW - 1
+    T uh[kRW];
+#pragma unroll
+    for (int c = 0; c < kRW + 2; ++c) {
+      const size_t row = (size_t)min(max(i0 - 1 + c, 0), M - 1) * N;
+      ra[c] = load(row, ja);
+      rb[c] = load(row, jb);
+      if (c <= kRW) {
+        v[c].a = V[row + ja];
+        v[c].b = V[row + jb];
+      }
+      if (c > 0 && c <= kRW) {
+        rh[c - 1] = load(row, jh);
+        u[c - 1].a = U[row + ja];
+        u[c - 1].b = U[row + jb];
+        uh[c - 1] = U[row + ju];
+        oa[c - 1] = own(row, ja);
+        ob[c - 1] = own(row, jb);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    auto operand = [&](const Raw& r, int i, int j, bool okc) {
+      return okc && (unsigned)i < (unsigned)M ? make(r, i, j) : T(0);
+    };
+    R2<T> xm{operand(ra[0], i0 - 1, ca, oka), operand(rb[0], i0 - 1, cb, okb)};
+    R2<T> xc{operand(ra[1], i0, ca, oka), operand(rb[1], i0, cb, okb)};
+    if (i0 == 0) v[0].a = v[0].b = T(0);
+#pragma unroll
+    for (int c = 0; c < kRW; ++c) {
+      const int i = i0 + c;
+      if (i >= i_end) break;  // uniform over the wave
+      const R2<T> xp{operand(ra[c + 2], i + 1, ca, oka), operand(rb[c + 2], i + 1, cb, okb)};
+      R2<T> xw, xe, uw, ue;
+      neighbours(xc, operand(rh[c], i, hj, okh), xw, xe);
+      neighbours(u[c], j0 > 0 ? uh[c] : T(0), uw, ue);
+      const T qa = stencil5<T>(uw.a, u[c].a, v[c].a, v[c + 1].a, xc.a, xw.a, xe.a, xm.a, xp.a);
+      const T qb = stencil5<T>(uw.b, u[c].b, v[c].b, v[c + 1].b, xc.b, xw.b, xe.b, xm.b, xp.b);
+      const size_t row = (size_t)i * N;
+      if (oka) ts.put(ta[c], epi(i, row, ja, xc.a, qa, ra[c + 1], oa[c]));
+      if (okb) ts.put(tb[c], epi(i, row, jb, xc.b, qb, rb[c + 1], ob[c]));
+      xm = xc;
+      xc = xp;
+    }
+    ts.template add<kRW>(i0 == tp.i0 + wrow, ta, tb);
+  }
+  ts.finish();
 }
 
 // Elementwise walk over the tile's pixels.
@@ -259,7 +318,7 @@ template <typename E>
 __device__ __forceinline__ void march_points(const TilePos& tp, E epi) {
   const int l = lane_id();
   const int kend = min(tp.rows, tp.M - tp.i0);
-  for (int k = 0; k < kend; ++k) {
+  for (int k = wave_id(); k < kend; k += wave_count()) {
     const int i = tp.i0 + k;
     const int ca = tp.j0 + l, cb = tp.j0 + 64 + l;
     if (ca < tp.N) epi(i, ca);
@@ -269,18 +328,22 @@ __device__ __forceinline__ void march_points(const TilePos& tp, E epi) {
 
 // Elementwise walk in groups of G rows: load(i, j) issues every load of one
 // pixel (the walk passes in-grid coordinates, clamped for lanes and rows past
-// the map, whose results are dropped), store(i, j, v) computes and stores.
+// the map, whose results are dropped), store(i, j, v) computes and stores
+// (and returns the pixel's terms of the sums in ts).
 // All loads of a group are issued before its first store: loads and stores
 // share one wait counter, so a load issued after a store would also wait for
 // the store, a memory round trip per pixel row.
-template <int G, typename L, typename S>
-__device__ __forceinline__ void march_points_grouped(const TilePos& tp, L load, S store) {
+template <int G, typename T, int NS, bool OR, typename L, typename S>
+__device__ __forceinline__ void march_points_grouped(const TilePos& tp, TileSum<T, NS, OR>& ts, L load,
+                                                     S store) {
   const int l = lane_id();
   const int kend = min(tp.rows, tp.M - tp.i0);
   const int ca = tp.j0 + l, cb = tp.j0 + 64 + l;
   const int ja = min(ca, tp.N - 1), jb = min(cb, tp.N - 1);
   using Val = decltype(load(0, 0));
-  for (int k0 = 0; k0 < kend; k0 += G) {
+  const int wrow = wave_id() * G, lead = OR ? wrow : 0;  // as in stencil_tile
+  for (int k0 = wrow; k0 - lead < kend; k0 += wave_count() * G) {
+    Terms<T, NS> ta[G] = {}, tb[G] = {};
     Val v[G][2];
 #pragma unroll
     for (int c = 0; c < G; ++c) {
@@ -292,10 +355,20 @@ __device__ __forceinline__ void march_points_grouped(const TilePos& tp, L load, 
     for (int c = 0; c < G; ++c) {
       if (k0 + c >= kend) break;  // uniform over the wave
       const int i = tp.i0 + k0 + c;
-      if (ca < tp.N) store(i, ca, v[c][0]);
-      if (cb < tp.N) store(i, cb, v[c][1]);
+      if (ca < tp.N) ts.put(ta[c], store(i, ca, v[c][0]));
+      if (cb < tp.N) ts.put(tb[c], store(i, cb, v[c][1]));
     }
+    ts.template add<G>(k0 == wrow, ta, tb);
   }
+  ts.finish();
+}
+template <int G, typename L, typename S>
+__device__ __forceinline__ void march_points_grouped(const TilePos& tp, L load, S store) {
+  TileSum<float, 0, false> none(nullptr);
+  march_points_grouped<G>(tp, none, load, [&](int i, int j, const auto& v) {
+    store(i, j, v);
+    return Terms<float, 0>{};
+  });
 }
 
 template <typename T>
@@ -311,9 +384,8 @@ __device__ __forceinline__ const T* cvec(const void* base, long long off) {
 struct EArgs {
   const MapDesc* desc;
   MapState* ms;
-  const int* tile_map;
-  const int* act;
-  int act_cap;  // entries of act (its capacity)
+  const int* act;  // (tile, map) pairs
+  int act_cap;     // its capacity in pairs
   const int* counts;
   double* P;
   long long pstride;
@@ -332,16 +404,21 @@ __device__ __forceinline__ Arrival arrival(const EArgs& A) {
   return Arrival{A.fcnt, A.gcnt, A.gsum, A.gstride, A.P, A.pstride};
 }
 
+__device__ __forceinline__ TileRef tile_ref(const EArgs& A, int t) {
+  return TileRef{A.act[2 * (size_t)t], A.act[2 * (size_t)t + 1]};
+}
+
 // Grid-stride walk over the active tiles.  The block's first list entry is
 // requested together with the list's length (through an index clamped to
-// the list's capacity; it is used only when the block has a tile), so the
-// walk starts one memory round trip earlier.
+// the list's capacity; it is used only when the block has a tile), and the
+// entry names the tile's map, so the map's descriptor and state are the
+// second memory round trip of a block and its pixels the third.
 #define TILE_LOOP(A)                                                          \
   const int n_act_ = (A).counts[0];                                           \
-  const int g_first_ = (A).act[min((int)blockIdx.x, max((A).act_cap - 1, 0))]; \
-  __asm__ volatile("" ::"s"(n_act_), "s"(g_first_)); /* both loads issued here */ \
+  const TileRef first_ = tile_ref(A, min((int)blockIdx.x, max((A).act_cap - 1, 0))); \
+  __asm__ volatile("" ::"s"(n_act_), "s"(first_.g), "s"(first_.m)); /* loads issued here */ \
   for (int t_ = blockIdx.x; t_ < n_act_; t_ += gridDim.x)
-#define TILE_G(A) (t_ == (int)blockIdx.x ? g_first_ : (A).act[t_])
+#define TILE_REF(A) (t_ == (int)blockIdx.x ? first_ : tile_ref(A, t_))
 
 // ---------------------------------------------------------------------------
 // Set-up kernels: wrapped differences, weights, Jacobi diagonal, isolation
@@ -354,10 +431,10 @@ __device__ __forceinline__ double wrap_w(double x) {
 
 // zero_phi: also set the caller's phi to 0 (the start value when the caller
 // does not supply one)
-__global__ void __launch_bounds__(64) k_e_wrapdiff(EArgs A, int zero_phi) {
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_wrapdiff(EArgs A, int zero_phi) {
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     const double* psi = A.desc[tp.m].psi;
     double* phi = A.desc[tp.m].phi;
     double* dx = A.dx + tp.off;
@@ -387,11 +464,11 @@ __global__ void __launch_bounds__(64) k_e_wrapdiff(EArgs A, int zero_phi) {
 
 // Input check of every map in one launch: *bad |= 1 when psi holds a
 // non-finite value or the mask one outside [0, 1].
-__global__ void __launch_bounds__(64) k_e_check(EArgs A, unsigned int* bad) {
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_check(EArgs A, unsigned int* bad) {
   unsigned int b = 0;
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     const double* psi = A.desc[tp.m].psi;
     const float* mask = A.desc[tp.m].mask;
     march_points(tp, [&](int i, int j) {
@@ -413,10 +490,10 @@ __device__ __forceinline__ double abs_pow(double r, double e) {
 // U, V of Eq. (6) from phi (FP64), stored as T; also the Jacobi inverse
 // diagonal needs U, V of neighbours, so it is a separate pass.
 template <typename T>
-__global__ void __launch_bounds__(64) k_e_weights(EArgs A, double e, double tau) {
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_weights(EArgs A, double e, double tau) {
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     const MapDesc& d = A.desc[tp.m];
     const double* phi = d.phi;
     const float* mask = d.mask;
@@ -466,10 +543,10 @@ __global__ void __launch_bounds__(64) k_e_weights(EArgs A, double e, double tau)
 
 // Jacobi inverse diagonal (0 on isolated pixels) and isolation flags.
 template <typename T>
-__global__ void __launch_bounds__(64) k_e_diag(EArgs A, int want_inv) {
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_diag(EArgs A, int want_inv) {
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     const T* U = cvec<T>(A.U, tp.off);
     const T* V = cvec<T>(A.V, tp.off);
     T* inv = vec<T>(A.aux, tp.off);
@@ -489,10 +566,11 @@ __global__ void __launch_bounds__(64) k_e_diag(EArgs A, int want_inv) {
 // mode 2: r64 only.  Partials: slot 0 = r.r (mode 0: b.b), slot 1 = b.b.
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ void __launch_bounds__(64) k_e_rhs(EArgs A, int mode) {
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_rhs(EArgs A, int mode) {
+  __shared__ double red[2 * 64];
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     const MapDesc& d = A.desc[tp.m];
     const T* U = cvec<T>(A.U, tp.off);
     const T* V = cvec<T>(A.V, tp.off);
@@ -503,13 +581,13 @@ __global__ void __launch_bounds__(64) k_e_rhs(EArgs A, int mode) {
     double* r64 = A.r64 + tp.off;
     const int M = tp.M, N = tp.N;
     const bool usephi = mode != 0;
-    double srr = 0.0, sbb = 0.0;
+    TileSum<double, 2, kOrdered<T>> ts(red);  // r.r, b.b
     struct Px {
       double pc, pe, pw, pn, ps, dxc, dxw, dyc, dyn;
       T uc, uw, vc, vn;
     };
     march_points_grouped<2>(
-        tp,
+        tp, ts,
         [&](int i, int j) {
           // neighbours outside the grid read the pixel itself (never used)
           const size_t p = (size_t)i * N + j;
@@ -559,14 +637,11 @@ __global__ void __launch_bounds__(64) k_e_rhs(EArgs A, int mode) {
           if (mode == 0) bT[p] = (T)b;
           if (mode == 1) bT[p] = (T)r;
           r64[p] = mode == 0 ? b : r;
-          srr += r * r;
-          sbb += b * b;
+          return Terms<double, 2>{{r, b}, {r, b}};
         });
-    srr = wave_sum(srr);
-    sbb = wave_sum(sbb);
-    if (lane_id() == 0) {
-      A.P[0 * A.pstride + g] = srr;
-      A.P[1 * A.pstride + g] = sbb;
+    if (threadIdx.x == 0) {
+      A.P[0 * A.pstride + ref.g] = ts.sum[0];
+      A.P[1 * A.pstride + ref.g] = ts.sum[1];
     }
   }
 }
@@ -579,10 +654,11 @@ __global__ void __launch_bounds__(64) k_e_rhs(EArgs A, int mode) {
 // ||phi - phi_prev||^2 (slot 0) and ||phi_prev||^2 (slot 1);
 // op 5: phi = x_final (FP64 path).
 template <typename T>
-__global__ void __launch_bounds__(64) k_e_pass(EArgs A, int op) {
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_pass(EArgs A, int op) {
+  __shared__ double red[2 * 64];
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     double* phi = A.desc[tp.m].phi;
     double* pp = A.phi_prev + tp.off;
     const MapState& ms = A.ms[tp.m];
@@ -593,13 +669,13 @@ __global__ void __launch_bounds__(64) k_e_pass(EArgs A, int op) {
     const T* dp = cvec<T>((l & 1) ? A.d1 : A.d0, tp.off);
     const T ap = (T)ms.alpha_p;
     const bool pend = ms.alpha_p != 0.0;
-    double s0 = 0.0, s1 = 0.0;
+    TileSum<double, 2, kOrdered<T>> ts(red);  // op 4
     struct Px {
       double a, b;  // phi (ops 0, 1, 3, 4), phi_prev (op 4)
       T x, dd;      // final iterate and pending direction (ops 3, 5)
     };
     march_points_grouped<4>(
-        tp,
+        tp, ts,
         [&](int i, int j) {
           const size_t p = (size_t)i * tp.N + j;
           Px v{0.0, 0.0, T(0), T(0)};
@@ -613,6 +689,7 @@ __global__ void __launch_bounds__(64) k_e_pass(EArgs A, int op) {
         },
         [&](int i, int j, const Px& v) {
           const size_t p = (size_t)i * tp.N + j;
+          Terms<double, 2> t{{0.0, 0.0}, {0.0, 0.0}};
           switch (op) {
             case 0: pp[p] = v.a; break;
             case 1: x0[p] = (T)v.a; break;
@@ -620,19 +697,15 @@ __global__ void __launch_bounds__(64) k_e_pass(EArgs A, int op) {
             case 3: phi[p] = v.a + (double)(pend ? v.x + ap * v.dd : v.x); break;
             case 4: {
               const double dd = v.a - v.b;
-              s0 += dd * dd;
-              s1 += v.b * v.b;
+              t = Terms<double, 2>{{dd, v.b}, {dd, v.b}};
             } break;
             case 5: phi[p] = (double)(pend ? v.x + ap * v.dd : v.x); break;
           }
+          return t;
         });
-    if (op == 4) {
-      s0 = wave_sum(s0);
-      s1 = wave_sum(s1);
-      if (lane_id() == 0) {
-        A.P[0 * A.pstride + g] = s0;
-        A.P[1 * A.pstride + g] = s1;
-      }
+    if (op == 4 && threadIdx.x == 0) {
+      A.P[0 * A.pstride + ref.g] = ts.sum[0];
+      A.P[1 * A.pstride + ref.g] = ts.sum[1];
     }
   }
 }
@@ -643,10 +716,11 @@ __global__ void __launch_bounds__(64) k_e_pass(EArgs A, int op) {
 // init: r = b - A x0, d_old(parity 0) = 0, pointwise s; partials r.r, r.s, b.b
 // confirm (CONF = 1): r = b - A x (current parity), pointwise s; partials r.r, r.s
 template <typename T, int PC, int CONF>
-__global__ void __launch_bounds__(64) k_e_resid(EArgs A) {
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_resid(EArgs A) {
+  __shared__ double red[3 * 64];
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     const MapState& st = A.ms[tp.m];
     if (st.state != (CONF ? kConfirm : kRun)) continue;
     const long long l = st.l;
@@ -661,35 +735,30 @@ __global__ void __launch_bounds__(64) k_e_resid(EArgs A) {
     const bool pend = CONF && st.alpha_p != 0.0;
     T* r = vec<T>(A.r, tp.off);
     T* d0 = vec<T>(A.d0, tp.off);
-    const int M = tp.M, N = tp.N;
-    double srr = 0.0, srs = 0.0, sbb = 0.0;
-    march_tile<0, T>(tp, U, V,
-                     [&](int i, int j) {
-                       R3<T> v;  // x, unused, d (zero when no step is pending)
-                       v.s = ldz(x, i, j, M, N);
-                       v.w = T(1);
-                       v.d = pend ? ldz(dp, i, j, M, N) : T(0);
-                       return v;
-                     },
-                     [&](const R3<T>& v) { return pend ? v.s + ap * v.d : v.s; },
-                     [&](int i, int j, T, T ax) {
-                       const size_t p = (size_t)i * N + j;
-                       const T bv = b[p];
-                       const T rv = bv - ax;
-                       r[p] = rv;
-                       if (!CONF) d0[p] = T(0);
-                       const T sv = PC == kPcJacobi ? rv * aux[p] : rv;
-                       srr += (double)rv * (double)rv;
-                       srs += (double)rv * (double)sv;
-                       sbb += (double)bv * (double)bv;
-                     });
-    srr = wave_sum(srr);
-    srs = wave_sum(srs);
-    sbb = wave_sum(sbb);
-    if (lane_id() == 0) {
-      A.P[0 * A.pstride + g] = srr;
-      A.P[1 * A.pstride + g] = srs;
-      A.P[2 * A.pstride + g] = sbb;
+    TileSum<T, 3, kOrdered<T>> ts(red);  // r.r, r.s, b.b
+    struct Op {
+      T x, d;
+    };
+    struct Own {
+      T b, w;
+    };
+    stencil_tile<T>(
+        tp, ts, U, V, [&](size_t row, unsigned j) { return Op{x[row + j], pend ? dp[row + j] : T(0)}; },
+        [&](const Op& v, int, int) { return pend ? v.x + ap * v.d : v.x; },
+        [&](size_t row, unsigned j) {
+          return Own{b[row + j], PC == kPcJacobi ? aux[row + j] : T(1)};
+        },
+        [&](int, size_t row, unsigned j, T, T ax, const Op&, const Own& o) {
+          const T rv = o.b - ax;
+          r[row + j] = rv;
+          if (!CONF) d0[row + j] = T(0);
+          const T sv = PC == kPcJacobi ? rv * o.w : rv;
+          return Terms<T, 3>{{rv, rv, o.b}, {rv, sv, o.b}};
+        });
+    if (threadIdx.x == 0) {
+      A.P[0 * A.pstride + ref.g] = ts.sum[0];
+      A.P[1 * A.pstride + ref.g] = ts.sum[1];
+      A.P[2 * A.pstride + ref.g] = ts.sum[2];
     }
   }
 }
@@ -707,20 +776,25 @@ __device__ __forceinline__ void st_stream(T* p, T v) { __builtin_nontemporal_sto
 // leaves it here: x is first needed again by a replacement or at the end, and
 // this kernel reads d_old anyway, so the step costs one read and one write of
 // x instead of two reads, a write and a second read of d in the update).
-template <typename T, int PC, int TH>
-__global__ void __launch_bounds__(64) k_e_spmv(EArgs A) {
-  __shared__ double fred[3];
+template <typename T, int PC>
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_spmv(EArgs A) {
+  __shared__ double lsum[1 * 64];
+  __shared__ double fred[3 * kMaxTileWaves];
   __shared__ int fflag;
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     const MapState& st = A.ms[tp.m];
-    if (st.state != kRun) continue;
+    const int state = st.state, xi = st.xi;
     const long long l = st.l;
-    const T beta = (T)st.beta;
-    const T ap = (T)st.alpha_p;
-    const bool pend = st.alpha_p != 0.0;
-    T* x = vec<T>(st.xi ? A.x1 : A.x0, tp.off);
+    const double beta64 = st.beta, ap64 = st.alpha_p;
+    // requested together, with the descriptor
+    __asm__ volatile("" ::"s"(state), "s"(xi), "s"(l), "s"(beta64), "s"(ap64));
+    if (state != kRun) continue;
+    const T beta = (T)beta64;
+    const T ap = (T)ap64;
+    const bool pend = ap64 != 0.0;
+    T* x = vec<T>(xi ? A.x1 : A.x0, tp.off);
     const T* U = cvec<T>(A.U, tp.off);
     const T* V = cvec<T>(A.V, tp.off);
     const T* aux = cvec<T>(A.aux, tp.off);
@@ -728,40 +802,27 @@ __global__ void __launch_bounds__(64) k_e_spmv(EArgs A) {
     const T* dold = cvec<T>((l & 1) ? A.d1 : A.d0, tp.off);
     T* dnew = vec<T>((l & 1) ? A.d0 : A.d1, tp.off);
     T* q = vec<T>(A.q, tp.off);
-    const int M = tp.M, N = tp.N;
-    double sdq = 0.0;
-    // rows of the tile: x is loaded (with the operand's loads, two rows ahead)
-    // only for the tile's own elements, never for its halo
-    const int i_end = tp.i0 + (TH > 0 ? TH : tp.rows);
-    march_tile<TH, T>(
-        tp, U, V,
-        [&](int i, int j) {
-          bool ok;
-          const size_t p = clamp_at(i, j, M, N, ok);
-          // unconditional loads through the clamped index, zeroed outside the grid
-          const T s0 = src[p], d0 = dold[p];
-          R4<T> v;  // s (or r), inverse diagonal, d_old, x
-          v.s = ok ? s0 : T(0);
-          v.w = PC == kPcJacobi ? aux[p] : T(1);
-          v.d = ok ? d0 : T(0);
-          v.x = T(0);
-          if (pend && i >= tp.i0 && i < i_end && j >= tp.j0 && j < tp.j0 + kTW) v.x = ld_stream(x + p);
-          return v;
+    TileSum<T, 1, kOrdered<T>> ts(lsum);  // d_new^T q
+    struct Op {
+      T s, w, d;  // s (or r), inverse diagonal, d_old
+    };
+    stencil_tile<T>(
+        tp, ts, U, V,
+        [&](size_t row, unsigned j) {
+          return Op{src[row + j], PC == kPcJacobi ? aux[row + j] : T(1), dold[row + j]};
         },
-        [&](const R4<T>& v) { return (PC == kPcJacobi ? v.s * v.w : v.s) + beta * v.d; },
-        [&](int i, int j, T dv, T qv, const R4<T>& raw) {
-          const size_t p = (size_t)i * N + j;
-          st_stream(dnew + p, dv);
-          q[p] = qv;
-          if (pend) st_stream(x + p, raw.x + ap * raw.d);
-          sdq += (double)dv * (double)qv;
+        [&](const Op& v, int, int) { return (PC == kPcJacobi ? v.s * v.w : v.s) + beta * v.d; },
+        [&](size_t row, unsigned j) { return ld_stream(x + row + j); },
+        [&](int, size_t row, unsigned j, T dv, T qv, const Op& v, T xv) {
+          st_stream(dnew + row + j, dv);
+          q[row + j] = qv;
+          if (pend) st_stream(x + row + j, xv + ap * v.d);
+          return Terms<T, 1>{{dv}, {qv}};
         });
-    sdq = wave_sum(sdq);
-    if (lane_id() == 0) store_partial(A.P + 0 * A.pstride + g, sdq);
+    if (threadIdx.x == 0) store_partial(A.P + 0 * A.pstride + ref.g, ts.sum[0]);
     if (A.fuse_pw >= 0) {
-      const MapDesc& dm = A.desc[tp.m];
       const int sl[1] = {0};
-      fused_finish<kFinAlpha, 1>(arrival(A), sl, dm.tile0, g - dm.tile0, dm.ntiles, dm.gb, A.desc,
+      fused_finish<kFinAlpha, 1, 64>(arrival(A), sl, ref.g - tp.local, tp.local, tp.ntiles, tp.gb, A.desc,
                                  A.ms, tp.m, kFinishNone, A.fuse_pw, &fflag, fred);
     }
   }
@@ -770,107 +831,78 @@ __global__ void __launch_bounds__(64) k_e_spmv(EArgs A) {
 // update: r -= alpha q (the step alpha d is added to x by the next SpMV), or,
 // when l is a multiple of the replacement period, x_new = x + alpha d into
 // the other x buffer and r = b - A x_new; pointwise s; partials r.r, r.s
-// Five waves per SIMD fit without spills (96 VGPRs); the update is a short
-// stream, so the extra wave in flight helps a little (about 1 %).
-template <typename T, int PC, int TH>
-__global__ void __launch_bounds__(64, 5) k_e_update(EArgs A) {
-  __shared__ double fred[3];
+template <typename T, int PC>
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_update(EArgs A) {
+  __shared__ double lsum[2 * 64];
+  __shared__ double fred[3 * kMaxTileWaves];
   __shared__ int fflag;
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     const MapState& st = A.ms[tp.m];
-    if (st.state != kRun) continue;
-    const long long l = st.l;
-    const T alpha = (T)st.alpha;
-    const bool replace = (l % st.period) == 0;
+    const int state = st.state, xi = st.xi;
+    const long long l = st.l, period = st.period;
+    const double alpha64 = st.alpha;
+    // requested together, with the descriptor
+    __asm__ volatile("" ::"s"(state), "s"(xi), "s"(l), "s"(period), "s"(alpha64));
+    if (state != kRun) continue;
+    const T alpha = (T)alpha64;
+    const bool replace = (l % period) == 0;
     const T* U = cvec<T>(A.U, tp.off);
     const T* V = cvec<T>(A.V, tp.off);
     const T* aux = cvec<T>(A.aux, tp.off);
     const T* b = cvec<T>(A.b, tp.off);
     const T* q = cvec<T>(A.q, tp.off);
     T* r = vec<T>(A.r, tp.off);
-    const int M = tp.M, N = tp.N;
-    double srr = 0.0, srs = 0.0;
+    TileSum<T, 2, kOrdered<T>> ts(lsum);  // r.r, r.s
     if (replace) {
-      const T* xold = cvec<T>(st.xi ? A.x1 : A.x0, tp.off);
-      T* xnew = vec<T>(st.xi ? A.x0 : A.x1, tp.off);
+      const T* xold = cvec<T>(xi ? A.x1 : A.x0, tp.off);
+      T* xnew = vec<T>(xi ? A.x0 : A.x1, tp.off);
       const T* d = cvec<T>((l & 1) ? A.d0 : A.d1, tp.off);
-      march_tile<TH, T>(
-          tp, U, V,
-          [&](int i, int j) {
-            bool ok;
-            const size_t p = clamp_at(i, j, M, N, ok);
-            const T x0 = xold[p], d0 = d[p];
-            R3<T> v;  // x_old, unused, d; zeroed outside the grid
-            v.s = ok ? x0 : T(0);
-            v.w = T(1);
-            v.d = ok ? d0 : T(0);
-            return v;
+      struct Op {
+        T x, d;
+      };
+      struct Own {
+        T b, w;
+      };
+      stencil_tile<T>(
+          tp, ts, U, V, [&](size_t row, unsigned j) { return Op{xold[row + j], d[row + j]}; },
+          [&](const Op& v, int, int) { return v.x + alpha * v.d; },
+          [&](size_t row, unsigned j) {
+            return Own{b[row + j], PC == kPcJacobi ? aux[row + j] : T(1)};
           },
-          [&](const R3<T>& v) { return v.s + alpha * v.d; },
-          [&](int i, int j, T xv, T ax) {
-            const size_t p = (size_t)i * N + j;
-            const T rv = b[p] - ax;
-            xnew[p] = xv;
-            r[p] = rv;
-            const T sv = PC == kPcJacobi ? rv * aux[p] : rv;
-            srr += (double)rv * (double)rv;
-            srs += (double)rv * (double)sv;
+          [&](int, size_t row, unsigned j, T xv, T ax, const Op&, const Own& o) {
+            const T rv = o.b - ax;
+            xnew[row + j] = xv;
+            r[row + j] = rv;
+            const T sv = PC == kPcJacobi ? rv * o.w : rv;
+            return Terms<T, 2>{{rv, rv}, {rv, sv}};
           });
     } else {
-      // elementwise; loads through a clamped column (always executed, so the
-      // loads of several rows can be in flight), stores only on the map
-      const int l = lane_id();
-      const int ja = min(tp.j0 + l, N - 1), jb = min(tp.j0 + 64 + l, N - 1);
-      const bool oka = tp.j0 + l < N, okb = tp.j0 + 64 + l < N;
-      const int kend = min(TH > 0 ? TH : tp.rows, M - tp.i0);
-      // eight rows at a time: all loads of the group (through a clamped row)
-      // are issued before its first store, so 32 loads per wave are in flight
-      auto walk = [&](auto full_tag) {
-        constexpr bool FULL = decltype(full_tag)::value;
-        constexpr int G = 8;
-        for (int k0 = 0; k0 < kend; k0 += G) {
-          T rv[G][2], qv[G][2], wv[G][2];
-#pragma unroll
-          for (int c = 0; c < G; ++c) {
-            const size_t row = (size_t)min(tp.i0 + k0 + c, M - 1) * N;
-            const size_t pa = row + ja, pb = row + jb;
-            rv[c][0] = r[pa], rv[c][1] = r[pb];
-            qv[c][0] = ld_stream(q + pa), qv[c][1] = ld_stream(q + pb);
-            wv[c][0] = PC == kPcJacobi ? aux[pa] : T(1);
-            wv[c][1] = PC == kPcJacobi ? aux[pb] : T(1);
-          }
-#pragma unroll
-          for (int c = 0; c < G; ++c) {
-            if (k0 + c >= kend) break;  // uniform over the wave
-            const size_t row = (size_t)(tp.i0 + k0 + c) * N;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              if (!FULL && !(h ? okb : oka)) continue;
-              const size_t p = row + (h ? jb : ja);
-              const T rn = rv[c][h] - alpha * qv[c][h];
-              r[p] = rn;
-              const T sv = PC == kPcJacobi ? rn * wv[c][h] : rn;
-              srr += (double)rn * (double)rn;
-              srs += (double)rn * (double)sv;
-            }
-          }
-        }
+      struct Px {
+        T r, q, w;
       };
-      if (tp.j0 + kTW <= N) walk(std::true_type());
-      else walk(std::false_type());
+      march_points_grouped<kRWUpdate>(
+          tp, ts,
+          [&](int i, int j) {
+            const size_t row = (size_t)i * tp.N;
+            return Px{r[row + (unsigned)j], ld_stream(q + row + (unsigned)j),
+                      PC == kPcJacobi ? aux[row + (unsigned)j] : T(1)};
+          },
+          [&](int i, int j, const Px& v) {
+            const T rn = v.r - alpha * v.q;
+            r[(size_t)i * tp.N + (unsigned)j] = rn;
+            const T sv = PC == kPcJacobi ? rn * v.w : rn;
+            return Terms<T, 2>{{rn, rn}, {rn, sv}};
+          });
     }
-    srr = wave_sum(srr);
-    srs = wave_sum(srs);
-    if (lane_id() == 0) {
-      store_partial(A.P + 0 * A.pstride + g, srr);
-      store_partial(A.P + 1 * A.pstride + g, srs);
+    if (threadIdx.x == 0) {
+      store_partial(A.P + 0 * A.pstride + ref.g, ts.sum[0]);
+      store_partial(A.P + 1 * A.pstride + ref.g, ts.sum[1]);
     }
     if (A.fuse_pw >= 0) {
-      const MapDesc& dm = A.desc[tp.m];
       const int sl[2] = {0, 1};
-      fused_finish<kFinUpdate, 2>(arrival(A), sl, dm.tile0, g - dm.tile0, dm.ntiles, dm.gb, A.desc,
+      fused_finish<kFinUpdate, 2, 64>(arrival(A), sl, ref.g - tp.local, tp.local, tp.ntiles, tp.gb, A.desc,
                                   A.ms, tp.m, kFinishNone, A.fuse_pw, &fflag, fred);
     }
   }
@@ -893,10 +925,10 @@ __global__ void __launch_bounds__(64, 5) k_e_update(EArgs A) {
 // the colour it does not write.
 // ---------------------------------------------------------------------------
 template <typename T>
-__global__ void __launch_bounds__(64) k_e_tc_pivots(EArgs A, int ssor, double omega) {
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_tc_pivots(EArgs A, int ssor, double omega) {
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     const T* U = cvec<T>(A.U, tp.off);
     const T* V = cvec<T>(A.V, tp.off);
     T* piv = vec<T>(A.aux, tp.off);
@@ -931,13 +963,14 @@ __global__ void __launch_bounds__(64) k_e_tc_pivots(EArgs A, int ssor, double om
   }
 }
 
-template <typename T, int PASS, int TH>
-__global__ void __launch_bounds__(64) k_e_twocolor(EArgs A, T c) {
-  __shared__ double fred[3];
+template <typename T, int PASS>
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_twocolor(EArgs A, T c) {
+  __shared__ double lsum[64];
+  __shared__ double fred[3 * kMaxTileWaves];
   __shared__ int fflag;
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     if (A.ms[tp.m].state != A.expect) continue;
     const T* U = cvec<T>(A.U, tp.off);
     const T* V = cvec<T>(A.V, tp.off);
@@ -945,50 +978,45 @@ __global__ void __launch_bounds__(64) k_e_twocolor(EArgs A, T c) {
     const T* r = cvec<T>(A.r, tp.off);
     T* s = vec<T>(A.s, tp.off);
     const unsigned char* iso = A.iso + tp.off;
-    const int M = tp.M, N = tp.N;
-    double part = 0.0;
-    march_tile<TH, T>(
-        tp, U, V,
-        [&](int i, int j) {
-          bool ok;
-          const size_t p = clamp_at(i, j, M, N, ok);
-          const bool even = ((i + j) & 1) == 0;
-          R3<T> v;  // pass 0: r and the pivot on even pixels; pass 1: s on odd pixels
-          if (PASS == 0) {
-            const T r0 = r[p], p0 = piv[p];
-            v.s = ok && even ? r0 : T(0);
-            v.w = p0;
-          } else {
-            const T s0 = s[p];
-            v.s = ok && !even ? s0 : T(0);
-            v.w = T(1);
-          }
-          v.d = T(0);
-          return v;
+    TileSum<T, PASS, kOrdered<T>> ts(lsum);  // r^T s (pass 1)
+    struct Op {
+      T v, p;  // pass 0: r and the pivot; pass 1: s
+    };
+    struct Own {
+      T r, p;  // pass 1
+      unsigned char iso;
+    };
+    auto even = [](int i, int j) { return ((i + j) & 1) == 0; };
+    stencil_tile<T>(
+        tp, ts, U, V,
+        [&](size_t row, unsigned j) {
+          return Op{PASS == 0 ? r[row + j] : s[row + j], PASS == 0 ? piv[row + j] : T(1)};
         },
-        [&](const R3<T>& v) { return PASS == 0 ? v.s / v.w : v.s; },
-        [&](int i, int j, T xv, T ax) {
-          const size_t p = (size_t)i * N + j;
-          const bool even = ((i + j) & 1) == 0;
-          if (PASS == 0) {
-            if (!even) s[p] = iso[p] ? T(0) : c * (r[p] - ax) / piv[p];
+        [&](const Op& v, int i, int j) {
+          if (PASS == 0) return even(i, j) ? v.v / v.p : T(0);
+          return even(i, j) ? T(0) : v.v;
+        },
+        [&](size_t row, unsigned j) {
+          return Own{PASS == 1 ? r[row + j] : T(0), PASS == 1 ? piv[row + j] : T(1), iso[row + j]};
+        },
+        [&](int i, size_t row, unsigned j, T xv, T ax, const Op& v, const Own& o) {
+          if constexpr (PASS == 0) {
+            if (!even(i, j)) s[row + j] = o.iso ? T(0) : c * (v.v - ax) / v.p;
+            return Terms<T, 0>{};
           } else {
-            const T rv = r[p];
             T sv = xv;
-            if (even) {
-              sv = iso[p] ? T(0) : (c * rv - ax) / piv[p];
-              s[p] = sv;
+            if (even(i, j)) {
+              sv = o.iso ? T(0) : (c * o.r - ax) / o.p;
+              s[row + j] = sv;
             }
-            part += (double)rv * (double)sv;
+            return Terms<T, 1>{{o.r}, {sv}};
           }
         });
-    if (PASS == 1) {
-      part = wave_sum(part);
-      if (lane_id() == 0) store_partial(A.P + 1 * A.pstride + g, part);
+    if constexpr (PASS == 1) {
+      if (threadIdx.x == 0) store_partial(A.P + 1 * A.pstride + ref.g, ts.sum[0]);
       if (A.fin_mode) {
-        const MapDesc& dm = A.desc[tp.m];
-        const int sl[1] = {1};
-        fused_finish<kFinTailS, 1>(arrival(A), sl, dm.tile0, g - dm.tile0, dm.ntiles, dm.gb, A.desc,
+          const int sl[1] = {1};
+        fused_finish<kFinTailS, 1, 64>(arrival(A), sl, ref.g - tp.local, tp.local, tp.ntiles, tp.gb, A.desc,
                                    A.ms, tp.m, A.fin_mode, 0, &fflag, fred);
       }
     }
@@ -997,18 +1025,22 @@ __global__ void __launch_bounds__(64) k_e_twocolor(EArgs A, T c) {
 
 // y = A x for the step entry point (x in A.s, y in A.q)
 template <typename T>
-__global__ void __launch_bounds__(64) k_e_apply(EArgs A) {
+__global__ void __launch_bounds__(kMaxTileThreads) k_e_apply(EArgs A) {
   TILE_LOOP(A) {
-    const int g = TILE_G(A);
-    const TilePos tp = tile_pos(A.desc, A.tile_map, g);
+    const TileRef ref = TILE_REF(A);
+    const TilePos tp = tile_pos(A.desc, ref);
     const T* U = cvec<T>(A.U, tp.off);
     const T* V = cvec<T>(A.V, tp.off);
     const T* x = cvec<T>(A.s, tp.off);
     T* y = vec<T>(A.q, tp.off);
-    const int M = tp.M, N = tp.N;
-    march_tile<0, T>(tp, U, V, [&](int i, int j) { return ldz(x, i, j, M, N); },
-                     [](T v) { return v; },
-                     [&](int i, int j, T, T ax) { y[(size_t)i * N + j] = ax; });
+    TileSum<T, 0, false> ts(nullptr);
+    stencil_tile<T>(
+        tp, ts, U, V, [&](size_t row, unsigned j) { return x[row + j]; }, [](T v, int, int) { return v; },
+        [](size_t, unsigned) { return 0; },
+        [&](int, size_t row, unsigned j, T, T ax, T, int) {
+          y[row + j] = ax;
+          return Terms<T, 0>{};
+        });
   }
 }
 
@@ -1022,7 +1054,7 @@ __global__ void __launch_bounds__(256) k_e_finish(const MapDesc* __restrict__ de
   __shared__ double red[3 * 4];
   const int m = blockIdx.x;
   if (expect >= 0 && ms[m].state != expect) return;
-  const FinSrc src{P, pstride, nullptr, 0};
+  const FinSrc src{P, pstride, nullptr, 0, (int)blockDim.x};
   finish_map<false>(desc, ms, src, m, op, mode, pointwise, red);
 }
 
@@ -1038,11 +1070,14 @@ int egrid(const Engine& e, int ntiles) {
   return std::max(1, std::min(g, e.grid));
 }
 
+static int tile_threads(const Engine& e, int rows = kRW) {
+  return 64 * std::min((e.th + rows - 1) / rows, kMaxTileWaves);
+}
+
 EArgs make_args(const Engine& e) {
   EArgs a;
   a.desc = e.desc;
   a.ms = e.ms;
-  a.tile_map = e.tile_map;
   a.act = e.act;
   a.act_cap = (int)e.cap_tiles;
   a.counts = e.counts;
@@ -1075,43 +1110,43 @@ EArgs make_args(const Engine& e) {
 }
 
 void e_wrapdiff(hipStream_t st, const Engine& e, int ntiles, bool zero_phi) {
-  hipLaunchKernelGGL(k_e_wrapdiff, dim3(egrid(e, ntiles)), dim3(64), 0, st, make_args(e),
+  hipLaunchKernelGGL(k_e_wrapdiff, dim3(egrid(e, ntiles)), dim3(tile_threads(e)), 0, st, make_args(e),
                      zero_phi ? 1 : 0);
 }
 
 void e_check(hipStream_t st, const Engine& e, int ntiles, unsigned int* bad) {
-  hipLaunchKernelGGL(k_e_check, dim3(egrid(e, ntiles)), dim3(64), 0, st, make_args(e), bad);
+  hipLaunchKernelGGL(k_e_check, dim3(egrid(e, ntiles)), dim3(tile_threads(e)), 0, st, make_args(e), bad);
 }
 
 template <typename T>
 void e_weights(hipStream_t st, const Engine& e, int ntiles, double p, double tau) {
-  hipLaunchKernelGGL(k_e_weights<T>, dim3(egrid(e, ntiles)), dim3(64), 0, st, make_args(e),
+  hipLaunchKernelGGL(k_e_weights<T>, dim3(egrid(e, ntiles)), dim3(tile_threads(e)), 0, st, make_args(e),
                      2.0 - p, tau);
 }
 
 template <typename T>
 void e_diag(hipStream_t st, const Engine& e, int ntiles, bool inv) {
-  hipLaunchKernelGGL(k_e_diag<T>, dim3(egrid(e, ntiles)), dim3(64), 0, st, make_args(e),
+  hipLaunchKernelGGL(k_e_diag<T>, dim3(egrid(e, ntiles)), dim3(tile_threads(e)), 0, st, make_args(e),
                      inv ? 1 : 0);
 }
 
 template <typename T>
 void e_rhs(hipStream_t st, const Engine& e, int ntiles, int mode) {
-  hipLaunchKernelGGL(k_e_rhs<T>, dim3(egrid(e, ntiles)), dim3(64), 0, st, make_args(e), mode);
+  hipLaunchKernelGGL(k_e_rhs<T>, dim3(egrid(e, ntiles)), dim3(tile_threads(e)), 0, st, make_args(e), mode);
 }
 
 template <typename T>
 void e_pass(hipStream_t st, const Engine& e, int ntiles, int op) {
-  hipLaunchKernelGGL(k_e_pass<T>, dim3(egrid(e, ntiles)), dim3(64), 0, st, make_args(e), op);
+  hipLaunchKernelGGL(k_e_pass<T>, dim3(egrid(e, ntiles)), dim3(tile_threads(e)), 0, st, make_args(e), op);
 }
 
 template <typename T, int PC>
 static void e_resid_pc(hipStream_t st, const Engine& e, int ntiles, bool confirm) {
   if (confirm)
-    hipLaunchKernelGGL((k_e_resid<T, PC, 1>), dim3(egrid(e, ntiles)), dim3(64), 0, st,
+    hipLaunchKernelGGL((k_e_resid<T, PC, 1>), dim3(egrid(e, ntiles)), dim3(tile_threads(e)), 0, st,
                        make_args(e));
   else
-    hipLaunchKernelGGL((k_e_resid<T, PC, 0>), dim3(egrid(e, ntiles)), dim3(64), 0, st,
+    hipLaunchKernelGGL((k_e_resid<T, PC, 0>), dim3(egrid(e, ntiles)), dim3(tile_threads(e)), 0, st,
                        make_args(e));
 }
 
@@ -1125,13 +1160,7 @@ template <typename T, int PC>
 static void e_spmv_pc(hipStream_t st, const Engine& e, int gr, int fuse_pw) {
   EArgs a = make_args(e);
   a.fuse_pw = fuse_pw;
-  switch (e.th) {
-    case 4: hipLaunchKernelGGL((k_e_spmv<T, PC, 4>), dim3(gr), dim3(64), 0, st, a); break;
-    case 8: hipLaunchKernelGGL((k_e_spmv<T, PC, 8>), dim3(gr), dim3(64), 0, st, a); break;
-    case 16: hipLaunchKernelGGL((k_e_spmv<T, PC, 16>), dim3(gr), dim3(64), 0, st, a); break;
-    case 32: hipLaunchKernelGGL((k_e_spmv<T, PC, 32>), dim3(gr), dim3(64), 0, st, a); break;
-    default: hipLaunchKernelGGL((k_e_spmv<T, PC, 0>), dim3(gr), dim3(64), 0, st, a); break;
-  }
+  hipLaunchKernelGGL((k_e_spmv<T, PC>), dim3(gr), dim3(tile_threads(e)), 0, st, a);
 }
 
 // fused: the launch also runs the per-map finisher of its partials (alpha
@@ -1150,13 +1179,7 @@ template <typename T, int PC>
 static void e_update_pc(hipStream_t st, const Engine& e, int gr, int fuse_pw) {
   EArgs a = make_args(e);
   a.fuse_pw = fuse_pw;
-  switch (e.th) {
-    case 4: hipLaunchKernelGGL((k_e_update<T, PC, 4>), dim3(gr), dim3(64), 0, st, a); break;
-    case 8: hipLaunchKernelGGL((k_e_update<T, PC, 8>), dim3(gr), dim3(64), 0, st, a); break;
-    case 16: hipLaunchKernelGGL((k_e_update<T, PC, 16>), dim3(gr), dim3(64), 0, st, a); break;
-    case 32: hipLaunchKernelGGL((k_e_update<T, PC, 32>), dim3(gr), dim3(64), 0, st, a); break;
-    default: hipLaunchKernelGGL((k_e_update<T, PC, 0>), dim3(gr), dim3(64), 0, st, a); break;
-  }
+  hipLaunchKernelGGL((k_e_update<T, PC>), dim3(gr), dim3(tile_threads(e, kRWUpdate)), 0, st, a);
 }
 
 template <typename T>
@@ -1170,19 +1193,13 @@ void e_update(hipStream_t st, const Engine& e, int ntiles, int pc, bool fused) {
 
 template <typename T>
 void e_tc_pivots(hipStream_t st, const Engine& e, int ntiles, bool ssor, double omega) {
-  hipLaunchKernelGGL(k_e_tc_pivots<T>, dim3(egrid(e, ntiles)), dim3(64), 0, st, make_args(e),
+  hipLaunchKernelGGL(k_e_tc_pivots<T>, dim3(egrid(e, ntiles)), dim3(tile_threads(e)), 0, st, make_args(e),
                      ssor ? 1 : 0, omega);
 }
 
 template <typename T, int PASS>
 static void e_twocolor_pass(hipStream_t st, const Engine& e, int gr, const EArgs& a, T c) {
-  switch (e.th) {
-    case 4: hipLaunchKernelGGL((k_e_twocolor<T, PASS, 4>), dim3(gr), dim3(64), 0, st, a, c); break;
-    case 8: hipLaunchKernelGGL((k_e_twocolor<T, PASS, 8>), dim3(gr), dim3(64), 0, st, a, c); break;
-    case 16: hipLaunchKernelGGL((k_e_twocolor<T, PASS, 16>), dim3(gr), dim3(64), 0, st, a, c); break;
-    case 32: hipLaunchKernelGGL((k_e_twocolor<T, PASS, 32>), dim3(gr), dim3(64), 0, st, a, c); break;
-    default: hipLaunchKernelGGL((k_e_twocolor<T, PASS, 0>), dim3(gr), dim3(64), 0, st, a, c); break;
-  }
+  hipLaunchKernelGGL((k_e_twocolor<T, PASS>), dim3(gr), dim3(tile_threads(e)), 0, st, a, c);
 }
 
 // s = M^-1 r of the two-colour preconditioner for the maps in state `expect`;
@@ -1201,7 +1218,7 @@ void e_twocolor(hipStream_t st, const Engine& e, int ntiles, int expect, bool ss
 
 template <typename T>
 void e_apply(hipStream_t st, const Engine& e, int ntiles) {
-  hipLaunchKernelGGL(k_e_apply<T>, dim3(egrid(e, ntiles)), dim3(64), 0, st, make_args(e));
+  hipLaunchKernelGGL(k_e_apply<T>, dim3(egrid(e, ntiles)), dim3(tile_threads(e)), 0, st, make_args(e));
 }
 
 void e_finish(hipStream_t st, const Engine& e, int op, int expect, int mode, bool pointwise) {

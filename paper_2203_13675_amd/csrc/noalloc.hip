@@ -40,14 +40,13 @@ constexpr int kNoAllocMaxStrips = (int)(kNoAllocMaxPixels / 64);  // a map one p
 // edge entries 2 ceil(M / 64) N of a map of at most 4096 columns
 constexpr size_t kNoAllocEdges = 2 * ((size_t)kNoAllocMaxPixels / 64 + 4096);
 // counts, one active map, its strips, tiles
-constexpr size_t kListInts = kListHead + 1 + 2 * (size_t)kNoAllocMaxStrips + kNoAllocMaxTiles;
+constexpr size_t kListInts = kListHead + 1 + 2 * (size_t)kNoAllocMaxStrips + 2 * (size_t)kNoAllocMaxTiles;
 constexpr size_t kOffCounts = kOffState + al256(sizeof(MapState));
-constexpr size_t kOffTileMap = kOffCounts + al256(4 * kListInts);
 constexpr size_t kGroups = kNoAllocMaxTiles / kArriveGroup + 8;
-constexpr size_t kOffFcnt = kOffTileMap + al256(4 * (size_t)kNoAllocMaxTiles);
+constexpr size_t kOffFcnt = kOffCounts + al256(4 * kListInts);
 constexpr size_t kOffGcnt = kOffFcnt + 256;
 constexpr long long kPstride = kNoAllocMaxTiles + 64;
-constexpr size_t kOffP = kOffGcnt + al256(4 * kGroups);
+constexpr size_t kOffP = kOffGcnt + al256(4 * kGroups * kArriveStride);
 constexpr size_t kOffAux = kOffP + al256(8 * (size_t)kNumSlots * kPstride);
 constexpr size_t kOffT1 = kOffAux + al256(8 * (size_t)kNoAllocMaxPixels);
 constexpr size_t kOffIso = kOffT1 + al256(8 * (size_t)kNoAllocMaxPixels);
@@ -84,7 +83,7 @@ static void* scratch_of(int device) {
 
 // Descriptor, state and tile lists of one M x N map at element offset 0 with
 // `th`-row stencil tiles; clears the arrival counters.
-__global__ void k_na_layout(MapDesc* desc, MapState* ms, int* counts, int* tile_map, int* fcnt,
+__global__ void k_na_layout(MapDesc* desc, MapState* ms, int* counts, int* fcnt,
                             int* gcnt, unsigned int* wctl, int M, int N, int th, int ntiles, int ngroups,
                             int nstrips) {
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
@@ -97,10 +96,10 @@ __global__ void k_na_layout(MapDesc* desc, MapState* ms, int* counts, int* tile_
     slist[2 * t + 1] = t;
   }
   for (int t = tid; t < ntiles; t += nth) {
-    tile_map[t] = 0;
-    act[t] = t;
+    act[2 * t] = t;
+    act[2 * t + 1] = 0;
   }
-  for (int g = tid; g < ngroups; g += nth) gcnt[g] = 0;
+  for (int g = tid; g < ngroups; g += nth) gcnt[kArriveStride * g] = 0;
   if (tid == 0) {
     MapDesc d;
     d.M = M;
@@ -169,7 +168,6 @@ static int apply(lp_unwrap_ctx* ctx, int M, int N, int pc, double omega, const T
   e.mact = e.counts + kListHead;
   e.slist = e.mact + 1;
   e.act = e.slist + 2 * kNoAllocMaxStrips;
-  e.tile_map = reinterpret_cast<int*>(base + kOffTileMap);
   e.fcnt = reinterpret_cast<int*>(base + kOffFcnt);
   e.gcnt = reinterpret_cast<int*>(base + kOffGcnt);
   e.P = reinterpret_cast<double*>(base + kOffP);
@@ -184,7 +182,7 @@ static int apply(lp_unwrap_ctx* ctx, int M, int N, int pc, double omega, const T
   e.r = const_cast<T*>(r);
   e.s = s;
   const int lg = std::max(1, std::min(1024, (ntiles + 255) / 256));
-  hipLaunchKernelGGL(k_na_layout, dim3(lg), dim3(256), 0, st, e.desc, e.ms, e.counts, e.tile_map,
+  hipLaunchKernelGGL(k_na_layout, dim3(lg), dim3(256), 0, st, e.desc, e.ms, e.counts,
                      e.fcnt, e.gcnt, e.wctl, M, N, th, ntiles, ngroups, e.total_strips);
   // as lpu_precond_apply: isolation flags (and the inverse diagonal for Jacobi)
   e_diag<T>(st, e, ntiles, pc == kPcJacobi);
