@@ -29,6 +29,12 @@ static float bf16_to_f32(uint16_t h) {
   return f;
 }
 
+// Position of (row, col) in a matrix of K columns kept in blocks of 16 rows by
+// 32 columns (the layout the even/odd kernels read, eo_at).
+static size_t block_at(size_t row, size_t col, size_t K) {
+  return row / 16 * 16 * K + col / 32 * 512 + row % 16 * 32 + col % 32;
+}
+
 static void free_tables(DctTables& t) {
   void* tp[] = {t.c64,   t.ct64,   t.c32,  t.ct32,   t.c_hi,   t.c_lo, t.ct_hi,    t.ct_lo, t.c_h,
                 t.ct_h,  t.lam,    t.eo_hi, t.eo_lo, t.eo_h, t.eot_hi, t.eot_lo, t.eot_h, t.lam_split};
@@ -106,13 +112,14 @@ const DctTables* get_dct_tables(lp_unwrap_ctx* ctx, int n, int* status) {
         const _Float16 hv = (_Float16)v;
         uint16_t hb;
         std::memcpy(&hb, &hv, 2);
-        // EO[c][j] and EOt[j][c]
-        eh[(size_t)c * h + j] = hi;
-        el[(size_t)c * h + j] = lo;
-        e16[(size_t)c * h + j] = hb;
-        th[(size_t)j * n + c] = hi;
-        tl[(size_t)j * n + c] = lo;
-        t16[(size_t)j * n + c] = hb;
+        // EO[c][j] and EOt[j][c], in blocks of 16 x 32
+        const size_t o = block_at(c, j, h), ot = block_at(j, c, n);
+        eh[o] = hi;
+        el[o] = lo;
+        e16[o] = hb;
+        th[ot] = hi;
+        tl[ot] = lo;
+        t16[ot] = hb;
       }
     }
     up((void**)&t.eo_hi, eh.data(), nh * 2);

@@ -37,7 +37,7 @@ void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int ex
                  const void* X, void* Out, const void* rvec, int fin_mode);
 int egrid(const Engine& e, int ntiles);
 int dct_grid_for(const Engine& e, int ndtiles);
-bool dct_wide_for(const Engine& e, int ndtiles, int kind);
+int dct_shape_for(const Engine& e, int ndtiles, int kind);
 int dct_side(int M, int N, bool fp64);
 template <typename T> void e_pivots(hipStream_t, const Engine&, int, bool, double, bool);
 int wf_strips(int M);
@@ -156,11 +156,12 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     d.dtr = dct_tile ? dct_tile : dct_side(d.M, d.N, elem == 8);
     d.ndt = ((d.M + d.dtr - 1) / d.dtr) * ((d.N + d.dtr - 1) / d.dtr);
     d.dtile0 = dtiles;
+    d.dparts = dct_tile == 128 ? kEoParts : 1;
     dtiles += d.ndt;
     d.gb = groups;
     groups += (d.ntiles + kArriveGroup - 1) / kArriveGroup;
     d.gbd = groups;
-    groups += (d.ndt + kArriveGroup - 1) / kArriveGroup;
+    groups += (d.ndt * d.dparts + kArriveGroup - 1) / kArriveGroup;
     d.off = px;
     px += ((long long)d.M * d.N + 63) / 64 * 64;
     d.psi = maps[m].psi;
@@ -187,7 +188,7 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     engine_free(e);
     const long long cpx = std::max(px, 1LL);
     const size_t eb = (size_t)cpx * elem;
-    const long long pst = std::max(tiles, dtiles) + 64;
+    const long long pst = std::max<long long>(tiles, (long long)kEoParts * dtiles) + 64;
     bool ok = true;
     auto A = [&](void** p, size_t bytes) {
       if (ok && hipMalloc(p, std::max<size_t>(bytes, 256)) != hipSuccess) ok = false;
@@ -212,8 +213,8 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     A((void**)&e.fcnt, 4 * (size_t)n * kArriveStride);
     A((void**)&e.wctl, 256);
     A((void**)&e.wedge, 8 * (size_t)edges);
-    // groups <= tiles / G + dtiles / G + 2 n for any layout within these capacities
-    const long long gcap = (long long)(tiles + dtiles) / kArriveGroup + 2LL * n + 8;
+    // groups <= tiles / G + kEoParts dtiles / G + 2 n for any layout within these capacities
+    const long long gcap = (tiles + (long long)kEoParts * dtiles) / kArriveGroup + 2LL * n + 8;
     A((void**)&e.gcnt, 4 * (size_t)gcap * kArriveStride);
     A((void**)&e.gsum, 8 * 2 * (size_t)gcap);
     A((void**)&e.dx, 8 * (size_t)cpx);
@@ -556,7 +557,7 @@ struct Pcg {
     for (int chunk = 8; chunk >= 1; chunk >>= 1) {
       if (K < chunk) continue;
       const int key[kGraphKey] = {egrid(e, nt), pointwise() ? 0 : dct_grid_for(e, nd),
-                                  pc == kPcDct && (dct_wide_for(e, nd, dct_kind) || e.dct_tile64) ? 1 : 0,
+                                  pc == kPcDct ? dct_shape_for(e, nd, dct_kind) : 0,
                                   sweep ? wf_grid(e) : 0, pc, dct_kind,
                                   (int)sizeof(T), e.th, om[0], om[1], chunk};
       hipGraphExec_t ex = nullptr;

@@ -27,6 +27,7 @@ constexpr int kEngineGrid = 16384;  // default cap on the blocks of the grid-str
 constexpr int kDctGrid = 2048;     // default cap on the blocks of a DCT stage
 constexpr int kArriveGroup = 32;   // tiles per first-level arrival counter of the fused finishers
 constexpr int kArriveStride = 64;  // ints from one arrival counter to the next (a 256-byte line each)
+constexpr int kEoParts = 4;        // partials of r^T s of an even/odd DCT tile, one per quarter
 constexpr int kNumSlots = 4;       // partial-sum slots
 constexpr int kListHead = 16;      // ints of counts[] ahead of the active-map list
 
@@ -60,6 +61,7 @@ struct MapDesc {
   int th;                     // stencil tile height (rows)
   int tiles_x, ntiles, tile0;  // stencil tiles
   int ndt, dtile0;             // DCT tiles (same count in every stage)
+  int dparts;                  // partials of r^T s per DCT tile: kEoParts (even/odd MFMA) or 1
   int dtr;                     // side of a DCT tile: 128 (even/odd MFMA), 64 or 32
   int gb, gbd;                 // first arrival-group counter of the stencil / DCT tiles
   int use_iso;                 // zero the preconditioner output on isolated pixels

@@ -101,16 +101,26 @@ __device__ __forceinline__ float fp16_scale(float amax) {
 //   inverse: half 0 = u (spectrum columns [0, h)), half 1 = v (columns
 //            [h, n)), combined at the end into outputs c and n-1-c.
 // Wave w computes rows 64 (w & 1) .. +63 of half w >> 1 as 4 x 4 MFMA tiles
-// of 16 x 16 (64 accumulator registers).  Each K step of KS (32 for the bf16
-// split, 64 for fp16, whose operands take half the registers) stages both
-// halves of A (128 x KS) and of the table slice (64 x KS) in LDS, converted
-// once to bf16 hi/lo (or scaled fp16); the next step's global loads are in
-// flight while the MFMAs of the current one run, so a longer step keeps more
-// bytes in flight per block.  LDS rows are KS 16-bit values without padding;
-// the 16-byte chunk q of row r sits at q ^ swz(r), which keeps both the
-// staging writes and the fragment reads free of bank conflicts (rows of 4
-// chunks: 8 rows read in one LDS cycle land in 8 distinct bank quads; rows of
-// 8 chunks: likewise for 8 or 16 rows).
+// of 16 x 16 (64 accumulator registers).  Each K step stages both halves of A
+// and of the table slice in LDS, A converted on the way to bf16 hi/lo (or
+// scaled fp16).  LDS rows are KS 16-bit values without padding; the 16-byte
+// chunk q of row r sits at q ^ swz(r), which keeps both the staging writes and
+// the fragment reads free of bank conflicts (rows of 4 chunks: 8 rows read in
+// one LDS cycle land in 8 distinct bank quads; rows of 8 chunks: likewise for 8
+// or 16 rows).
+//
+// What bounds it: a block's steps.  Small launches wait for memory, so the
+// operands of two steps are held in registers on top of the two buffers in
+// LDS (one barrier a step), and tiles are a quarter as large; large ones share
+// their time between matrix cores, LDS and the L1 fill (28 to 35 us each of
+// a 4096^2 fp16 stage's 81 to 105), so the tile is as wide as the registers
+// allow, which leaves room for one step in registers only (two: 5 to 10 %
+// slower), and the 16-bit matrices are laid out for whole lines (eo_at: 427
+// against 385 us for the four stages; half-line requests had the L1 wait half
+// of its cycles).  KS = 64 with one buffer: 465.  Four stages, one launch, us,
+// against the kernel before (KS = 64, one buffer, one step ahead, row-major, 128
+// rows for every launch): 1024^2 fp16 36 / 65, bf16 split 64 / 115, 2048^2 fp16
+// 96 / 117, 4096^2 fp16 385 / 489.
 // ---------------------------------------------------------------------------
 template <int NC>
 __device__ __forceinline__ int swz(int r) {
@@ -122,62 +132,80 @@ __device__ __forceinline__ int lds_at(int r, int q) { return r * (8 * NC) + ((q 
 
 typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 
-// NW: 16-column groups per wave.  NW = 4 is the tile described above
-// (64 output pairs).  NW = 8 (scaled fp16 only, 32-wide K steps) covers two
-// such tiles side by side, 128 output pairs, from the same staged rows of X:
-// half the re-reads of X and less LDS traffic per output.  It pays on
-// launches of many tiles only (half as many tiles to spread over the CUs):
-// the first three stages of the batch's launches of at least 1024 list
-// positions take 6-9 % less time, those of a 4096 x 4096 map 15 % less.  A
-// wide tile is named by its left narrow tile; where the map has no right
-// partner (h an odd multiple of 64) it stages its own table rows twice and
-// stores the left half only.  Per output the MFMAs run over the same K
-// chunks in the same order in both shapes, so the outputs are identical.
-template <int SPLIT, int INV, int IN16, int OUT16, int NW>
+// The 16-bit matrices of these stages (tables, and the scaled-fp16 values
+// between the stages) lie in blocks of 16 rows by 32 columns, row by row in
+// each, so that one load of a wave, 16 rows of a K step, is 1 KB on end.
+// Offset of (row, col) in a matrix of K columns, from a row that starts a block.
+template <typename I>
+__device__ __forceinline__ I eo_at(I row, I col, I K) {
+  return (row & ~I(15)) * K + (col >> 5) * 512 + (row & 15) * 32 + (col & 31);
+}
+
+// Tile shapes: the tile above (NI = NJ = 4: 4 x 4 MFMA tiles a wave); NJ = 8
+// (scaled fp16 only), "wide": two such tiles side by side, 128 output pairs,
+// from the same staged rows of X; NI = NJ = 2, "fine": a quarter of the tile,
+// 64 rows and 32 output pairs, four blocks to a list entry.  A wide tile is
+// named by its left narrow tile; where the map has no right partner (h an odd
+// multiple of 64) it stages its own table rows twice and stores the left half
+// only.  Per output the MFMAs run over the same K chunks in the same order in
+// every shape, and stage 3 writes one partial of r^T s per quarter tile, summed
+// in one order whatever the shape, so the results are identical.
+template <int SPLIT, int INV, int IN16, int OUT16, int NI, int NJ>
 __global__ void __launch_bounds__(256, 2) k_e_dct_eo(DArgs a) {
-  static_assert(NW == 4 || (NW == 8 && !SPLIT && OUT16), "wide tiles: scaled fp16, stages 0-2");
+  static_assert((NI == 4 && NJ == 4) || (NI == 2 && NJ == 2) ||
+                    (NI == 4 && NJ == 8 && !SPLIT), "wide tiles: scaled fp16");
+  constexpr bool FINE = NI == 2;
   constexpr int NP = SPLIT ? 2 : 1;                // hi (+ lo) planes
-  constexpr int KS = (SPLIT || NW == 8) ? 32 : 64;  // K step
+  constexpr int KS = FINE ? 64 : 32;                      // K step
+  constexpr int NBUF = SPLIT ? 1 : 2;
+  constexpr int DEPTH = NJ == 8 || (SPLIT && !FINE) ? 1 : 2;
   constexpr int NC = KS / 8;                       // 16-byte chunks per LDS row
-  constexpr int kBW = 16 * NW;                     // table rows per half (output pairs)
-  constexpr int kA = 128 * KS, kB = kBW * KS;      // elements of one A / B half-plane
-  constexpr int kStage = NP * 2 * (kA + kB) * 2;   // bytes of staged operands
-  constexpr int kXchg = 2 * 2 * 16 * 64 * 16;      // bytes of the inverse's u/v exchange (4 column groups)
-  constexpr int kSmem = kStage > kXchg ? kStage : kXchg;
+  constexpr int TR = 32 * NI;                      // rows of X
+  constexpr int kBW = 16 * NJ;                     // table rows per half (output pairs)
+  constexpr int kA = TR * KS, kB = kBW * KS;       // elements of one A / B half-plane
+  constexpr int kBuf = NP * 2 * (kA + kB);         // elements of one step's operands
+  constexpr int JR = NJ < 4 ? NJ : 4;              // column groups per round of the inverse's exchange
+  constexpr int kXchg = INV ? 2 * 2 * NI * JR * 64 * 16 : 0;  // its bytes
+  constexpr int kSmem = NBUF * kBuf * 2 > kXchg ? NBUF * kBuf * 2 : kXchg;
   constexpr int VPT = IN16 ? 8 : 4;                // X staging: values per thread and load
   constexpr int TPR = KS / VPT;                    // X staging: threads per row
-  constexpr int XP = 128 * TPR / 256;              // X staging passes (rows xr + XP-stride)
+  constexpr int XP = TR * TPR / 256;               // X staging passes (rows xr + XP-stride)
   constexpr int SEGS = 256 / NC;                   // table staging: segments per pass
   constexpr int TP = NP * 2 * kBW / SEGS;          // table staging passes
-  static_assert(NW == 4 || SEGS == 64, "wide tiles: a pass stages 64 rows of one half");
+  static_assert(XP >= 1 && TP >= 1, "a pass of the block covers at most one step");
+  static_assert(kBW % SEGS == 0, "a pass stages rows of one half and plane");
   __shared__ __attribute__((aligned(16))) unsigned char smem[kSmem];
-  __shared__ double red[4];
+  __shared__ double red[4 * NJ];
   __shared__ double fred[3 * 4];
   __shared__ int fflag;
-  uint16_t* As = reinterpret_cast<uint16_t*>(smem);  // [plane][half][128 x KS]
-  uint16_t* Bs = As + NP * 2 * kA;                   // [plane][half][kBW x KS]
   const int nact = a.counts[a.cidx];
+  // list position and quarter of a block's k-th tile: the four quarters of a
+  // list entry go to blocks 8 apart, so to the XCD of the entry
+  auto pos_of = [](int b) { return FINE ? (b >> 5) * 8 + (b & 7) : b; };
   // the block's first list entry is requested with the list's length
-  const int g_first = a.dact[min((int)blockIdx.x, max(a.dact_cap - 1, 0))];
+  const int g_first = a.dact[min(pos_of((int)blockIdx.x), max(a.dact_cap - 1, 0))];
   __asm__ volatile("" ::"s"(nact), "s"(g_first));  // both loads issued before the loop test
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63;
-  const int wr = (w & 1) * 64, hf = w >> 1;
+  const int wr = (w & 1) * 16 * NI, hf = w >> 1;
   const int lr = lane & 15, kq = lane >> 4;        // MFMA operand map: row lr, k chunk kq
   const int xr = tid / TPR, xk = (tid % TPR) * VPT;  // X staging: rows xr + (256/TPR) p, k xk ..
   static_assert(!(SPLIT && (IN16 || OUT16)), "the bf16 split keeps FP32 intermediates");
   const int bseg = tid / NC, bq = tid % NC;         // table staging: segment, 16-byte chunk
-  for (int t_ = blockIdx.x; t_ < nact; t_ += gridDim.x) {
-    const int g = t_ == (int)blockIdx.x ? g_first : a.dact[t_];
+  for (int t_ = blockIdx.x; FINE ? (t_ >> 5) * 8 < nact : t_ < nact; t_ += gridDim.x) {
+    const int pos = pos_of(t_), quarter = FINE ? (t_ >> 3) & 3 : 0;
+    if (FINE && pos >= nact) continue;
+    const int g = t_ == (int)blockIdx.x ? g_first : a.dact[pos];
     if (g < 0) continue;  // padding slot of the XCD-ordered list
-    // the tile's record (one load); its first K step is fetched before the
+    // the tile's record (one load); its first K steps are fetched before the
     // map's state is read, so the two round trips overlap
     const EoTile& tt = a.eot[(size_t)(a.stage & 1) * a.eot_cap + g];
-    const int R = tt.R, n = tt.K, h = n >> 1, c0 = tt.c0, r0 = tt.r0, tm = tt.m;
+    const int R = tt.R, n = tt.K, h = n >> 1, tm = tt.m;
+    const int c0 = tt.c0 + 32 * (quarter >> 1), r0 = tt.r0 + 64 * (quarter & 1);
     const long long toff = tt.off;
     const int t_local = tt.local, t_ndt = tt.ndt, t_gbd = tt.gbd;
     const float t_lmin = tt.lmin;
     // wide tiles: does the right partner exist (uniform over the block)?
-    const bool full = NW == 4 || c0 + 128 <= h;
+    const bool full = NJ != 8 || c0 + 128 <= h;
     const double* t_lam_m = tt.lam_m;
     const double* t_lam_n = tt.lam_n;
     const float* X = reinterpret_cast<const float*>(a.X) + toff;
@@ -188,48 +216,64 @@ __global__ void __launch_bounds__(256, 2) k_e_dct_eo(DArgs a) {
     const uint16_t* T1 = INV ? tt.ti[2] : tt.tf[2];
     float xs = 1.0f, inv_xs = 1.0f, os = 1.0f;
     // register staging of one K step
-    float4 sa[IN16 ? 1 : XP], sb[IN16 ? 1 : XP];
-    u16x8 ha[IN16 ? XP : 1], hb[IN16 ? XP : 1];
-    u16x8 sT[TP];
-    auto fetch = [&](int k0) {
+    struct Held {
+      float4 sa[IN16 ? 1 : XP], sb[IN16 ? 1 : XP];
+      u16x8 ha[IN16 ? XP : 1], hb[IN16 ? XP : 1];
+      u16x8 sT[TP];
+    };
+    // a load's address is a uniform base, which moves with the step, and a
+    // 32-bit offset of the lane, which does not
+    unsigned xa[XP], xb[XP], to[TP];
+#pragma unroll
+    for (int p = 0; p < XP; ++p) {
+      const unsigned row = xr + (256 / TPR) * p;
+      const unsigned kb = INV ? xk : KS - VPT - xk;  // forward: from the top, mirrored
+      xa[p] = IN16 ? eo_at<unsigned>(row, xk, n) : row * (unsigned)n + xk;
+      xb[p] = IN16 ? eo_at<unsigned>(row, kb, n) : row * (unsigned)n + kb;
+    }
+#pragma unroll
+    for (int p = 0; p < TP; ++p) {
+      // a wide tile without its partner stages its own rows twice (the
+      // extra outputs are computed but never stored)
+      const int s = p * SEGS + bseg, row = full ? s % kBW : s % 64;
+      to[p] = eo_at<unsigned>(row, 8 * bq, INV ? n : h);
+    }
+    auto fetch = [&](Held& v, int k0) {
+      const size_t rb = (size_t)r0 * n, kb = INV ? h + k0 : n - KS - k0;
 #pragma unroll
       for (int p = 0; p < XP; ++p) {
-        const size_t ro = (size_t)(r0 + xr + (256 / TPR) * p) * n;
-        const int ka = k0 + xk, kb = INV ? h + k0 + xk : n - VPT - k0 - xk;
         if (IN16) {
-          ha[p] = *reinterpret_cast<const u16x8*>(X16 + ro + ka);
-          hb[p] = *reinterpret_cast<const u16x8*>(X16 + ro + kb);
+          v.ha[p] = *reinterpret_cast<const u16x8*>(X16 + rb + 16 * (size_t)k0 + xa[p]);
+          v.hb[p] = *reinterpret_cast<const u16x8*>(X16 + rb + 16 * kb + xb[p]);
         } else {
-          sa[p] = *reinterpret_cast<const float4*>(X + ro + ka);
-          sb[p] = *reinterpret_cast<const float4*>(X + ro + kb);
+          v.sa[p] = *reinterpret_cast<const float4*>(X + rb + k0 + xa[p]);
+          v.sb[p] = *reinterpret_cast<const float4*>(X + rb + kb + xb[p]);
         }
       }
 #pragma unroll
       for (int p = 0; p < TP; ++p) {
-        const int s = p * SEGS + bseg;                // segment: ((half * NP) + plane) * kBW + row
-        const int half = s / (kBW * NP), plane = (s / kBW) % NP;
-        // a wide tile without its partner stages its own rows twice (the
-        // extra outputs are computed but never stored)
-        const int row = full ? s % kBW : s % 64;
-        const uint16_t* T = plane ? T1 : T0;
-        const uint16_t* src = INV ? T + (size_t)(c0 + row) * n + (half ? h : 0) + k0 + 8 * bq
-                                  : T + (size_t)((half ? h : 0) + c0 + row) * h + k0 + 8 * bq;
-        sT[p] = *as_global(reinterpret_cast<const u16x8*>(src));
+        // segment ((half * NP) + plane) * kBW + row: half and plane by the pass
+        const int half = p * SEGS / (kBW * NP), plane = (p * SEGS / kBW) % NP;
+        const uint16_t* T = (plane ? T1 : T0) + 16 * (size_t)k0 +
+                            (INV ? (size_t)c0 * n + (half ? 16 * (size_t)h : 0)
+                                 : (size_t)((half ? h : 0) + c0) * h);
+        v.sT[p] = *as_global(reinterpret_cast<const u16x8*>(T + to[p]));
       }
     };
-    auto stash = [&]() {
+    auto stash = [&](const Held& v, uint16_t* As) {  // As: [plane][half][TR x KS], then the table's
+      uint16_t* Bs = As + NP * 2 * kA;               // [plane][half][kBW x KS]
       if constexpr (IN16) {
         // fp16 input already carries the stage's scale: the inverse copies
         // it, the forward folds x_a +- x_b in FP32 and rounds once more
 #pragma unroll
         for (int p = 0; p < XP; ++p) {
           const int r = xr + (256 / TPR) * p;
-          u16x8 v0 = ha[p], v1 = hb[p];
+          u16x8 v0 = v.ha[p], v1 = v.hb[p];
           if (!INV) {
             // whole-vector form: x_b reversed (it holds x[n-1-k] from the top),
             // sum and difference in FP32, one rounding back to fp16
-            const f16x8 fa = __builtin_bit_cast(f16x8, ha[p]);
-            const f16x8 fbr = __builtin_bit_cast(f16x8, hb[p]);
+            const f16x8 fa = __builtin_bit_cast(f16x8, v.ha[p]);
+            const f16x8 fbr = __builtin_bit_cast(f16x8, v.hb[p]);
             const f16x8 fb = __builtin_shufflevector(fbr, fbr, 7, 6, 5, 4, 3, 2, 1, 0);
             const f32x8 a32 = __builtin_convertvector(fa, f32x8);
             const f32x8 b32 = __builtin_convertvector(fb, f32x8);
@@ -242,57 +286,97 @@ __global__ void __launch_bounds__(256, 2) k_e_dct_eo(DArgs a) {
         }
       } else {
 #pragma unroll
-      for (int p = 0; p < XP; ++p) {
-        const int r = xr + (256 / TPR) * p;
-        const float av[4] = {sa[p].x, sa[p].y, sa[p].z, sa[p].w};
-        // forward: the b part is x mirrored, x[n-1-k] for k = k0 + xk .. +3
-        const float bv[4] = {INV ? sb[p].x : sb[p].w, INV ? sb[p].y : sb[p].z,
-                             INV ? sb[p].z : sb[p].y, INV ? sb[p].w : sb[p].x};
-        u16x4 hv[2], lv[2];
+        for (int p = 0; p < XP; ++p) {
+          const int r = xr + (256 / TPR) * p;
+          const float av[4] = {v.sa[p].x, v.sa[p].y, v.sa[p].z, v.sa[p].w};
+          // forward: the b part is x mirrored, x[n-1-k] for k = k0 + xk .. +3
+          const float bv[4] = {INV ? v.sb[p].x : v.sb[p].w, INV ? v.sb[p].y : v.sb[p].z,
+                               INV ? v.sb[p].z : v.sb[p].y, INV ? v.sb[p].w : v.sb[p].x};
+          u16x4 hv[2], lv[2];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float v0 = INV ? av[e] : av[e] + bv[e];
-          const float v1 = INV ? bv[e] : av[e] - bv[e];
-          if (SPLIT) {
-            const __bf16 h0 = (__bf16)v0, h1 = (__bf16)v1;
-            hv[0][e] = __builtin_bit_cast(uint16_t, h0);
-            hv[1][e] = __builtin_bit_cast(uint16_t, h1);
-            lv[0][e] = __builtin_bit_cast(uint16_t, (__bf16)(v0 - (float)h0));
-            lv[1][e] = __builtin_bit_cast(uint16_t, (__bf16)(v1 - (float)h1));
-          } else {
-            hv[0][e] = __builtin_bit_cast(uint16_t, (_Float16)(v0 * xs));
-            hv[1][e] = __builtin_bit_cast(uint16_t, (_Float16)(v1 * xs));
+          for (int e = 0; e < 4; ++e) {
+            const float v0 = INV ? av[e] : av[e] + bv[e];
+            const float v1 = INV ? bv[e] : av[e] - bv[e];
+            if (SPLIT) {
+              const __bf16 h0 = (__bf16)v0, h1 = (__bf16)v1;
+              hv[0][e] = __builtin_bit_cast(uint16_t, h0);
+              hv[1][e] = __builtin_bit_cast(uint16_t, h1);
+              lv[0][e] = __builtin_bit_cast(uint16_t, (__bf16)(v0 - (float)h0));
+              lv[1][e] = __builtin_bit_cast(uint16_t, (__bf16)(v1 - (float)h1));
+            } else {
+              hv[0][e] = __builtin_bit_cast(uint16_t, (_Float16)(v0 * xs));
+              hv[1][e] = __builtin_bit_cast(uint16_t, (_Float16)(v1 * xs));
+            }
+          }
+          const int o = lds_at<NC>(r, xk >> 3) + (xk & 4);
+#pragma unroll
+          for (int half = 0; half < 2; ++half) {
+            *reinterpret_cast<u16x4*>(As + (0 * 2 + half) * kA + o) = hv[half];
+            if (SPLIT) *reinterpret_cast<u16x4*>(As + (1 * 2 + half) * kA + o) = lv[half];
           }
         }
-        const int o = lds_at<NC>(r, xk >> 3) + (xk & 4);
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          *reinterpret_cast<u16x4*>(As + (0 * 2 + half) * kA + o) = hv[half];
-          if (SPLIT) *reinterpret_cast<u16x4*>(As + (1 * 2 + half) * kA + o) = lv[half];
-        }
-      }
       }
 #pragma unroll
       for (int p = 0; p < TP; ++p) {
-        const int s = p * SEGS + bseg;
-        const int half = s / (kBW * NP), plane = (s / kBW) % NP, row = s % kBW;
-        *reinterpret_cast<u16x8*>(Bs + (plane * 2 + half) * kB + lds_at<NC>(row, bq)) = sT[p];
+        const int half = p * SEGS / (kBW * NP), plane = (p * SEGS / kBW) % NP;
+        const int row = (p * SEGS + bseg) % kBW;
+        *reinterpret_cast<u16x8*>(Bs + (plane * 2 + half) * kB + lds_at<NC>(row, bq)) = v.sT[p];
       }
     };
-    f32x4 acc[4][NW];
+    f32x4 acc[NI][NJ];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int j = 0; j < NW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < NJ; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto product = [&](const uint16_t* As) {
+      const uint16_t* Bs = As + NP * 2 * kA;
+      const uint16_t* Ah = As + (0 * 2 + hf) * kA;
+      const uint16_t* Al = As + (1 * 2 + hf) * kA;
+      const uint16_t* Bh = Bs + (0 * 2 + hf) * kB;
+      const uint16_t* Bl = Bs + (1 * 2 + hf) * kB;
+#pragma unroll
+      for (int ks = 0; ks < KS / 32; ++ks) {
+        const int q = 4 * ks + kq;
+        // the smaller operand's fragments are held, the other's come one by one
+        u16x8 ah[NI], al[NI];
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+          ah[i] = *reinterpret_cast<const u16x8*>(Ah + lds_at<NC>(wr + 16 * i + lr, q));
+          if (SPLIT) al[i] = *reinterpret_cast<const u16x8*>(Al + lds_at<NC>(wr + 16 * i + lr, q));
+        }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const u16x8 bh = *reinterpret_cast<const u16x8*>(Bh + lds_at<NC>(16 * j + lr, q));
+          u16x8 bl;
+          if (SPLIT) bl = *reinterpret_cast<const u16x8*>(Bl + lds_at<NC>(16 * j + lr, q));
+#pragma unroll
+          for (int i = 0; i < NI; ++i) {
+            if (SPLIT) {
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf16x8, ah[i]), __builtin_bit_cast(bf16x8, bh), acc[i][j], 0, 0, 0);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf16x8, ah[i]), __builtin_bit_cast(bf16x8, bl), acc[i][j], 0, 0, 0);
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  __builtin_bit_cast(bf16x8, al[i]), __builtin_bit_cast(bf16x8, bh), acc[i][j], 0, 0, 0);
+            } else {
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                  __builtin_bit_cast(f16x8, ah[i]), __builtin_bit_cast(f16x8, bh), acc[i][j], 0, 0, 0);
+            }
+          }
+        }
+      }
+    };
     const int nsteps = h / KS;
-    // the map's state and the first step's operands are requested together;
+    // the map's state and the first steps' operands are requested together;
     // the compiler barriers keep that order (it would otherwise sink the
     // operand loads behind the state test's branch)
     const int m_state = a.ms[tm].state;
     const double m_rr = a.ms[tm].rr;
     const int t_iso = a.desc[tm].use_iso;
     __asm__ volatile("" ::: "memory");
-    fetch(0);
+    Held va, vb;
+    fetch(va, 0);
+    if (DEPTH > 1) fetch(vb, min(1, nsteps - 1) * KS);
     __asm__ volatile("" ::: "memory");
     if (m_state != a.expect) continue;  // uniform over the block
     const auto* lamMs = as_global(t_lam_m);
@@ -303,26 +387,12 @@ __global__ void __launch_bounds__(256, 2) k_e_dct_eo(DArgs a) {
       return INV ? (hf ? n - 1 - c : c) : (hf ? h : 0) + c;
     };
     auto out_rb = [&](int i) { return r0 + wr + 16 * i + 4 * kq; };
-    // Everything the epilogue reads is loaded before its first store: loads
-    // and stores share one counter, so a load issued after a store would wait
-    // for that store too, one memory round trip per output tile.  The
-    // eigenvalues are requested here, ahead of the K loop; r and the
-    // isolated-pixel flags (stage 3) one column group ahead in the epilogue.
     // Which stages an instance can run: the forward instances with fp16 input
     // (or the split's, which serve both forward stages) run stage 1, the
     // inverse instances with an FP32 output run stage 3.
     constexpr bool kS1 = !INV && (SPLIT || IN16);
     constexpr bool kS3 = INV && !OUT16;
     const bool st1 = kS1 && a.stage == 1, st3 = kS3 && a.stage == 3;
-    float lam_c[NW], lam_r[4][4];  // stage 1: eigenvalues along M and N (FP32)
-    if (st1) {
-#pragma unroll
-      for (int j = 0; j < NW; ++j) lam_c[j] = (j < 4 || full) ? (float)lamMs[out_c(j)] : 0.0f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) lam_r[i][e] = (float)lamNs[out_rb(i) + e];
-    }
     if (!SPLIT) {
       // Scaled fp16: power-of-two scales from bounds that hold before any
       // value exists.  The transforms are orthonormal, so every stage output
@@ -335,64 +405,89 @@ __global__ void __launch_bounds__(256, 2) k_e_dct_eo(DArgs a) {
       inv_xs = 1.0f / xs;
       os = fp16_scale(a.stage == 0 ? b01 : b23);
     }
-    for (int s = 0; s < nsteps; ++s) {
-      __syncthreads();  // readers of the previous step (or tile) are done
-      stash();
+    uint16_t* cur = reinterpret_cast<uint16_t*>(smem);
+    uint16_t* nxt = cur + (NBUF - 1) * kBuf;
+    // Past the last step the last one is fetched again: with as many loads in
+    // flight on every path, the wait for one step's leaves the later ones' alone.
+    auto at = [&](int s) { return min(s, nsteps - 1) * KS; };
+    if constexpr (NBUF == 2) {
+      stash(va, cur);
+      fetch(va, at(DEPTH));
       __syncthreads();
-      if (s + 1 < nsteps) fetch((s + 1) * KS);
-      const uint16_t* Ah = As + (0 * 2 + hf) * kA;
-      const uint16_t* Al = As + (1 * 2 + hf) * kA;
-      const uint16_t* Bh = Bs + (0 * 2 + hf) * kB;
-      const uint16_t* Bl = Bs + (1 * 2 + hf) * kB;
-#pragma unroll
-      for (int ks = 0; ks < KS / 32; ++ks) {
-      const int q = 4 * ks + kq;
-      u16x8 bh[NW], bl[NW];
-#pragma unroll
-      for (int j = 0; j < NW; ++j) {
-        bh[j] = *reinterpret_cast<const u16x8*>(Bh + lds_at<NC>(16 * j + lr, q));
-        if (SPLIT) bl[j] = *reinterpret_cast<const u16x8*>(Bl + lds_at<NC>(16 * j + lr, q));
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const u16x8 ah = *reinterpret_cast<const u16x8*>(Ah + lds_at<NC>(wr + 16 * i + lr, q));
-        u16x8 al;
-        if (SPLIT) al = *reinterpret_cast<const u16x8*>(Al + lds_at<NC>(wr + 16 * i + lr, q));
-#pragma unroll
-        for (int j = 0; j < NW; ++j) {
-          if (SPLIT) {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, ah), __builtin_bit_cast(bf16x8, bh[j]), acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, ah), __builtin_bit_cast(bf16x8, bl[j]), acc[i][j], 0, 0, 0);
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                __builtin_bit_cast(bf16x8, al), __builtin_bit_cast(bf16x8, bh[j]), acc[i][j], 0, 0, 0);
-          } else {
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                __builtin_bit_cast(f16x8, ah), __builtin_bit_cast(f16x8, bh[j]), acc[i][j], 0, 0, 0);
-          }
+      // v: step s + 1's operands, replaced by those of step s + 1 + DEPTH
+      auto step = [&](int s, Held& v) {
+        stash(v, nxt);
+        fetch(v, at(s + 1 + DEPTH));
+        product(cur);
+        __syncthreads();
+        uint16_t* const c = cur;
+        cur = nxt;
+        nxt = c;
+      };
+      int s = 0;
+      if constexpr (DEPTH > 1) {
+        for (; s + 2 < nsteps; s += 2) {
+          step(s, vb);
+          step(s + 1, va);
         }
+        if (s + 1 < nsteps) step(s, vb);
+      } else {
+        for (; s + 1 < nsteps; ++s) step(s, va);
       }
-      }  // ks
+      product(cur);
+    } else {
+      auto step = [&](int s, Held& v) {
+        stash(v, cur);
+        __syncthreads();
+        fetch(v, at(s + DEPTH));
+        product(cur);
+        __syncthreads();
+      };
+      int s = 0;
+      if constexpr (DEPTH > 1) {
+        for (; s + 1 < nsteps; s += 2) {
+          step(s, va);
+          step(s + 1, vb);
+        }
+        if (s < nsteps) step(s, va);
+      } else {
+        for (; s < nsteps; ++s) step(s, va);
+      }
     }
     // epilogue: lane holds D[row 4*(lane/16) + e][col lane mod 16] of each 16x16 tile,
-    // i.e. outputs (c, rb .. rb+3) with rb a multiple of 4
+    // i.e. outputs (c, rb .. rb+3) with rb a multiple of 4.  Everything it
+    // reads is loaded before its first store: loads and stores share one
+    // counter, so a load issued after a store would wait for that store too,
+    // one memory round trip per output tile (r and the isolated-pixel flags of
+    // stage 3: one column group ahead).
+    float lam_c[NJ], lam_r[NI][4];  // stage 1: eigenvalues along M and N (FP32)
+    if (st1) {
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) lam_c[j] = (j < 4 || full) ? (float)lamMs[out_c(j)] : 0.0f;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) lam_r[i][e] = (float)lamNs[out_rb(i) + e];
+    }
     const float* rv = reinterpret_cast<const float*>(a.rvec) + toff;
     const unsigned char* iso = (a.iso && t_iso) ? a.iso + toff : nullptr;
-    // stage 3: r and the isolated-pixel flags at the outputs of one column
-    // group, loaded one group ahead of the group being stored
-    f32x4 r_cur[4], r_nxt[4];
-    unsigned int z_cur[4], z_nxt[4];
-    auto load_rz = [&](int j, f32x4 (&rr)[4], unsigned int (&zz)[4]) {
+    f32x4 r_cur[NI], r_nxt[NI];
+    unsigned int z_cur[NI], z_nxt[NI];
+    auto load_rz = [&](int j, f32x4 (&rr)[NI], unsigned int (&zz)[NI]) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
+      for (int i = 0; i < NI; ++i) {
         const size_t o = (size_t)out_c(j) * R + out_rb(i);
         rr[i] = *as_global(reinterpret_cast<const f32x4*>(rv + o));
         zz[i] = iso ? *as_global(reinterpret_cast<const unsigned int*>(iso + o)) : 0u;
       }
     };
     if (st3) load_rz(0, r_cur, z_cur);
-    double part = 0.0;
+    // stage 3: this wave's sums of r^T s over 32 rows by 32 output pairs each
+    double part[NI / 2][NJ / 2];
+#pragma unroll
+    for (int i = 0; i < NI / 2; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ / 2; ++j) part[i][j] = 0.0;
     auto emit = [&](int i, int j, const float (&y)[4]) {
       const int c = out_c(j), rb = out_rb(i);
       float v[4] = {y[0], y[1], y[2], y[3]};
@@ -411,24 +506,24 @@ __global__ void __launch_bounds__(256, 2) k_e_dct_eo(DArgs a) {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           if ((z >> (8 * e)) & 0xffu) v[e] = 0.0f;
-          part += (double)r_cur[i][e] * (double)v[e];
+          part[i / 2][j / 2] = fma((double)r_cur[i][e], (double)v[e], part[i / 2][j / 2]);
         }
       }
       if (OUT16) {
         u16x4 hv;
 #pragma unroll
         for (int e = 0; e < 4; ++e) hv[e] = __builtin_bit_cast(uint16_t, (_Float16)(v[e] * os));
-        *reinterpret_cast<u16x4*>(Out16 + (size_t)c * R + rb) = hv;
+        *reinterpret_cast<u16x4*>(Out16 + eo_at<size_t>(c, rb, R)) = hv;
       } else {
         *reinterpret_cast<float4*>(Out + (size_t)c * R + rb) = make_float4(v[0], v[1], v[2], v[3]);
       }
     };
     if (!INV) {
 #pragma unroll
-      for (int j = 0; j < NW; ++j) {
+      for (int j = 0; j < NJ; ++j) {
         if (j >= 4 && !full) continue;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
+        for (int i = 0; i < NI; ++i) {
           const float y[4] = {acc[i][j][0] * inv_xs, acc[i][j][1] * inv_xs, acc[i][j][2] * inv_xs,
                               acc[i][j][3] * inv_xs};
           emit(i, j, y);
@@ -438,51 +533,74 @@ __global__ void __launch_bounds__(256, 2) k_e_dct_eo(DArgs a) {
       // u (half 0) and v (half 1) of the same rows meet through LDS: the
       // waves of half 0 write u + v to output c, those of half 1 write
       // u - v to output n-1-c
-      f32x4* xg = reinterpret_cast<f32x4*>(smem);  // [half][row group][16 tiles][64 lanes]
+      f32x4* xg = reinterpret_cast<f32x4*>(smem);  // [half][row group][NI JR tiles][64 lanes]
       const int oh = hf ^ 1;
       // one round per four column groups (wide tiles: two rounds, the
       // second only when the partner exists; uniform over the block)
 #pragma unroll
-      for (int jr = 0; jr < NW / 4; ++jr) {
+      for (int jr = 0; jr < NJ / JR; ++jr) {
         if (jr > 0 && !full) break;
         __syncthreads();  // every wave is done reading the staged operands (or the last round)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < NI; ++i)
 #pragma unroll
-          for (int jj = 0; jj < 4; ++jj)
-            xg[((hf * 2 + (w & 1)) * 16 + i * 4 + jj) * 64 + lane] = acc[i][4 * jr + jj];
+          for (int jj = 0; jj < JR; ++jj)
+            xg[((hf * 2 + (w & 1)) * NI * JR + i * JR + jj) * 64 + lane] = acc[i][JR * jr + jj];
         __syncthreads();
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          const int j = 4 * jr + jj;
-          if (st3 && j < 3) load_rz(j + 1, r_nxt, z_nxt);
+        for (int jj = 0; jj < JR; ++jj) {
+          const int j = JR * jr + jj;
+          if (st3 && j < NJ - 1) load_rz(j + 1, r_nxt, z_nxt);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const f32x4 o = xg[((oh * 2 + (w & 1)) * 16 + i * 4 + jj) * 64 + lane];  // the other half
+          for (int i = 0; i < NI; ++i) {
+            const f32x4 o = xg[((oh * 2 + (w & 1)) * NI * JR + i * JR + jj) * 64 + lane];  // the other half
             const float y[4] = {(hf ? o[0] - acc[i][j][0] : acc[i][j][0] + o[0]) * inv_xs,
                                 (hf ? o[1] - acc[i][j][1] : acc[i][j][1] + o[1]) * inv_xs,
                                 (hf ? o[2] - acc[i][j][2] : acc[i][j][2] + o[2]) * inv_xs,
                                 (hf ? o[3] - acc[i][j][3] : acc[i][j][3] + o[3]) * inv_xs};
             emit(i, j, y);
           }
-          if (st3 && j < 3) {
+          if (st3 && j < NJ - 1) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) r_cur[i] = r_nxt[i], z_cur[i] = z_nxt[i];
+            for (int i = 0; i < NI; ++i) r_cur[i] = r_nxt[i], z_cur[i] = z_nxt[i];
           }
         }
       }
     }
     if (st3) {
-      double vv[1] = {part};
-      block_sum<1>(vv, red);
-      if (tid == 0) store_partial(a.P + 1 * a.pstride + g, vv[0]);
+      // one partial per quarter of the 128-row tile: its four sums (two row
+      // groups of two halves) in order
+      if constexpr (FINE) {
+        double vv[1] = {part[0][0]};
+        block_sum<1>(vv, red);
+        if (tid == 0) store_partial(a.P + 1 * a.pstride + kEoParts * g + quarter, vv[0]);
+      } else {
+#pragma unroll
+        for (int i = 0; i < NI / 2; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ / 2; ++j) {
+            const double v = tree64(part[i][j]);
+            if (lane == 0) red[(2 * j + (w & 1)) * 4 + 2 * hf + i] = v;  // [quarter][half, row group]
+          }
+        __syncthreads();
+        if (tid < (full ? NJ : 4)) {  // a wide tile's right half: the partner's quarters
+          double v = 0.0;
+#pragma unroll
+          for (int k = 0; k < 4; ++k) v += red[4 * tid + k];
+          store_partial(a.P + 1 * a.pstride + kEoParts * (g + (tid < 4 ? 0 : R / 128)) + (tid & 3), v);
+        }
+      }
       if (a.fin_mode) {
         const int sl[1] = {1};
-        fused_finish<kFinTail, 1>(Arrival{a.fcnt, a.gcnt, a.gsum, a.gstride, a.P, a.pstride}, sl,
-                                  g - t_local, t_local, t_ndt, t_gbd, a.desc, a.ms, tm,
-                                  a.fin_mode, 0, &fflag, fred);
+        for (int k = 0; k < (NJ == 8 && full ? 2 : 1); ++k)
+          fused_finish<kFinTail, 1>(Arrival{a.fcnt, a.gcnt, a.gsum, a.gstride, a.P, a.pstride}, sl,
+                                    kEoParts * (g - t_local),
+                                    kEoParts * (t_local + k * (R / 128)) + quarter,
+                                    kEoParts * t_ndt, t_gbd, a.desc, a.ms, tm, a.fin_mode, 0, &fflag,
+                                    fred, FINE ? 1 : kEoParts);
       }
     }
+    __syncthreads();  // the next tile's first step may overwrite what slower waves still read
   }
 }
 
@@ -1259,21 +1377,35 @@ int dct_grid_for(const Engine& e, int ndtiles) {
   return std::min(g, cap);
 }
 
-// Launches over at least kWideMin list positions of narrow tiles run the
-// first three stages of the scaled-fp16 even/odd path on wide tiles (on
-// fewer tiles, half as many wide ones leave CUs idle).  The choice changes no
-// output: the last stage, whose per-tile partial sums fix the association of
-// r^T s, always runs on narrow tiles.  It is part of the captured graphs' key.
-constexpr int kWideMin = 1024;
+// Tile shape of the even/odd stages (k_e_dct_eo): 0 fine, 1 narrow, 2 wide in
+// the first three stages, 3 wide in all; elsewhere 1 if the instances that take
+// tiles of 64 x 64 run, else 0.  It changes no result and is part of the
+// captured graphs' key.
+//
+// Four stages, us, of fine / narrow / wide tiles, scaled fp16 (narrow list
+// positions): 512^2 (16) 39 / 67 / 60, 1024^2 (64) 36 / 55 / 88, 1536^2 (144)
+// 81 / 74 / 118, 2048^2 (256) 128 / 96 / 148, 2560^2 (400) 275 / 167 / 189,
+// 3072^2 (576) 366 / 282 / 277, 4096^2 (1024) 832 / 507 / 386; bf16 split: 64 /
+// 116, 169 / 171, 265 / 228 at 1024^2 to 2048^2.  The last stage, with its FP32
+// output and reads of r, gains from wide tiles later: 70 / 82 us at 576
+// positions, 122 / 109 at 1024.
+constexpr int kFineMax = 128;
+constexpr int kWideMin = 576;
+constexpr int kWideLastMin = 1024;
 
-bool dct_wide_for(const Engine& e, int ndtiles, int kind) {
-  return kind == 5 && e.dct_trows == 128 && ndtiles >= kWideMin;
+int dct_shape_for(const Engine& e, int ndtiles, int kind) {
+  if (kind < 4) return e.dct_tile64 ? 1 : 0;
+  if (ndtiles < kFineMax) return 0;
+  if (kind != 5 || ndtiles < kWideMin) return 1;
+  return ndtiles < kWideLastMin ? 2 : 3;
 }
 
 void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int expect, int kind,
                  const void* X, void* Out, const void* rvec, int fin_mode) {
-  const int grid = dct_grid_for(e, ndtiles);
-  const bool wide = stage < 3 && dct_wide_for(e, ndtiles, kind);
+  const int shape = dct_shape_for(e, ndtiles, kind);
+  const bool fine = kind >= 4 && shape == 0;
+  const bool wide = kind >= 4 && (shape == 3 || (shape == 2 && stage < 3));
+  const int grid = dct_grid_for(e, fine ? 4 * ndtiles : ndtiles);
   DArgs a;
   a.fcnt = e.fcnt;
   a.gcnt = e.gcnt;
@@ -1316,15 +1448,29 @@ void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int ex
   else if (kind == 3) hipLaunchKernelGGL((k_e_dct_dense<0, 32>), dim3(grid), dim3(256), 0, st, a);
   // scaled fp16 even/odd: intermediates between the stages are stored as
   // scaled fp16 (first stage reads FP32 r, last stage writes FP32 s)
-  else if (kind == 4 && stage < 2) hipLaunchKernelGGL((k_e_dct_eo<1, 0, 0, 0, 4>), dim3(grid), dim3(256), 0, st, a);
-  else if (kind == 4) hipLaunchKernelGGL((k_e_dct_eo<1, 1, 0, 0, 4>), dim3(grid), dim3(256), 0, st, a);
-  else if (stage == 0 && wide) hipLaunchKernelGGL((k_e_dct_eo<0, 0, 0, 1, 8>), dim3(grid), dim3(256), 0, st, a);
-  else if (stage == 0) hipLaunchKernelGGL((k_e_dct_eo<0, 0, 0, 1, 4>), dim3(grid), dim3(256), 0, st, a);
-  else if (stage == 1 && wide) hipLaunchKernelGGL((k_e_dct_eo<0, 0, 1, 1, 8>), dim3(grid), dim3(256), 0, st, a);
-  else if (stage == 1) hipLaunchKernelGGL((k_e_dct_eo<0, 0, 1, 1, 4>), dim3(grid), dim3(256), 0, st, a);
-  else if (stage == 2 && wide) hipLaunchKernelGGL((k_e_dct_eo<0, 1, 1, 1, 8>), dim3(grid), dim3(256), 0, st, a);
-  else if (stage == 2) hipLaunchKernelGGL((k_e_dct_eo<0, 1, 1, 1, 4>), dim3(grid), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((k_e_dct_eo<0, 1, 1, 0, 4>), dim3(grid), dim3(256), 0, st, a);
+  else if (kind == 4 && stage < 2) {
+    if (fine) hipLaunchKernelGGL((k_e_dct_eo<1, 0, 0, 0, 2, 2>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_e_dct_eo<1, 0, 0, 0, 4, 4>), dim3(grid), dim3(256), 0, st, a);
+  } else if (kind == 4) {
+    if (fine) hipLaunchKernelGGL((k_e_dct_eo<1, 1, 0, 0, 2, 2>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_e_dct_eo<1, 1, 0, 0, 4, 4>), dim3(grid), dim3(256), 0, st, a);
+  } else if (stage == 0) {
+    if (fine) hipLaunchKernelGGL((k_e_dct_eo<0, 0, 0, 1, 2, 2>), dim3(grid), dim3(256), 0, st, a);
+    else if (wide) hipLaunchKernelGGL((k_e_dct_eo<0, 0, 0, 1, 4, 8>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_e_dct_eo<0, 0, 0, 1, 4, 4>), dim3(grid), dim3(256), 0, st, a);
+  } else if (stage == 1) {
+    if (fine) hipLaunchKernelGGL((k_e_dct_eo<0, 0, 1, 1, 2, 2>), dim3(grid), dim3(256), 0, st, a);
+    else if (wide) hipLaunchKernelGGL((k_e_dct_eo<0, 0, 1, 1, 4, 8>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_e_dct_eo<0, 0, 1, 1, 4, 4>), dim3(grid), dim3(256), 0, st, a);
+  } else if (stage == 2) {
+    if (fine) hipLaunchKernelGGL((k_e_dct_eo<0, 1, 1, 1, 2, 2>), dim3(grid), dim3(256), 0, st, a);
+    else if (wide) hipLaunchKernelGGL((k_e_dct_eo<0, 1, 1, 1, 4, 8>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_e_dct_eo<0, 1, 1, 1, 4, 4>), dim3(grid), dim3(256), 0, st, a);
+  } else {
+    if (fine) hipLaunchKernelGGL((k_e_dct_eo<0, 1, 1, 0, 2, 2>), dim3(grid), dim3(256), 0, st, a);
+    else if (wide) hipLaunchKernelGGL((k_e_dct_eo<0, 1, 1, 0, 4, 8>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_e_dct_eo<0, 1, 1, 0, 4, 4>), dim3(grid), dim3(256), 0, st, a);
+  }
 }
 
 }  // namespace lpu

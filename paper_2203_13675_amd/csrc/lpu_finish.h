@@ -221,7 +221,7 @@ __device__ inline void finish_map(const MapDesc* __restrict__ desc, MapState* ms
   } else if (op == kFinTail) {
     const int sl[1] = {1};
     double w[1];
-    fin_sums<GROUPS, 1>(src, d.dtile0, d.ndt, d.gbd, sl, w, smem);
+    fin_sums<GROUPS, 1>(src, d.dtile0 * d.dparts, d.ndt * d.dparts, d.gbd, sl, w, smem);
     v[0] = w[0];
   } else if (op == kFinTailW) {
     const int sl[1] = {1};
@@ -343,10 +343,11 @@ enum ArrivalKind : int {
   kArrGroups = 2    // the map's last block: sums of the published group sums
 };
 
-// flag is shared memory; nt: the threads that form flat sums.
+// flag is shared memory; nt: the threads that form flat sums; n: the block's
+// partials, tiles local .. local + n - 1 of one group (n divides the group).
 template <int NS>
 __device__ inline int last_arrival(const Arrival& a, const int (&slots)[NS], int first, int m,
-                                   int local, int total, int gbase, int nt, int* flag) {
+                                   int local, int total, int gbase, int nt, int* flag, int n) {
   static_assert(NS <= 2, "one slot per half-wave");
   const int grp = local / kArriveGroup;
   const int ngrp = (total + kArriveGroup - 1) / kArriveGroup;
@@ -356,7 +357,7 @@ __device__ inline int last_arrival(const Arrival& a, const int (&slots)[NS], int
     const int in_grp = min(kArriveGroup, total - grp * kArriveGroup);
     int kind = kArrNotLast;
     int* gc = a.gcnt + kArriveStride * (gbase + grp);
-    if (__hip_atomic_fetch_add(gc, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == in_grp - 1) {
+    if (__hip_atomic_fetch_add(gc, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == in_grp - n) {
       __hip_atomic_store(gc, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       kind = kArrGroups;  // this block completed the group
       if (!publish)       // a map of one group is complete with it
@@ -399,10 +400,10 @@ __device__ inline int last_arrival(const Arrival& a, const int (&slots)[NS], int
 template <int OP, int NS, int NT = 0>
 __device__ inline void fused_finish(const Arrival& a, const int (&slots)[NS], int first, int local,
                                     int total, int gbase, const MapDesc* desc, MapState* ms, int m,
-                                    int mode, int pointwise, int* flag, double* smem) {
+                                    int mode, int pointwise, int* flag, double* smem, int n = 1) {
   static_assert(OP != kFinInit, "group sums hold two slots; the set-up sums are not fused");
   const int nt = NT ? NT : (int)blockDim.x;
-  const int kind = last_arrival<NS>(a, slots, first, m, local, total, gbase, nt, flag);
+  const int kind = last_arrival<NS>(a, slots, first, m, local, total, gbase, nt, flag, n);
   if (kind == kArrNotLast) return;
   const FinSrc src{a.P, a.pstride, a.gsum, a.gstride, nt};
   if (kind == kArrFlat) finish_map<false>(desc, ms, src, m, OP, mode, pointwise, smem);

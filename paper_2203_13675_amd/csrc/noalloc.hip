@@ -110,6 +110,7 @@ __global__ void k_na_layout(MapDesc* desc, MapState* ms, int* counts, int* fcnt,
     d.tile0 = 0;
     d.ndt = ((M + 63) / 64) * ((N + 63) / 64);  // slots of the strips' partials
     d.dtile0 = 0;
+    d.dparts = 1;
     d.dtr = 64;
     d.gb = 0;
     d.gbd = ngroups;
