@@ -100,18 +100,18 @@ __device__ __forceinline__ TilePos tile_pos(const MapDesc* __restrict__ desc,
   return t;
 }
 
-// left/right neighbours of a row pair (lane shuffles + halo values)
+// left/right neighbours of a row pair: lane shuffles, and the halo values
+// h0 (column j0 - 1) and h1 (column j0 + 128)
 template <typename T>
-__device__ __forceinline__ void neighbours(const R2<T>& v, T halo, R2<T>& w, R2<T>& e) {
+__device__ __forceinline__ void neighbours(const R2<T>& v, T h0, T h1, R2<T>& w, R2<T>& e) {
   const int l = lane_id();
   const T up_a = shup(v.a), up_b = shup(v.b);
   const T dn_a = shdn(v.a), dn_b = shdn(v.b);
   const T a63 = shfrom(v.a, 63), b0 = shfrom(v.b, 0);
-  const T h0 = shfrom(halo, 0), h63 = shfrom(halo, 63);
-  w.a = l > 0 ? up_a : h0;     // column j0 - 1 for lane 0
-  w.b = l > 0 ? up_b : a63;    // column j0 + 63 for lane 0
-  e.a = l < 63 ? dn_a : b0;    // column j0 + 64 for lane 63
-  e.b = l < 63 ? dn_b : h63;   // column j0 + 128 for lane 63
+  w.a = l > 0 ? up_a : h0;   // column j0 - 1 for lane 0
+  w.b = l > 0 ? up_b : a63;  // column j0 + 63 for lane 0
+  e.a = l < 63 ? dn_a : b0;  // column j0 + 64 for lane 63
+  e.b = l < 63 ? dn_b : h1;  // column j0 + 128 for lane 63
 }
 
 // a(i, j), or zero outside the grid; the load goes through a clamped index, so
@@ -122,15 +122,6 @@ __device__ __forceinline__ T ldz(const T* __restrict__ a, int i, int j, int M, i
   const int ic = min(max(i, 0), M - 1), jc = min(max(j, 0), N - 1);
   const T v = a[(size_t)ic * N + jc];
   return ok ? v : T(0);
-}
-
-// Halo column of this lane's halo load: lane 0 uses column j0 - 1, lane 63
-// column j0 + 128.  The other lanes' values are never used, but the load is
-// one instruction for the whole wave: they read the same two columns, so the
-// instruction touches only the two halo lines (a lane clamped to column 0
-// would fetch one more line of every row).
-__device__ __forceinline__ int halo_col(int j0) {
-  return lane_id() < 32 ? j0 - 1 : j0 + kTW;
 }
 
 template <typename T>
@@ -250,11 +241,15 @@ __device__ __forceinline__ void stencil_tile(const TilePos& tp, TileSum<T, NS, O
                                              const T* __restrict__ U, const T* __restrict__ V,
                                              Ld load, Mk make, Ow own, E epi) {
   const int M = tp.M, N = tp.N, j0 = tp.j0, l = lane_id();
-  const int hj = halo_col(j0);
   const int ca = j0 + l, cb = j0 + 64 + l;
-  const bool oka = ca < N, okb = cb < N, okh = (unsigned)hj < (unsigned)N;
-  const unsigned ja = min(ca, N - 1), jb = min(cb, N - 1), jh = min(max(hj, 0), N - 1);
-  const unsigned ju = max(j0 - 1, 0);  // U's halo: column j0 - 1 (lane 0's), every lane
+  const bool oka = ca < N, okb = cb < N;
+  const unsigned ja = min(ca, N - 1), jb = min(cb, N - 1);
+  // The halo columns of the wave's rows come in one load: lane 2 c + side holds
+  // row c's column j0 - 1 (side 0) or j0 + 128 (side 1).
+  static_assert(kRW <= 32, "two lanes a row");
+  const int hj = (l & 1) ? j0 + kTW : j0 - 1;
+  const bool okh = (unsigned)hj < (unsigned)N;
+  const unsigned jh = min(max(hj, 0), N - 1);
   const int i_end = min(tp.i0 + tp.rows, M);
   using Raw = decltype(load(size_t(0), 0u));
   using Own = decltype(own(size_t(0), 0u));
@@ -263,10 +258,13 @@ __device__ __forceinline__ void stencil_tile(const TilePos& tp, TileSum<T, NS, O
   const int wrow = wave_id() * kRW, step = wave_count() * kRW, lead = OR ? wrow : 0;
   for (int i0 = tp.i0 + wrow; i0 - lead < i_end; i0 += step) {
     Terms<T, NS> ta[kRW] = {}, tb[kRW] = {};
-    Raw ra[kRW + 2], rb[kRW + 2], rh[kRW];  // operand rows i0 - 1 .. i0 + kRW
+    Raw ra[kRW + 2], rb[kRW + 2];  // operand rows i0 - 1 .. i0 + kRW
     Own oa[kRW], ob[kRW];
     R2<T> u[kRW], v[kRW + 1];  // V rows i0 - 1 .. i0 + kRW - 1
-    T uh[kRW];
+    const int ih = i0 + (l >> 1) % kRW;
+    const size_t hrow = (size_t)min(ih, M - 1) * N;
+    const Raw rh = load(hrow, jh);
+    const T uh = U[hrow + jh];
 #pragma unroll
     for (int c = 0; c < kRW + 2; ++c) {
       const size_t row = (size_t)min(max(i0 - 1 + c, 0), M - 1) * N;
@@ -277,10 +275,8 @@ __device__ __forceinline__ void stencil_tile(const TilePos& tp, TileSum<T, NS, O
         v[c].b = V[row + jb];
       }
       if (c > 0 && c <= kRW) {
-        rh[c - 1] = load(row, jh);
         u[c - 1].a = U[row + ja];
         u[c - 1].b = U[row + jb];
-        uh[c - 1] = U[row + ju];
         oa[c - 1] = own(row, ja);
         ob[c - 1] = own(row, jb);
       }
@@ -291,6 +287,8 @@ __device__ __forceinline__ void stencil_tile(const TilePos& tp, TileSum<T, NS, O
     };
     R2<T> xm{operand(ra[0], i0 - 1, ca, oka), operand(rb[0], i0 - 1, cb, okb)};
     R2<T> xc{operand(ra[1], i0, ca, oka), operand(rb[1], i0, cb, okb)};
+    const T xh = operand(rh, ih, hj, okh);
+    const T uw0 = j0 > 0 ? uh : T(0);  // the couplings to column j0 - 1
     if (i0 == 0) v[0].a = v[0].b = T(0);
 #pragma unroll
     for (int c = 0; c < kRW; ++c) {
@@ -298,8 +296,8 @@ __device__ __forceinline__ void stencil_tile(const TilePos& tp, TileSum<T, NS, O
       if (i >= i_end) break;  // uniform over the wave
       const R2<T> xp{operand(ra[c + 2], i + 1, ca, oka), operand(rb[c + 2], i + 1, cb, okb)};
       R2<T> xw, xe, uw, ue;
-      neighbours(xc, operand(rh[c], i, hj, okh), xw, xe);
-      neighbours(u[c], j0 > 0 ? uh[c] : T(0), uw, ue);
+      neighbours(xc, shfrom(xh, 2 * c), shfrom(xh, 2 * c + 1), xw, xe);
+      neighbours(u[c], shfrom(uw0, 2 * c), T(0), uw, ue);
       const T qa = stencil5<T>(uw.a, u[c].a, v[c].a, v[c + 1].a, xc.a, xw.a, xe.a, xm.a, xp.a);
       const T qb = stencil5<T>(uw.b, u[c].b, v[c].b, v[c + 1].b, xc.b, xw.b, xe.b, xm.b, xp.b);
       const size_t row = (size_t)i * N;
@@ -847,7 +845,7 @@ __global__ void __launch_bounds__(kMaxTileThreads) k_e_update(EArgs A) {
     __asm__ volatile("" ::"s"(state), "s"(xi), "s"(l), "s"(period), "s"(alpha64));
     if (state != kRun) continue;
     const T alpha = (T)alpha64;
-    const bool replace = (l % period) == 0;
+    const bool replace = divides(period, l);
     const T* U = cvec<T>(A.U, tp.off);
     const T* V = cvec<T>(A.V, tp.off);
     const T* aux = cvec<T>(A.aux, tp.off);

@@ -21,6 +21,13 @@ enum FinOp : int {
   kFinTailW = 7     // slot 1 over the 64-row strips of the natural-order sweeps: r.s
 };
 
+// Whether period divides l, without the long 64-bit remainder for the values
+// an iteration count takes.
+__device__ __forceinline__ bool divides(long long period, long long l) {
+  if ((unsigned long long)(period | l) >> 32 == 0) return (unsigned)l % (unsigned)period == 0;
+  return l % period == 0;
+}
+
 __device__ inline void map_finish(MapState& s, int mode, double rs) {
   if (mode == kFinishIter) {
     s.delta_old = s.delta_new;
@@ -129,28 +136,28 @@ template <int NS>
 __device__ __forceinline__ void fin_sums_flat(const FinSrc& src, int first, int count,
                                               const int (&slots)[NS], double (&out)[NS],
                                               double* smem) {
-  // The loads of kFlatLoads consecutive terms are issued together, since
-  // they go to the level the XCDs share and a chain of single loads would put
+  // The loads of kFlatLoads consecutive terms of every slot are issued together,
+  // since they go to the level the XCDs share and a chain of single loads would put
   // their full latency on the map's finisher, often the last work of a launch.
   constexpr int kU = kFlatLoads;
   const int nb = src.nt;
   if ((int)threadIdx.x >= nb) count = 0;
 #pragma unroll
-  for (int k = 0; k < NS; ++k) {
-    const double* base = src.P + slots[k] * src.pstride + first;
-    double v = 0.0;
-    for (int t0 = threadIdx.x; t0 < count; t0 += kU * nb) {
-      double x[kU];
+  for (int k = 0; k < NS; ++k) out[k] = 0.0;
+  for (int t0 = threadIdx.x; t0 < count; t0 += kU * nb) {
+    double x[NS][kU];
+#pragma unroll
+    for (int k = 0; k < NS; ++k)
 #pragma unroll
       for (int u = 0; u < kU; ++u) {
         const int t = t0 + u * nb;
-        x[u] = t < count ? load_partial(base + t) : 0.0;
+        x[k][u] = t < count ? load_partial(src.P + slots[k] * src.pstride + first + t) : 0.0;
       }
 #pragma unroll
+    for (int k = 0; k < NS; ++k)
+#pragma unroll
       for (int u = 0; u < kU; ++u)
-        if (t0 + u * nb < count) v += x[u];
-    }
-    out[k] = v;
+        if (t0 + u * nb < count) out[k] += x[k][u];
   }
   block_sum<NS>(out, smem);
 }
@@ -263,7 +270,7 @@ __device__ inline void finish_map(const MapDesc* __restrict__ desc, MapState* ms
       else s.alpha = s.delta_new / v[0];
       break;
     case kFinUpdate: {
-      const bool replace = (s.l % s.period) == 0;
+      const bool replace = divides(s.period, s.l);
       s.rr = v[0];
       s.replaced = replace ? 1 : 0;
       // a replacement wrote x + alpha d to the other buffer; otherwise the
