@@ -333,6 +333,11 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
       // iteration n chunk n is swept, chunk n + 2 written to LDS (its lines
       // reach into chunk n + 3's steps) and the lines that end in chunk n - 1
       // stored.
+      // The second wave of a SIMD (5 to 7) would fall behind the first, which is
+      // the older one, and a chunk waits for the last wave: with priority over
+      // the first the solves take 3 to 6 % less (840 x 1120 FP64 SSOR apply 318
+      // against 300 us, FP32 270 / 257).
+      if (wv >= 5) __builtin_amdgcn_s_setprio(1);
       if (wv == 0) {
         const int l = wf_lane();
         wf_barrier();
