@@ -31,7 +31,7 @@ sys.path.insert(0, ROOT)
 PEAK_HBM_GBS = 8000.0
 PEAK_BF16_TFLOPS = 2500.0
 PEAK_FP16_TFLOPS = 2500.0
-PEAK_FP64_TFLOPS = 78.6  # vector FMA units: the plain FP64 path's DCT stages run there
+PEAK_FP64_TFLOPS = 78.6  # FP64 matrix cores: the plain FP64 path's DCT stages run there
 # measured HBM traffic per launch (rocprofv3 FETCH_SIZE / WRITE_SIZE passes,
 # scaled by a plain copy), valid while the kernel sources hash as recorded
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "traffic_batch256_fp16.txt")
@@ -235,7 +235,7 @@ def main():
         # the binding roof is the one whose time at peak is longer: MFMA when
         # the launch's flops per algorithmic byte exceed the ridge point
         # (peak flops / peak bandwidth), HBM otherwise
-        # (on the plain FP64 path the DCT stages run on the FP64 FMA units)
+        # (on the plain FP64 path the DCT stages run on the FP64 matrix cores)
         peak_flops = PEAK_FP64_TFLOPS if fp64 else PEAK_FP16_TFLOPS
         ridge = peak_flops * 1e12 / (PEAK_HBM_GBS * 1e9)
         intensity = kt["flops"] / kt["bytes"] if kt["bytes"] > 0 else float("inf")

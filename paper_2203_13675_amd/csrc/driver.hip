@@ -766,10 +766,10 @@ static int run_maps(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, double p, do
       const double Mm = maps[m].rows, Nn = maps[m].cols;
       if (pc == kPcDct) {
         // per application: 4 contractions; MFMA products per multiply-add
-        // (3 for the bf16 split); the even/odd kernels do half the work
+        // (3 for the bf16 split); the even/odd kernels (FP64 too) do half the work
         const int kd = pcg.dct_kind;
         const double prod = (kd == 2 || kd == 4) ? 3.0 : 1.0;
-        const double half = kd >= 4 ? 0.5 : 1.0;
+        const double half = kd >= 4 || kd == 0 ? 0.5 : 1.0;
         // X in, Out out per stage (the scaled-fp16 even/odd path keeps the
         // three intermediates in 2 bytes), and r again in the last stage
         const double io = (kd == 5 ? px * (4.0 + 2.0 + 2.0 + 2.0 + 2.0 + 2.0 + 2.0 + 4.0)
@@ -793,7 +793,7 @@ static int run_maps(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, double p, do
       // entries (n x n/2 for the even/odd split), 2, 4 (the bf16 hi and lo
       // planes, or FP32) or 8 bytes each
       const int kd = pcg.dct_kind;
-      const double half = kd >= 4 ? 0.5 : 1.0;
+      const double half = kd >= 4 || kd == 0 ? 0.5 : 1.0;
       const double tab = kd == 0 ? 8.0 : (kd == 1 ? 4.0 : ((kd == 2 || kd == 4) ? 4.0 : 2.0));
       for (const auto& sa : side_apps)
         kt.credit(LPU_KC_DCT, 0, (double)sa.second * 2.0 * half * sa.first * sa.first * tab, 0.0);

@@ -917,7 +917,7 @@ __global__ void __launch_bounds__(kMaxTileThreads) k_e_update(EArgs A) {
 // applied in two passes, c = 2 - omega for SSOR and 1 otherwise:
 //   odd pixels:  s_o = c (r_o + sum_e w_oe r_e / p_e) / p_o   (forward solve)
 //   even pixels: s_e = (c r_e + sum_o w_eo s_o) / p_e         (backward solve)
-// Each pass is a stencil march of Eq. (7) with an operand that is zero on the
+// Each pass is a stencil pass of Eq. (7) with an operand that is zero on the
 // pixels it writes, so the neighbour sum is -(A x) there; the first pass only
 // writes odd pixels and the second only even ones, and each reads s only on
 // the colour it does not write.

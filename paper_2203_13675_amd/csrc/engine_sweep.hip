@@ -46,14 +46,15 @@
 // same; a strip whose wait runs out goes on with NaN, which ends that map's
 // solve as a breakdown.
 //
-// Measured (960 x 1280 FP64; 840 x 1120 FP32): a forward solve 154 and 110 us,
-// a backward one 164 and 121 us, the pivots 284 and 213 us, where one launch
+// Measured (960 x 1280 FP64; 840 x 1120 FP32): a forward solve 143 and 105 us,
+// a backward one 148 and 112 us, the pivots 286 and 213 us, where one launch
 // per anti-diagonal of 64 x 64 tiles took 34 x 14.7 us and 31 x 13.4 us for a
-// solve and 1290 and 1020 us for the pivots.  A chunk of 16 steps takes 0.6 us
-// (FP32) to 0.8 us (FP64), of which the sweeping wave computes 0.45 and 0.6, and
-// a strip starts 5.6 to 6.3 us after the one above it: 80 steps it must wait
-// (64 of skew and the chunk), two chunks of look-ahead, and the trip of the
-// last row's values through memory.
+// solve and 1290 and 1020 us for the pivots.  A chunk of 16 steps takes 0.5 us
+// (FP32) to 0.75 us (FP64), nearly all of it the sweeping wave's (76 and 105
+// cycles a step forward; leaving out any one of its LDS reads, its writes or the
+// lane shift saves 3 to 7 %), and a strip starts 5 to 6 us after the one above
+// it: 80 steps it must wait (64 of skew and the chunk), two chunks of
+// look-ahead, and the trip of the last row's values through memory.
 
 #include <type_traits>
 
