@@ -13,6 +13,8 @@
 //               - V_{i,j} x_{i+1,j} - V_{i-1,j} x_{i-1,j},
 // out-of-grid terms zero (U is 0 on the last column, V on the last row).
 
+#include <type_traits>
+
 #include "lpu_internal.h"
 #include "lpu_device.h"
 #include "lpu_finish.h"
@@ -124,6 +126,9 @@ __device__ __forceinline__ T ldz(const T* __restrict__ a, int i, int j, int M, i
   return ok ? v : T(0);
 }
 
+__device__ __forceinline__ float fused(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fused(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 template <typename T>
 __device__ __forceinline__ T stencil5(T uw, T uc, T vn, T vc, T xc, T xw, T xe, T xn, T xs) {
   return (uw + uc + vn + vc) * xc - uc * xe - uw * xw - vc * xs - vn * xn;
@@ -231,15 +236,16 @@ struct TileSum {
 // Stencil over the tile's rows of this wave: for every interior pixel
 // epi(i, row, j, x_ij, (A x)_ij, raw_ij, own_ij), row = i N, which returns the
 // pixel's terms of the sums in ts.  The operand x is
-// formed as make(load(row, j), i, j) and is zero outside the grid; own(row, j)
+// formed as make(load(row, j), i, j) (make_north in the first column group of
+// the row above the tile) and is zero outside the grid; own(row, j)
 // loads what only the pixel itself needs.  load and own must only load: every
 // load of kRW rows (and of the operand rows above and below them) is issued
 // through clamped coordinates before the first value is used, so a wave pays
 // one memory round trip per kRW rows.
-template <typename T, int NS, bool OR, typename Ld, typename Mk, typename Ow, typename E>
+template <typename T, int NS, bool OR, typename Ld, typename Mk, typename Mn, typename Ow, typename E>
 __device__ __forceinline__ void stencil_tile(const TilePos& tp, TileSum<T, NS, OR>& ts,
                                              const T* __restrict__ U, const T* __restrict__ V,
-                                             Ld load, Mk make, Ow own, E epi) {
+                                             Ld load, Mk make, Mn make_north, Ow own, E epi) {
   const int M = tp.M, N = tp.N, j0 = tp.j0, l = lane_id();
   const int ca = j0 + l, cb = j0 + 64 + l;
   const bool oka = ca < N, okb = cb < N;
@@ -286,6 +292,9 @@ __device__ __forceinline__ void stencil_tile(const TilePos& tp, TileSum<T, NS, O
       return okc && (unsigned)i < (unsigned)M ? make(r, i, j) : T(0);
     };
     R2<T> xm{operand(ra[0], i0 - 1, ca, oka), operand(rb[0], i0 - 1, cb, okb)};
+    if constexpr (!std::is_same_v<Mk, Mn>) {
+      if (i0 == tp.i0) xm.a = oka && i0 > 0 ? make_north(ra[0], i0 - 1, ca) : T(0);
+    }
     R2<T> xc{operand(ra[1], i0, ca, oka), operand(rb[1], i0, cb, okb)};
     const T xh = operand(rh, ih, hj, okh);
     const T uw0 = j0 > 0 ? uh : T(0);  // the couplings to column j0 - 1
@@ -309,6 +318,13 @@ __device__ __forceinline__ void stencil_tile(const TilePos& tp, TileSum<T, NS, O
     ts.template add<kRW>(i0 == tp.i0 + wrow, ta, tb);
   }
   ts.finish();
+}
+
+template <typename T, int NS, bool OR, typename Ld, typename Mk, typename Ow, typename E>
+__device__ __forceinline__ void stencil_tile(const TilePos& tp, TileSum<T, NS, OR>& ts,
+                                             const T* __restrict__ U, const T* __restrict__ V,
+                                             Ld load, Mk make, Ow own, E epi) {
+  stencil_tile<T>(tp, ts, U, V, load, make, make, own, epi);
 }
 
 // Elementwise walk over the tile's pixels.
@@ -809,7 +825,15 @@ __global__ void __launch_bounds__(kMaxTileThreads) k_e_spmv(EArgs A) {
         [&](size_t row, unsigned j) {
           return Op{src[row + j], PC == kPcJacobi ? aux[row + j] : T(1), dold[row + j]};
         },
-        [&](const Op& v, int, int) { return (PC == kPcJacobi ? v.s * v.w : v.s) + beta * v.d; },
+        // Jacobi: s w + beta d rounds beta d first, except in the left half of the
+        // row above the tile: solves keep the bits they have always had (a mixed
+        // one of a thousand iterations moves by 1e-4 with one such rounding)
+        [&](const Op& v, int, int) {
+          return PC == kPcJacobi ? fused(v.s, v.w, beta * v.d) : fused(beta, v.d, v.s);
+        },
+        [&](const Op& v, int, int) {
+          return fused(beta, v.d, PC == kPcJacobi ? v.s * v.w : v.s);
+        },
         [&](size_t row, unsigned j) { return ld_stream(x + row + j); },
         [&](int, size_t row, unsigned j, T dv, T qv, const Op& v, T xv) {
           st_stream(dnew + row + j, dv);
