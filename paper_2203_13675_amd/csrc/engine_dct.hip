@@ -592,12 +592,14 @@ __global__ void __launch_bounds__(256, 2) k_e_dct_eo(DArgs a) {
       }
       if (a.fin_mode) {
         const int sl[1] = {1};
-        for (int k = 0; k < (NJ == 8 && full ? 2 : 1); ++k)
+        for (int k = 0; k < (NJ == 8 && full ? 2 : 1); ++k) {
+          if (k > 0) __syncthreads();  // every wave has read fflag
           fused_finish<kFinTail, 1>(Arrival{a.fcnt, a.gcnt, a.gsum, a.gstride, a.P, a.pstride}, sl,
                                     kEoParts * (g - t_local),
                                     kEoParts * (t_local + k * (R / 128)) + quarter,
                                     kEoParts * t_ndt, t_gbd, a.desc, a.ms, tm, a.fin_mode, 0, &fflag,
                                     fred, FINE ? 1 : kEoParts);
+        }
       }
     }
     __syncthreads();  // the next tile's first step may overwrite what slower waves still read
