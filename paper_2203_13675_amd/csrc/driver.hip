@@ -39,6 +39,7 @@ int egrid(const Engine& e, int ntiles);
 int dct_grid_for(const Engine& e, int ndtiles);
 int dct_shape_for(const Engine& e, int ndtiles, int kind);
 int dct_side(int M, int N, bool fp64);
+int dct_tiles_most(int M, int N);
 template <typename T> void e_pivots(hipStream_t, const Engine&, int, bool, double, bool);
 int wf_strips(int M);
 int wf_grid(const Engine& e);
@@ -135,8 +136,9 @@ static int dct_tile_for(const lpu_map* maps, int n, bool mixed, int dct_mode) {
   return mixed && dct_mode == LPU_DCT_FP32 ? kDT : 0;
 }
 
+// least_dtiles: DCT tiles to make room for whatever the maps have.
 static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem, bool need_dct,
-                        int dct_tile = kDT) {
+                        int dct_tile = kDT, int least_dtiles = 0) {
   Engine& e = ctx->eng;
   std::vector<MapDesc> hd(n);
   long long px = 0;
@@ -179,7 +181,8 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
       if (!d.tabM || !d.tabN) return stt ? stt : LPU_ERR_OOM;
     }
   }
-  const bool grow = px > e.cap_px || tiles > e.cap_tiles || dtiles > e.cap_dtiles ||
+  const int cdt = std::max(dtiles, least_dtiles);
+  const bool grow = px > e.cap_px || tiles > e.cap_tiles || cdt > e.cap_dtiles ||
                     n > e.cap_maps || elem > e.elem || strips > e.cap_strips || edges > e.cap_edge;
   if (grow) {
     // captured graphs hold the buffers' addresses; every other argument they
@@ -188,19 +191,19 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     engine_free(e);
     const long long cpx = std::max(px, 1LL);
     const size_t eb = (size_t)cpx * elem;
-    const long long pst = std::max<long long>(tiles, (long long)kEoParts * dtiles) + 64;
+    const long long pst = std::max<long long>(tiles, (long long)kEoParts * cdt) + 64;
     bool ok = true;
     auto A = [&](void** p, size_t bytes) {
       if (ok && hipMalloc(p, std::max<size_t>(bytes, 256)) != hipSuccess) ok = false;
     };
     A((void**)&e.desc, sizeof(MapDesc) * n);
     A((void**)&e.ms, sizeof(MapState) * n);
-    A((void**)&e.dtile_map, 4 * (size_t)dtiles);
-    A((void**)&e.eot, sizeof(EoTile) * 2 * (size_t)std::max(dtiles, 1));
+    A((void**)&e.dtile_map, 4 * (size_t)cdt);
+    A((void**)&e.eot, sizeof(EoTile) * 2 * (size_t)std::max(cdt, 1));
     // the lists of one activation, in one allocation laid out like the
     // pinned staging (counts, active maps, stencil tiles, the two DCT
     // lists), so the first three go up in one copy
-    const long long dcap = (long long)dtiles + 8LL * (n + 1) * 256 + 64;
+    const long long dcap = (long long)cdt + 8LL * (n + 1) * 256 + 64;
     const size_t list_ints =
         kListHead + (size_t)n + 2 * (size_t)strips + 2 * (size_t)tiles + 4 * (size_t)dcap;
     A((void**)&e.counts, 4 * list_ints);
@@ -214,7 +217,7 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     A((void**)&e.wctl, 256);
     A((void**)&e.wedge, 8 * (size_t)edges);
     // groups <= tiles / G + kEoParts dtiles / G + 2 n for any layout within these capacities
-    const long long gcap = (tiles + (long long)kEoParts * dtiles) / kArriveGroup + 2LL * n + 8;
+    const long long gcap = (tiles + (long long)kEoParts * cdt) / kArriveGroup + 2LL * n + 8;
     A((void**)&e.gcnt, 4 * (size_t)gcap * kArriveStride);
     A((void**)&e.gsum, 8 * 2 * (size_t)gcap);
     A((void**)&e.dx, 8 * (size_t)cpx);
@@ -235,7 +238,7 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     }
     e.cap_px = px;
     e.cap_tiles = tiles;
-    e.cap_dtiles = dtiles;
+    e.cap_dtiles = cdt;
     e.cap_maps = n;
     e.cap_strips = strips;
     e.cap_edge = edges;
@@ -329,8 +332,9 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
 }
 
 // Size the work buffers for one map of M x N in FP64 (enough for any one map
-// of at most that size in either precision, under the current tile height);
-// called by lp_unwrap_create so a first solve allocates nothing.
+// of at most that size in either precision, under the current tile height; of
+// DCT tiles a smaller map may have more); called by lp_unwrap_create so a first
+// solve allocates its DCT tables only.
 int engine_reserve(lp_unwrap_ctx* ctx, int M, int N) {
   lpu_map mp;
   mp.rows = M;
@@ -338,7 +342,7 @@ int engine_reserve(lp_unwrap_ctx* ctx, int M, int N) {
   mp.psi = nullptr;
   mp.mask = nullptr;
   mp.phi = nullptr;
-  return engine_setup(ctx, 1, &mp, 8, false, kDT);
+  return engine_setup(ctx, 1, &mp, 8, false, kDT, dct_tiles_most(M, N));
 }
 
 // Make the tile lists cover exactly the maps in `set`.

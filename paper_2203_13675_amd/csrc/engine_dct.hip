@@ -1370,6 +1370,16 @@ int dct_side(int M, int N, bool fp64) {
   return t >= (fp64 ? kF64Wide : kDenseWide) ? 64 : 32;
 }
 
+// An upper bound of the DCT tiles of any one map of at most M x N, in every kind of
+// stage: below the rule's line (kF64Wide tiles of 64 x 64, the higher one) a map has up
+// to four tiles of 32 x 32 for each of 64 x 64, so a smaller map can have more tiles than
+// a larger one.
+int dct_tiles_most(int M, int N) {
+  auto tiles = [&](int side) { return (long long)((M + side - 1) / side) * ((N + side - 1) / side); };
+  static_assert(kF64Wide >= kDenseWide, "the higher line");
+  return (int)std::max(tiles(64), std::min(tiles(32), 4LL * (kF64Wide - 1)));
+}
+
 // Grid of a DCT stage: the next power of two >= the list length, capped; a
 // multiple of 8, so list position q always runs on XCD q mod 8.
 int dct_grid_for(const Engine& e, int ndtiles) {
