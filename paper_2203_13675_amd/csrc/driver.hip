@@ -87,6 +87,62 @@ static void engine_free(Engine& e) {
   e = Engine();
 }
 
+// Buffers of the capacities c in the place of the engine's; on failure it is left
+// without any.
+static bool engine_allocate(Engine& e, const EngineCaps& c) {
+  engine_free(e);
+  const size_t px = (size_t)std::max(c.px, 1LL);
+  const long long pst = std::max<long long>(c.tiles, (long long)kEoParts * c.dtiles) + 64;
+  bool ok = true;
+  auto A = [&](void** p, size_t bytes) {
+    if (ok && hipMalloc(p, std::max<size_t>(bytes, 256)) != hipSuccess) ok = false;
+  };
+  A((void**)&e.desc, sizeof(MapDesc) * c.maps);
+  A((void**)&e.ms, sizeof(MapState) * c.maps);
+  A((void**)&e.dtile_map, 4 * (size_t)c.dtiles);
+  A((void**)&e.eot, sizeof(EoTile) * 2 * (size_t)std::max(c.dtiles, 1));
+  // the lists of one activation, in one allocation laid out like the
+  // pinned staging (counts, active maps, strips, stencil tiles, the DCT
+  // lists), so all but the DCT lists go up in one copy
+  const long long dcap = (long long)c.dtiles + 8LL * (c.maps + 1) * 256 + 64;
+  const size_t list_ints =
+      kListHead + (size_t)c.maps + 2 * (size_t)c.strips + 2 * (size_t)c.tiles + 4 * (size_t)dcap;
+  A((void**)&e.counts, 4 * list_ints);
+  if (ok) {
+    e.mact = e.counts + kListHead;
+    e.slist = e.mact + c.maps;
+    e.act = e.slist + 2 * (size_t)c.strips;
+    e.dact = e.act + 2 * (size_t)c.tiles;
+  }
+  A((void**)&e.fcnt, 4 * (size_t)c.maps * kArriveStride);
+  A((void**)&e.wctl, 256);
+  A((void**)&e.wedge, 8 * (size_t)c.edges);
+  // groups <= tiles / G + kEoParts dtiles / G + 2 n for any layout within these capacities
+  const long long gcap = (c.tiles + (long long)kEoParts * c.dtiles) / kArriveGroup + 2LL * c.maps + 8;
+  A((void**)&e.gcnt, 4 * (size_t)gcap * kArriveStride);
+  A((void**)&e.gsum, 8 * 2 * (size_t)gcap);
+  A((void**)&e.dx, 8 * px);
+  A((void**)&e.dy, 8 * px);
+  A((void**)&e.phi_prev, 8 * px);
+  A((void**)&e.r64, 8 * px);
+  void** tv[] = {&e.U, &e.V, &e.aux, &e.x[0], &e.x[1], &e.d[0], &e.d[1],
+                 &e.r, &e.s, &e.q, &e.b, &e.t1, &e.t2};
+  for (void** p : tv) A(p, (size_t)c.vec);
+  A((void**)&e.iso, px);
+  A((void**)&e.P, 8 * (size_t)kNumSlots * pst);
+  if (ok && hipHostMalloc((void**)&e.hms, sizeof(MapState) * c.maps) != hipSuccess) ok = false;
+  if (ok && hipHostMalloc((void**)&e.hlist, 4 * list_ints) != hipSuccess) ok = false;
+  if (!ok) {
+    engine_free(e);
+    return false;
+  }
+  e.caps = c;
+  e.dlist_cap = dcap;
+  e.pstride = pst;
+  e.gstride = gcap;
+  return true;
+}
+
 void release_graphs(lp_unwrap_ctx* ctx) {
   for (GraphEntry& g : ctx->graphs)
     if (g.exec) (void)hipGraphExecDestroy(g.exec);
@@ -117,7 +173,6 @@ static const DctTabDev* dct_dev(lp_unwrap_ctx* ctx, int n, int* status) {
   return d;
 }
 
-// Lay out n maps; (re)allocate grow-only; upload descriptors and tile maps.
 // DCT output tiles are 64 x 64 for the FP32 FMA kernel and 64 x 64 or 32 x 32 by
 // the map's size for the FP64 and dense MFMA ones (dct_tile 0); the even/odd kernels
 // (used when every side is a multiple of 128 in the mixed path with MFMA
@@ -136,7 +191,8 @@ static int dct_tile_for(const lpu_map* maps, int n, bool mixed, int dct_mode) {
   return mixed && dct_mode == LPU_DCT_FP32 ? kDT : 0;
 }
 
-// least_dtiles: DCT tiles to make room for whatever the maps have.
+// Lay out n maps; grow the buffers where these exceed them; upload descriptors and
+// tile maps.  least_dtiles: DCT tiles to make room for whatever the maps have.
 static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem, bool need_dct,
                         int dct_tile = kDT, int least_dtiles = 0) {
   Engine& e = ctx->eng;
@@ -181,75 +237,25 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
       if (!d.tabM || !d.tabN) return stt ? stt : LPU_ERR_OOM;
     }
   }
-  const int cdt = std::max(dtiles, least_dtiles);
-  const bool grow = px > e.cap_px || tiles > e.cap_tiles || cdt > e.cap_dtiles ||
-                    n > e.cap_maps || elem > e.elem || strips > e.cap_strips || edges > e.cap_edge;
-  if (grow) {
+  const EngineCaps own{px, px * elem, edges, tiles, std::max(dtiles, least_dtiles), n, strips};
+  if (!e.caps.cover(own)) {
     // captured graphs hold the buffers' addresses; every other argument they
     // capture is part of their key, and the layout itself is device data
     release_graphs(ctx);
-    engine_free(e);
-    const long long cpx = std::max(px, 1LL);
-    const size_t eb = (size_t)cpx * elem;
-    const long long pst = std::max<long long>(tiles, (long long)kEoParts * cdt) + 64;
-    bool ok = true;
-    auto A = [&](void** p, size_t bytes) {
-      if (ok && hipMalloc(p, std::max<size_t>(bytes, 256)) != hipSuccess) ok = false;
-    };
-    A((void**)&e.desc, sizeof(MapDesc) * n);
-    A((void**)&e.ms, sizeof(MapState) * n);
-    A((void**)&e.dtile_map, 4 * (size_t)cdt);
-    A((void**)&e.eot, sizeof(EoTile) * 2 * (size_t)std::max(cdt, 1));
-    // the lists of one activation, in one allocation laid out like the
-    // pinned staging (counts, active maps, stencil tiles, the two DCT
-    // lists), so the first three go up in one copy
-    const long long dcap = (long long)cdt + 8LL * (n + 1) * 256 + 64;
-    const size_t list_ints =
-        kListHead + (size_t)n + 2 * (size_t)strips + 2 * (size_t)tiles + 4 * (size_t)dcap;
-    A((void**)&e.counts, 4 * list_ints);
-    if (ok) {
-      e.mact = e.counts + kListHead;
-      e.slist = e.mact + n;
-      e.act = e.slist + 2 * (size_t)strips;
-      e.dact = e.act + 2 * (size_t)tiles;
+    // no capacity shrinks, so calls of different sizes settle on one allocation;
+    // where that much does not fit, this call's own sizes still may
+    const EngineCaps all = e.caps.with(own);
+    bool ok = engine_allocate(e, all);
+    if (!ok && !own.cover(all)) {
+      (void)hipGetLastError();
+      ok = engine_allocate(e, own);
     }
-    A((void**)&e.fcnt, 4 * (size_t)n * kArriveStride);
-    A((void**)&e.wctl, 256);
-    A((void**)&e.wedge, 8 * (size_t)edges);
-    // groups <= tiles / G + kEoParts dtiles / G + 2 n for any layout within these capacities
-    const long long gcap = (tiles + (long long)kEoParts * cdt) / kArriveGroup + 2LL * n + 8;
-    A((void**)&e.gcnt, 4 * (size_t)gcap * kArriveStride);
-    A((void**)&e.gsum, 8 * 2 * (size_t)gcap);
-    A((void**)&e.dx, 8 * (size_t)cpx);
-    A((void**)&e.dy, 8 * (size_t)cpx);
-    A((void**)&e.phi_prev, 8 * (size_t)cpx);
-    A((void**)&e.r64, 8 * (size_t)cpx);
-    void** tv[] = {&e.U, &e.V, &e.aux, &e.x[0], &e.x[1], &e.d[0], &e.d[1],
-                   &e.r, &e.s, &e.q, &e.b, &e.t1, &e.t2};
-    for (void** p : tv) A(p, eb);
-    A((void**)&e.iso, (size_t)cpx);
-    A((void**)&e.P, 8 * (size_t)kNumSlots * pst);
-    if (ok && hipHostMalloc((void**)&e.hms, sizeof(MapState) * n) != hipSuccess) ok = false;
-    if (ok && hipHostMalloc((void**)&e.hlist, 4 * list_ints) != hipSuccess) ok = false;
-    e.dlist_cap = dcap;
-    if (!ok) {
-      engine_free(e);
-      return set_error(ctx, LPU_ERR_OOM, "engine allocation failed");
-    }
-    e.cap_px = px;
-    e.cap_tiles = tiles;
-    e.cap_dtiles = cdt;
-    e.cap_maps = n;
-    e.cap_strips = strips;
-    e.cap_edge = edges;
-    e.elem = elem;
-    e.pstride = pst;
-    e.gstride = gcap;
-    if (hipMemset(e.iso, 0, (size_t)cpx) != hipSuccess)
+    if (!ok) return set_error(ctx, LPU_ERR_OOM, "engine allocation failed");
+    if (hipMemset(e.iso, 0, (size_t)std::max(e.caps.px, 1LL)) != hipSuccess)
       return set_error(ctx, LPU_ERR_HIP, "hipMemset");
     // no launch's tag (launches count from 1) is in a fresh edge buffer
     if (hipMemsetAsync(e.wctl, 0, 256, ctx->stream) != hipSuccess ||
-        hipMemsetAsync(e.wedge, 0, 8 * (size_t)edges, ctx->stream) != hipSuccess)
+        hipMemsetAsync(e.wedge, 0, 8 * (size_t)e.caps.edges, ctx->stream) != hipSuccess)
       return set_error(ctx, LPU_ERR_HIP, "hipMemsetAsync");
   }
   // arrival counters start at zero (every launch leaves them so; cleared
@@ -324,7 +330,7 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
       }
     }
     LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.eot, eo.data(), sizeof(EoTile) * dtiles, hipMemcpyHostToDevice, st));
-    LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.eot + e.cap_dtiles, eo.data() + dtiles, sizeof(EoTile) * dtiles,
+    LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.eot + e.caps.dtiles, eo.data() + dtiles, sizeof(EoTile) * dtiles,
                                       hipMemcpyHostToDevice, st));
   }
   LPU_HIP_CHECK(ctx, hipStreamSynchronize(st));  // pageable sources
@@ -358,9 +364,9 @@ static int engine_activate(lp_unwrap_ctx* ctx, const std::vector<int>& set, int*
   // staging with the device layout: counts, maps, stencil tiles, DCT lists
   int* hc = e.hlist;
   int* hm = hc + kListHead;
-  int* hs = hm + e.cap_maps;
-  int* h = hs + 2 * (size_t)e.cap_strips;
-  int* hd = h + 2 * (size_t)e.cap_tiles;
+  int* hs = hm + e.caps.maps;
+  int* h = hs + 2 * (size_t)e.caps.strips;
+  int* hd = h + 2 * (size_t)e.caps.tiles;
   int nt = 0;
   for (int m : set)
     for (int t = 0; t < e.hdesc[m].ntiles; ++t, ++nt) {
@@ -448,7 +454,7 @@ static int engine_activate(lp_unwrap_ctx* ctx, const std::vector<int>& set, int*
   hc[7] = ndl[3];
   // counts, maps, strips and stencil tiles in one copy, then each DCT list
   const size_t head =
-      (size_t)kListHead + (size_t)e.cap_maps + 2 * (size_t)e.cap_strips + 2 * (size_t)nt;
+      (size_t)kListHead + (size_t)e.caps.maps + 2 * (size_t)e.caps.strips + 2 * (size_t)nt;
   LPU_HIP_CHECK(ctx, hipMemcpyAsync(e.counts, hc, 4 * head, hipMemcpyHostToDevice, st));
   for (int li = 0; li < nlists; ++li)
     if (ndl[li])

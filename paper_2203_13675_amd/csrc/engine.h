@@ -15,6 +15,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <vector>
 
@@ -90,15 +91,31 @@ struct MapState {
   float amax[4];
 };
 
+// What an engine's buffers hold at most.  A smaller map can need more of one of them
+// than a larger one (DCT tiles, edge values), so they are kept one by one.
+struct EngineCaps {
+  long long px = 0;     // pixels
+  long long vec = 0;    // bytes of a vector of the working precision
+  long long edges = 0;  // entries of wedge
+  int tiles = 0, dtiles = 0, maps = 0, strips = 0;
+  bool cover(const EngineCaps& o) const {
+    return px >= o.px && vec >= o.vec && edges >= o.edges && tiles >= o.tiles && dtiles >= o.dtiles &&
+           maps >= o.maps && strips >= o.strips;
+  }
+  EngineCaps with(const EngineCaps& o) const {
+    return {std::max(px, o.px), std::max(vec, o.vec), std::max(edges, o.edges), std::max(tiles, o.tiles),
+            std::max(dtiles, o.dtiles), std::max(maps, o.maps), std::max(strips, o.strips)};
+  }
+};
+
 struct Engine {
-  int elem = 0;              // sizeof(T) of the vectors this engine was sized for
-  int n_maps = 0, cap_maps = 0;
-  long long total_px = 0, cap_px = 0;
-  int total_tiles = 0, total_dtiles = 0, cap_tiles = 0, cap_dtiles = 0;
+  EngineCaps caps;
+  int n_maps = 0;
+  long long total_px = 0;
+  int total_tiles = 0, total_dtiles = 0;
   int max_n = 1;             // widest map
-  int total_strips = 0, cap_strips = 0;  // 64-row strips of the natural-order sweeps
-  int act_strips = 0;                    // those of the active maps
-  long long cap_edge = 0;                // entries of wedge
+  int total_strips = 0;      // 64-row strips of the natural-order sweeps
+  int act_strips = 0;        // those of the active maps
   int th = kTH;              // stencil tile height (rows)
   int grid = kEngineGrid;    // cap on the blocks of the stencil tile kernels
   int dct_grid = kDctGrid;   // cap on the blocks of a DCT stage (multiple of 8)

@@ -1424,7 +1424,7 @@ void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int ex
   a.gsum = e.gsum;
   a.gstride = e.gstride;
   a.eot = e.eot;
-  a.eot_cap = e.cap_dtiles;
+  a.eot_cap = e.caps.dtiles;
   // the finisher rides on the last stage of every kernel but the FP32 FMA one
   a.fin_mode = (stage == 3 && kind != 1) ? fin_mode : 0;
   a.desc = e.desc;

@@ -1101,7 +1101,7 @@ EArgs make_args(const Engine& e) {
   a.desc = e.desc;
   a.ms = e.ms;
   a.act = e.act;
-  a.act_cap = (int)e.cap_tiles;
+  a.act_cap = (int)e.caps.tiles;
   a.counts = e.counts;
   a.P = e.P;
   a.pstride = e.pstride;
