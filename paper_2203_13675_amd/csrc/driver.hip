@@ -36,7 +36,7 @@ void e_finish(hipStream_t st, const Engine& e, int op, int expect, int mode, boo
 void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int expect, int kind,
                  const void* X, void* Out, const void* rvec, int fin_mode);
 int egrid(const Engine& e, int ntiles);
-int dct_grid_for(const Engine& e, int ndtiles);
+int dct_grid_for(const Engine& e, int ndtiles, int kind);
 int dct_shape_for(const Engine& e, int ndtiles, int kind);
 int dct_side(int M, int N, bool fp64);
 int dct_tiles_most(int M, int N);
@@ -566,7 +566,7 @@ struct Pcg {
     if (!pointwise() && pc != kPcDct) std::memcpy(om, &omega, sizeof(om));
     for (int chunk = 8; chunk >= 1; chunk >>= 1) {
       if (K < chunk) continue;
-      const int key[kGraphKey] = {egrid(e, nt), pointwise() ? 0 : dct_grid_for(e, nd),
+      const int key[kGraphKey] = {egrid(e, nt), pc == kPcDct ? dct_grid_for(e, nd, dct_kind) : 0,
                                   pc == kPcDct ? dct_shape_for(e, nd, dct_kind) : 0,
                                   sweep ? wf_grid(e) : 0, pc, dct_kind,
                                   (int)sizeof(T), e.th, om[0], om[1], chunk};

@@ -1380,15 +1380,6 @@ int dct_tiles_most(int M, int N) {
   return (int)std::max(tiles(64), std::min(tiles(32), 4LL * (kF64Wide - 1)));
 }
 
-// Grid of a DCT stage: the next power of two >= the list length, capped; a
-// multiple of 8, so list position q always runs on XCD q mod 8.
-int dct_grid_for(const Engine& e, int ndtiles) {
-  const int cap = std::max(8, e.dct_grid / 8 * 8);
-  int g = 8;
-  while (g < ndtiles && g < cap) g <<= 1;
-  return std::min(g, cap);
-}
-
 // Tile shape of the even/odd stages (k_e_dct_eo): 0 fine, 1 narrow, 2 wide in
 // the first three stages, 3 wide in all; elsewhere 1 if the instances that take
 // tiles of 64 x 64 run, else 0.  It changes no result and is part of the
@@ -1412,12 +1403,23 @@ int dct_shape_for(const Engine& e, int ndtiles, int kind) {
   return ndtiles < kWideLastMin ? 2 : 3;
 }
 
+// Grid of a DCT stage: the next power of two >= the list length (fine tiles: four
+// blocks to an entry), capped; a multiple of 8, so list position q always runs on
+// XCD q mod 8.
+int dct_grid_for(const Engine& e, int ndtiles, int kind) {
+  const long long blocks = kind >= 4 && dct_shape_for(e, ndtiles, kind) == 0 ? 4LL * ndtiles : ndtiles;
+  const int cap = std::max(8, e.dct_grid / 8 * 8);
+  int g = 8;
+  while (g < blocks && g < cap) g <<= 1;
+  return std::min(g, cap);
+}
+
 void e_dct_stage(hipStream_t st, const Engine& e, int ndtiles, int stage, int expect, int kind,
                  const void* X, void* Out, const void* rvec, int fin_mode) {
   const int shape = dct_shape_for(e, ndtiles, kind);
   const bool fine = kind >= 4 && shape == 0;
   const bool wide = kind >= 4 && (shape == 3 || (shape == 2 && stage < 3));
-  const int grid = dct_grid_for(e, fine ? 4 * ndtiles : ndtiles);
+  const int grid = dct_grid_for(e, ndtiles, kind);
   DArgs a;
   a.fcnt = e.fcnt;
   a.gcnt = e.gcnt;
