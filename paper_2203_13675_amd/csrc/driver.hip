@@ -494,6 +494,10 @@ struct Pcg {
 
   bool pointwise() const { return pc == kPcNone || pc == kPcJacobi; }
 
+  // Whether r^T s is reduced by a launch of its own, of one block per map: the FP32
+  // FMA stages carry no finisher.
+  bool separate_finisher() const { return pc == kPcDct && dct_kind == 1; }
+
   // Preconditioner apply s = M^-1 r for the maps in state `expect`, then the
   // per-map finisher of r^T s with FinishMode `mode` (inside the last DCT
   // stage for the MFMA kernels, the second two-colour pass and the
@@ -501,16 +505,13 @@ struct Pcg {
   void tail(hipStream_t st, int nt, int ndt, int expect, int mode) {
     Engine& e = ctx->eng;
     KTimer& kt = ctx->kt;
-    bool fused = false;
     if (two_colour(pc)) {
       const int ev = kt.begin(LPU_KC_TWOCOLOR, st);
       e_twocolor<T>(st, e, nt, expect, pc == kPcSsorRb, omega, mode);
       kt.end(ev, LPU_KC_TWOCOLOR, st);
-      fused = true;
     } else if (pc == kPcDct) {
       const void* in[4] = {e.r, e.t1, e.t2, e.t1};
       void* out[4] = {e.t1, e.t2, e.t1, e.s};
-      fused = dct_kind != 1;
       for (int s = 0; s < 4; ++s) {
         const int ev = kt.begin(LPU_KC_DCT, st);
         e_dct_stage(st, e, ndt, s, expect, dct_kind, in[s], out[s], e.r, mode);
@@ -520,9 +521,8 @@ struct Pcg {
       const int ev = kt.begin(LPU_KC_SWEEP, st);
       e_sweep<T>(st, e, expect, pc == kPcSsor, omega, e.r, e.s, e.t1, mode);
       kt.end(ev, LPU_KC_SWEEP, st);
-      fused = true;
     }
-    if (!fused) fin(st, kFinTailH, expect, mode);
+    if (separate_finisher()) fin(st, kFinTailH, expect, mode);
   }
 
   void fin(hipStream_t st, int op, int expect, int mode = kFinishNone) {
@@ -569,6 +569,7 @@ struct Pcg {
       const int key[kGraphKey] = {egrid(e, nt), pc == kPcDct ? dct_grid_for(e, nd, dct_kind) : 0,
                                   pc == kPcDct ? dct_shape_for(e, nd, dct_kind) : 0,
                                   sweep ? wf_grid(e) : 0, pc, dct_kind,
+                                  separate_finisher() ? e.n_maps : 0,
                                   (int)sizeof(T), e.th, om[0], om[1], chunk};
       hipGraphExec_t ex = nullptr;
       for (const GraphEntry& g : ctx->graphs)

@@ -48,3 +48,25 @@ def test_dct_grid_cap_takes_effect_after_a_capture():
         again, c = best(ctx, 2048)
     assert torch.equal(a, b) and torch.equal(a, c)
     assert narrow > 1.3 * max(wide, again), (wide, narrow, again)
+
+
+@pytest.mark.parametrize("dct_mode", ["fp32", "split_bf16"])
+def test_batches_of_more_maps_on_the_same_grids(dct_mode):
+    """Batches of two, three and five maps whose launches have the same grids, in
+    one context: the FP32 transforms' finisher is a launch of one block per map,
+    so a graph kept from two maps would never finish the third."""
+    from paper_2203_13675_amd.binding import Context
+    rng = np.random.default_rng(4)
+    shapes = [[(200, 200)] * 2, [(200, 200), (96, 100), (90, 120)], [(200, 200)] + [(90, 60)] * 4]
+    batches = [[dev(rng.uniform(-3.0, 3.0, s)) for s in b] for b in shapes]
+    kw = dict(p=0.0, preconditioner="dct", precision="mixed", dct_mode=dct_mode, k_max=1,
+              outer_tol=0.0, check=False)
+    want = []
+    for b in batches:
+        with Context(0) as ctx:
+            want.append(ctx.batch(b, **kw)[0])
+    with Context(0) as ctx:
+        ctx.batch([dev(rng.uniform(-3.0, 3.0, (220, 210)))] * 5, **kw)  # buffers that hold every batch
+        for k in (0, 1, 2, 0):
+            phis, _, _ = ctx.batch(batches[k], **kw)
+            assert all(torch.equal(x, y) for x, y in zip(phis, want[k])), k
