@@ -128,12 +128,20 @@ __device__ __forceinline__ double fma_t(double a, double b, double c) { return _
 // Quotients of the pivot recurrence.  Both a pivot's quotients (by the pivot
 // to its west and by the one to its north) divide by a value some lane formed
 // one step earlier, so that lane forms its reciprocal once, and the shift
-// brings it along with the pivot.  rcp_full: 1 / b to about an ulp of a double
-// (the hardware's estimate and two Newton steps).  quot: the correctly rounded
-// a / b, as the division operator gives it: for a double by Markstein's final
-// step (IBM J. Res. Dev. 34, 1990: q = a r, then q + r (a - b q)); for floats
-// the product in double, whose error of 2^-51 cannot reach across a rounding
-// boundary of a 24-bit quotient (2^-49 away at least).
+// brings it along with the pivot.  rcp_full: 1 / b (the hardware's estimate and two
+// Newton steps).  quot: a / b as the division operator rounds it.
+//  * float: the product in double, whose error of 2^-51 cannot reach across a rounding
+//    boundary of a normal 24-bit quotient (2^-49 away at least).  A subnormal quotient
+//    is too small to count: its diagonal is at least the coupling, and a coupling
+//    whose square is not 0 is above 2^-75.
+//  * double: the steps by which the operator itself is carried out here (product with
+//    the reciprocal, then q + r (a - b q): Markstein, IBM J. Res. Dev. 34, 1990), but
+//    without its scaling, so as long as nothing leaves the normal range.  Couplings of
+//    Eq. (6) are at most 1.  With every coupling 0 or in 2^-300 .. 2^300 a pivot lies
+//    between kPivotFloor times the least and four times the largest, and squares,
+//    quotients, reciprocals and residuals are normal numbers.  A strip that meets
+//    another coupling, or a pivot above it outside that range, divides by the operator
+//    from there on (840 x 1120: 280 us for the pivots where the reciprocals take 226).
 __device__ __forceinline__ double rcp_full(double b) {
   double r = __builtin_amdgcn_rcp(b);
   r = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
@@ -144,6 +152,22 @@ __device__ __forceinline__ double quot(double a, double b, double r) {
   const double q = a * r;
   return __builtin_fma(__builtin_fma(-b, q, a), r, q);
 }
+
+// Whether every value seen is 0 or a double within 2^-300 .. 2^300 (SLACK: 2^-(300 +
+// SLACK) .. 2^(300 + SLACK)), from the high words: the least and the largest.
+struct PlainRange {
+  unsigned int least = 0x3ff00000u, most = 0x3ff00000u;
+  __device__ __forceinline__ void see(double x) {
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, x);
+    const unsigned int h = b == 0 ? 0x3ff00000u : (unsigned int)(b >> 32);
+    least = min(least, h);
+    most = max(most, h);  // (a negative value or a NaN is large)
+  }
+  template <int SLACK = 0>
+  __device__ __forceinline__ bool holds() const {
+    return least >= (1023u - 300u - SLACK) << 20 && most < (1023u + 300u + SLACK) << 20;
+  }
+};
 
 // A value of a strip's last row with its launch's tag: one 8-byte word for a
 // float, two (low and high half) for a double.  Words are single agent-coherent
@@ -296,8 +320,10 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
   __shared__ double yr[MODE == kWPivots ? W::R : 1];  // pivots: its reciprocals
   __shared__ double red[kWThreads / 64 * 3];
   __shared__ int sh_ticket, fflag;
+  __shared__ int sh_divide;  // kWatch: the strip met a value outside PlainRange
   constexpr T kOff = MODE == kWPivots ? T(1) : T(0);  // value off the map
   constexpr bool kRev = MODE == kWBackward;           // the sweep runs from the map's last pixel
+  constexpr bool kWatch = MODE == kWPivots && sizeof(T) == 8;  // see quot
   constexpr int kWords = sizeof(T) / 4;               // words of an edge entry
   const int tid = threadIdx.x;
   const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -305,8 +331,10 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
   const unsigned int tag = a.ctl[2] + 1u;
   const bool one_each = (int)gridDim.x >= n_strips;
   for (;;) {
-    if (tid == 0)
+    if (tid == 0) {
+      if (kWatch) sh_divide = 0;
       sh_ticket = (int)__hip_atomic_fetch_add(a.ctl, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     __syncthreads();
     const int tk = __builtin_amdgcn_readfirstlane(sh_ticket);
     if (tk >= n_strips) break;
@@ -353,7 +381,7 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
           if (MODE == kWPivots) orf[u] = yr[u];
         }
         int b = 0, ob3 = 0;
-        for (int n = 0; n < nc; ++n) {
+        auto chunk = [&](auto divide) {
           const int bn = (b + C) & (W::R - 1);
 #pragma unroll
           for (int u = 0; u < C; ++u) {
@@ -364,8 +392,15 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
               const T uw = ob[k].a, vn = ob[k].b;
               const T av = uw + oa[k].a + vn + oa[k].b;
               v = av;
-              const double rup = from_prev_lane(orf[k], rown);
-              const T qw = quot(uw * uw, own, rown), qn = quot(vn * vn, up, rup);
+              T qw, qn;
+              if constexpr (decltype(divide)::value) {
+                qw = uw * uw / own;
+                qn = vn * vn / up;
+              } else {
+                const double rup = from_prev_lane(orf[k], rown);
+                qw = quot(uw * uw, own, rown);
+                qn = quot(vn * vn, up, rup);
+              }
               v = uw != T(0) ? v - qw : v;
               v = vn != T(0) ? v - qn : v;
               if (v < (T)kPivotFloor * av) v = av;
@@ -386,6 +421,19 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
           }
           b = bn;
           ob3 = ob3 == (kWOut - 1) * C ? 0 : ob3 + C;
+        };
+        // a value outside the range is seen two chunks before its use; the flag is
+        // read a chunk ahead, and stays up to the strip's end
+        int n = 0, divide = kWatch ? __builtin_amdgcn_readfirstlane(sh_divide) : 0;
+        for (; n < nc && !divide; ++n) {
+          const int next = kWatch ? sh_divide : 0;
+          if (kWatch) __asm__ volatile("" ::: "memory");
+          chunk(std::false_type{});
+          if (kWatch) divide = __builtin_amdgcn_readfirstlane(next);
+          wf_barrier();
+        }
+        for (; kWatch && n < nc; ++n) {
+          chunk(std::true_type{});
           wf_barrier();
         }
         __builtin_amdgcn_s_setprio(0);
@@ -444,6 +492,7 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
           if (q >= nc) return;
           ln.fresh();
           const bool inner = wf_inner<T>(q, rows, N);
+          PlainRange seen;
 #pragma unroll
           for (int g = 0; g < kGL; ++g) {
 #pragma unroll
@@ -460,6 +509,7 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
                 w = c < N - 1 ? u : T(0);
                 p = {ok ? p.a : T(0), ok ? p.b : T(1)};
               }
+              if (kWatch) seen.see(u), seen.see(v);
               if (kRev) {
                 pa[at][row] = p;
                 pb[at][row] = {u, v};
@@ -471,6 +521,7 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
               }
             }
           }
+          if (kWatch && !seen.holds()) sh_divide = 1;
         };
         // lines of chunk -1 reach into chunk 0's steps
         const std::false_type any{};
@@ -540,6 +591,12 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
           if (l < C) {
             yb[c & (W::R - 1)] = v;
             if (MODE == kWPivots) yr[c & (W::R - 1)] = rcp_full((double)v);
+            if (kWatch && mine) {
+              PlainRange seen, above;
+              seen.see(vn);
+              above.see(v);
+              if (!seen.holds() || !above.template holds<16>()) sh_divide = 1;
+            }
             if (!kRev) pb[c & (W::R - 1)][0].b = mine ? vn : T(0);
           }
         };
