@@ -224,7 +224,9 @@ int lpu_rhs(lp_unwrap_ctx* ctx, int M, int N, int precision, const void* U, cons
 
 /* s = M^{-1} r for the preconditioner built from U, V (Section 2.1's list
  * and the DCT Poisson solve); zero on pixels with no weighted edge.
- * dct_mode applies to LPU_MIXED only.  U, V, r, s: M*N elements. */
+ * dct_mode applies to LPU_MIXED only.  U, V, r, s: M*N elements.
+ * LPU_ERR_HIP also when a strip of a natural-order sweep gave up waiting for the
+ * strip above it (its wait is bounded; s then holds NaN). */
 int lpu_precond_apply(lp_unwrap_ctx* ctx, int M, int N, int precision, int preconditioner,
                       int dct_mode, double omega, const void* U, const void* V,
                       const void* r, void* s);
@@ -232,7 +234,7 @@ int lpu_precond_apply(lp_unwrap_ctx* ctx, int M, int N, int precision, int preco
 /* ILU(0) = IC(0) pivots of A(U,V) in natural order: the diagonal of the
  * no-fill factor, d_{i,j} = a_{i,j} - U_{i,j-1}^2/d_{i,j-1} - V_{i-1,j}^2/d_{i-1,j},
  * a pivot below 1e-4 a_{i,j} replaced by a_{i,j}; 1 on isolated pixels.
- * U, V, piv: M*N elements. */
+ * U, V, piv: M*N elements.  LPU_ERR_HIP as for lpu_precond_apply. */
 int lpu_ilu_pivots(lp_unwrap_ctx* ctx, int M, int N, int precision, const void* U,
                    const void* V, void* piv);
 
@@ -328,7 +330,8 @@ int lp_unwrap_autotune(lp_unwrap_ctx* ctx, int n_maps, const lpu_map* maps, doub
  * overlap on one device (several streams or contexts) race and must be
  * serialised by the caller.  The call only enqueues work on the context's
  * stream (no allocation, no synchronisation, no host read-back) and returns
- * LPU_OK; s is ready when the stream reaches that point.  Errors:
+ * LPU_OK; s is ready when the stream reaches that point (NaN from the strip on
+ * whose wait for the one above it ran out; there is no status for it).  Errors:
  * LPU_ERR_INVALID_ARG, LPU_ERR_HIP (launch failure, or the array's address
  * could not be looked up when the context was created).
  * ------------------------------------------------------------------------- */
@@ -344,6 +347,13 @@ int lpu_precond_apply_noalloc(lp_unwrap_ctx* ctx, int M, int N, int precision, i
  * switches it off.  Errors: LPU_ERR_INVALID_ARG for a null context.
  * ------------------------------------------------------------------------- */
 int lpu_debug_force_breakdown(lp_unwrap_ctx* ctx, long long iteration);
+
+/* Testing hook for the bounded wait of the natural-order sweeps, whose strips of
+ * 64 rows pass their last row on: from the next call on, a strip polls for a value
+ * at most max_polls times (< 0: the default, about a second) before it gives up and
+ * goes on with NaN.  Every kernel still runs to completion.  Errors:
+ * LPU_ERR_INVALID_ARG for a null context, LPU_ERR_HIP. */
+int lpu_debug_sweep_polls(lp_unwrap_ctx* ctx, int max_polls);
 
 #ifdef __cplusplus
 }

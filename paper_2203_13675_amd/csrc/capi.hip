@@ -190,6 +190,14 @@ int lpu_debug_force_breakdown(lp_unwrap_ctx* ctx, long long iteration) {
   return LPU_OK;
 }
 
+int lpu_debug_sweep_polls(lp_unwrap_ctx* ctx, int max_polls) {
+  if (!ctx) return LPU_ERR_INVALID_ARG;
+  if (hipSetDevice(ctx->device) != hipSuccess) return LPU_ERR_HIP;
+  release_graphs(ctx);  // (the bound is a launch argument)
+  ctx->debug_sweep_polls = max_polls < 0 ? -1 : max_polls;
+  return LPU_OK;
+}
+
 void lp_unwrap_destroy(lp_unwrap_ctx* ctx) {
   if (!ctx) return;
   (void)hipSetDevice(ctx->device);

@@ -84,6 +84,7 @@ static void engine_free(Engine& e) {
     if (p) (void)hipFree(p);
   if (e.hms) (void)hipHostFree(e.hms);
   if (e.hlist) (void)hipHostFree(e.hlist);
+  if (e.lost) (void)hipHostFree(e.lost);
   e = Engine();
 }
 
@@ -132,6 +133,7 @@ static bool engine_allocate(Engine& e, const EngineCaps& c) {
   A((void**)&e.P, 8 * (size_t)kNumSlots * pst);
   if (ok && hipHostMalloc((void**)&e.hms, sizeof(MapState) * c.maps) != hipSuccess) ok = false;
   if (ok && hipHostMalloc((void**)&e.hlist, 4 * list_ints) != hipSuccess) ok = false;
+  if (ok && hipHostMalloc((void**)&e.lost, sizeof(int)) != hipSuccess) ok = false;
   if (!ok) {
     engine_free(e);
     return false;
@@ -270,6 +272,8 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
   e.total_dtiles = dtiles;
   e.max_n = maxN;
   e.total_strips = strips;
+  e.max_polls = ctx->debug_sweep_polls >= 0 ? ctx->debug_sweep_polls : kSweepPolls;
+  *e.lost = 0;  // (no earlier call's launch is still running)
   e.th = ctx->tune.tile_rows;
   e.grid = ctx->tune.grid;
   e.dct_grid = ctx->tune.dct_grid;
@@ -482,6 +486,11 @@ static int write_states(lp_unwrap_ctx* ctx) {
   LPU_HIP_CHECK(ctx, hipStreamSynchronize(ctx->stream));
   return LPU_OK;
 }
+
+// Whether a strip of a natural-order sweep gave up waiting since the engine was laid
+// out (read once the stream has been waited for).
+static const char* const kSweepLost = "a strip of a sweep gave up waiting for the strip above it";
+static bool sweep_lost(const Engine& e) { return *(volatile int*)e.lost != 0; }
 
 // ---------------------------------------------------------------------------
 // PCG over a set of maps
@@ -948,7 +957,8 @@ static int run_maps(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, double p, do
       s.status = status[m];
     }
   }
-  if (worst == LPU_ERR_BREAKDOWN) set_error(ctx, worst, "PCG breakdown");
+  if (worst == LPU_ERR_BREAKDOWN)
+    set_error(ctx, worst, sweep_lost(e) ? std::string("PCG breakdown: ") + kSweepLost : "PCG breakdown");
   return worst;
 }
 
@@ -1048,7 +1058,7 @@ int step_pivots(lp_unwrap_ctx* ctx, int M, int N, const T* U, const T* V, T* piv
   e_pivots<T>(ctx->stream, e, 1, ssor, omega, false);
   if ((rc = copy_in(ctx, piv, e.aux, b))) return rc;
   LPU_HIP_CHECK(ctx, hipStreamSynchronize(ctx->stream));
-  return LPU_OK;
+  return sweep_lost(e) ? set_error(ctx, LPU_ERR_HIP, kSweepLost) : LPU_OK;
 }
 
 template <typename T>
@@ -1104,7 +1114,7 @@ int step_precond(lp_unwrap_ctx* ctx, int M, int N, int pc, int dct_mode, double 
     if ((rc = copy_in(ctx, s, e.s, b))) return rc;
   }
   LPU_HIP_CHECK(ctx, hipStreamSynchronize(st));
-  return LPU_OK;
+  return sweep_lost(e) ? set_error(ctx, LPU_ERR_HIP, kSweepLost) : LPU_OK;
 }
 
 #define LPU_INST_STEP(T)                                                                          \

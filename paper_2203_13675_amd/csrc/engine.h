@@ -31,6 +31,9 @@ constexpr int kArriveStride = 64;  // ints from one arrival counter to the next 
 constexpr int kEoParts = 4;        // partials of r^T s of an even/odd DCT tile, one per quarter
 constexpr int kNumSlots = 4;       // partial-sum slots
 constexpr int kListHead = 16;      // ints of counts[] ahead of the active-map list
+// polls of one wait of the sweeps: about a second, where a wait on a running predecessor
+// takes microseconds
+constexpr int kSweepPolls = 1 << 20;
 
 // DCT tables of one size n as seen by the FP32 FMA kernel.
 struct DctTabDev {
@@ -132,6 +135,8 @@ struct Engine {
   bool dct_tile64 = false;   // a map takes FP64 or dense MFMA DCT tiles of 64 x 64
   int* mact = nullptr;       // active maps (sweep kernels)
   int* slist = nullptr;      // (map, strip) pairs of the active maps' strips, strip by strip
+  int max_polls = kSweepPolls;  // sweeps: polls of a wait before it is given up
+  int* lost = nullptr;          // sweeps: pinned word, set when one was given up
   unsigned int* wctl = nullptr;        // sweeps: ticket, workgroups done, launches so far
   unsigned long long* wedge = nullptr; // sweeps: tagged last rows of the strips
   int* fcnt = nullptr;       // per-map arrival counters of the fused finishers (zero between launches)

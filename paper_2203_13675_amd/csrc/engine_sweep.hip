@@ -44,7 +44,8 @@
 // workgroup waits for is finished or held by a workgroup that already runs,
 // whatever the number of resident workgroups.  The wait is bounded all the
 // same; a strip whose wait runs out goes on with NaN, which ends that map's
-// solve as a breakdown.
+// solve as a breakdown, and says so in a word that the calls that wait for the
+// device read (WArgs::lost).
 //
 // Measured (960 x 1280 FP64; 840 x 1120 FP32): a forward solve 143 and 105 us,
 // a backward one 148 and 112 us, the pivots 286 and 213 us, where one launch
@@ -73,9 +74,6 @@ constexpr int kWAhead = 8;   // steps between reading a step's operands and usin
 constexpr int kWHeld = 3;    // chunks a loader or storer wave holds in registers
 constexpr int kWPitch = kWT + 1;  // LDS entries per step (an element's row + 1 is a valid entry)
 constexpr int kWMaxGrid = 512;
-// polls of one wait before it is given up: about a second, where a wait on a
-// running predecessor takes microseconds
-constexpr int kWMaxPolls = 1 << 20;
 
 enum SweepMode : int { kWPivots = 0, kWForward = 1, kWBackward = 2 };
 
@@ -97,6 +95,8 @@ struct WArgs {
   int expect;    // state of the maps to work on (-1: every active map)
   int fin_mode;  // backward: FinishMode of the fused finisher of r^T s (0: none)
   int recip;     // pivots: store 1 / p (what the solves read) instead of p
+  int max_polls; // of one wait before it is given up
+  int* lost;     // host word set when that happens, or null
   double omega;
   int ssor;
 };
@@ -580,8 +580,10 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
             for (int k = 0;; ++k) {
               if (need && ew.ready(tag)) v = ew.value(), need = false;
               if (__builtin_amdgcn_ballot_w64(need) == 0) break;
-              if (lost || k >= kWMaxPolls) {
+              if (lost || k >= a.max_polls) {
                 if (need) v = T(__builtin_nanf(""));
+                if (!lost && a.lost)
+                  __hip_atomic_store(a.lost, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                 lost = true;
                 break;
               }
@@ -797,6 +799,8 @@ static WArgs make_wargs(const Engine& e, int expect, bool ssor, double omega, co
   a.expect = expect;
   a.fin_mode = 0;
   a.recip = 1;
+  a.max_polls = e.max_polls;
+  a.lost = e.lost;
   a.omega = omega;
   a.ssor = ssor ? 1 : 0;
   return a;
