@@ -200,7 +200,7 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
   Engine& e = ctx->eng;
   std::vector<MapDesc> hd(n);
   long long px = 0;
-  int tiles = 0, dtiles = 0, maxN = 1, groups = 0, strips = 0;
+  int tiles = 0, dtiles = 0, groups = 0, strips = 0;
   long long edges = 0;
   for (int m = 0; m < n; ++m) {
     MapDesc& d = hd[m];
@@ -228,7 +228,6 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
     d.mask = maps[m].mask;
     d.phi = maps[m].phi;
     d.use_iso = maps[m].mask != nullptr ? 1 : 0;
-    maxN = std::max(maxN, d.N);
     d.edge0 = edges;
     edges += 2LL * wf_strips(d.M) * d.N;
     strips += wf_strips(d.M);
@@ -267,10 +266,8 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
       hipMemsetAsync(e.wctl, 0, 8, ctx->stream) != hipSuccess)
     return set_error(ctx, LPU_ERR_HIP, "hipMemsetAsync");
   e.n_maps = n;
-  e.total_px = px;
   e.total_tiles = tiles;
   e.total_dtiles = dtiles;
-  e.max_n = maxN;
   e.total_strips = strips;
   e.max_polls = ctx->debug_sweep_polls >= 0 ? ctx->debug_sweep_polls : kSweepPolls;
   *e.lost = 0;  // (no earlier call's launch is still running)

@@ -43,8 +43,9 @@ struct DctTabDev {
 };
 
 // One tile of the MFMA DCT stages for one stage parity (rows of X are the map's
-// rows for parity 0, its columns for parity 1), with everything a block reads to start the tile, so a tile costs one record
-// load instead of a chain of descriptor loads.
+// rows for parity 0, its columns for parity 1), with everything a block reads to
+// start the tile, so a tile costs one record load instead of a chain of descriptor
+// loads.
 struct EoTile {
   long long off;          // element offset of the map
   const uint16_t* tf[3];  // forward tables of the contracted side (EO, or the dense C with
@@ -114,9 +115,7 @@ struct EngineCaps {
 struct Engine {
   EngineCaps caps;
   int n_maps = 0;
-  long long total_px = 0;
   int total_tiles = 0, total_dtiles = 0;
-  int max_n = 1;             // widest map
   int total_strips = 0;      // 64-row strips of the natural-order sweeps
   int act_strips = 0;        // those of the active maps
   int th = kTH;              // stencil tile height (rows)
@@ -143,7 +142,7 @@ struct Engine {
   int* gcnt = nullptr;       // per-group arrival counters (groups of kArriveGroup tiles of one map)
   double* gsum = nullptr;    // group sums of the fused finishers: 2 rows of gstride
   long long gstride = 0;
-  EoTile* eot = nullptr;     // even/odd DCT tile records, [parity][global DCT tile]
+  EoTile* eot = nullptr;     // tile records of the MFMA DCT stages, [parity][global DCT tile]
   int* counts = nullptr;     // [0] active tiles, [1] DCT list (even stages), [2] active
                              // maps, [3] DCT list (odd stages), [4] active strips, [5] and
                              // [7] the wide-tile lists; kListHead ints, followed in the same

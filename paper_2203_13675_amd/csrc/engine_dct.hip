@@ -45,10 +45,10 @@ struct DArgs {
   int *fcnt, *gcnt;  // arrival counters of the fused finisher
   double* gsum;      // its group sums (rows of gstride)
   long long gstride;
-  const EoTile* eot;  // even/odd tile records: [stage parity][global DCT tile]
+  const EoTile* eot;  // tile records: [stage parity][global DCT tile]
   long long eot_cap;
-  int fin_mode;  // last stage of the even/odd kernels: 0, or the FinishMode of
-                 // the fused finisher (the map's r^T s, beta and stop tests)
+  int fin_mode;  // last stage of the MFMA kernels: 0, or the FinishMode of the
+                 // fused finisher (the map's r^T s, beta and stop tests)
 };
 
 struct DTile {
@@ -624,7 +624,11 @@ __global__ void __launch_bounds__(256, 2) k_e_dct_eo(DArgs a) {
 // (split bf16 / fp16) with tiles of 64 and of 32: 53 / 53 and 45 / 48 us at
 // 64^2, 88 / 79 and 75 / 75 at 480 x 640, 110 / 97 and 106 / 101 at 720 x 960
 // (180 tiles of 64), 176 / 144 and 209 / 185 at 1000 x 1500 (384), 436 / 305 and
-// 662 / 485 at 2000^2, hence the rule's kDenseWide.  The kernel it replaces
+// 662 / 485 at 2000^2.  kDenseWide lies just above 180 tiles, where the split
+// still prefers 32 (by 4 %) and fp16 already 64 (by 4 %); nothing was measured
+// between there and 384.  The side is the map's alone, so a full launch of many
+// small maps takes 32 as well (48 maps of 480 x 640, split: 99 ms a call where
+// the kernel before took 140).  The kernel it replaces
 // (64 x 64, operands straight from memory, no step ahead, element by element
 // where a side is not a multiple of 8) took 62 / 62, 145 / 133, 192 / 185,
 // 887 / 632 and 824 / 679 us, and 353 / 267 at 509 x 733, now 83 / 84.
@@ -1250,8 +1254,8 @@ __device__ __forceinline__ void dct_f64_tile(const DArgs& a, const EoTile& t, bo
 }
 
 // TMAX: the larger of the tile sides in the launch.  Launches of small maps
-// only take the instance for side 32, whose LDS leaves room for two blocks on
-// a CU.
+// only take the instance for side 32, whose LDS leaves room for three blocks on
+// a CU (side 64: two).
 template <int INV, int TMAX>
 __global__ void __launch_bounds__(256, 2) k_e_dct_f64(DArgs a) {
   // two K steps' operands; the inverse's exchange fits in them

@@ -826,8 +826,10 @@ __global__ void __launch_bounds__(kMaxTileThreads) k_e_spmv(EArgs A) {
           return Op{src[row + j], PC == kPcJacobi ? aux[row + j] : T(1), dold[row + j]};
         },
         // Jacobi: s w + beta d rounds beta d first, except in the left half of the
-        // row above the tile: solves keep the bits they have always had (a mixed
-        // one of a thousand iterations moves by 1e-4 with one such rounding)
+        // row above the tile, where q is formed with a d that differs from the one
+        // its own tile stores in the last bit.  One rounding everywhere would be as
+        // good, but solves keep the bits they have always had (a mixed one of a
+        // thousand iterations moves by 1e-4 with one such rounding)
         [&](const Op& v, int, int) {
           return PC == kPcJacobi ? fused(v.s, v.w, beta * v.d) : fused(beta, v.d, v.s);
         },

@@ -34,10 +34,11 @@
 // each some 150 to 200 steps behind the one above it.
 //
 // What one workgroup can bring from memory sets the pace (a compute unit gets
-// about 50 GB/s of misses), so nothing is fetched twice: a chunk is as many
-// steps as a 128-byte line has elements, and a row's share of it is one whole
-// aligned line, the one whose first element is due within the chunk's steps.
-// Its 16 bytes per lane make 8 rows per instruction.
+// about 50 GB/s of misses), so nothing is fetched twice: a chunk is 16 steps, and
+// a row's share of it is one aligned run of 16 elements, the one whose first
+// element is due within the chunk's steps: a 128-byte line of doubles, or half a
+// line of floats (the other half follows from the caches a chunk later).  At 16
+// bytes per lane an instruction brings 8 rows (floats: 16).
 //
 // Progress: workgroups take strips from a ticket counter, in an order in which
 // a strip's predecessor always has the smaller ticket, so the strip a

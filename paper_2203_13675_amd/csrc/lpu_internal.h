@@ -102,12 +102,13 @@ struct KTimer {
 
 namespace lpu {
 
-// Executable graph of one PCG iteration for one launch shape; valid until the
-// engine is laid out again (the cache is emptied by every engine set-up).
+// Executable graph of a few PCG iterations for one launch shape; valid, across calls,
+// as long as the engine's buffers stay where they are (engine_allocate drops them).
 constexpr int kGraphKey = 12;
 struct GraphEntry {
-  int key[kGraphKey];  // launch shapes, DCT tile width, preconditioner and its parameters, precision,
-                       // tile height, iterations per graph
+  int key[kGraphKey];  // every launch argument that is not a buffer's address: grids, DCT tile shape,
+                       // preconditioner and its parameters, precision, tile height, iterations per
+                       // graph
   hipGraphExec_t exec;
 };
 
@@ -120,7 +121,7 @@ struct lp_unwrap_ctx {
   std::string last_error;
   lpu_tuning tune;
   lpu::Engine eng;
-  std::vector<lpu::GraphEntry> graphs;  // small cache, emptied by every engine set-up
+  std::vector<lpu::GraphEntry> graphs;  // small cache, emptied when the buffers are reallocated
   std::deque<lpu::DctTables> dct;  // cached per size (deque: stable references)
   std::vector<std::pair<int, lpu::DctTabDev*>> dct_dev;
   hipEvent_t list_event = nullptr;  // last upload from the pinned list staging

@@ -155,9 +155,8 @@ static int apply(lp_unwrap_ctx* ctx, int M, int N, int pc, double omega, const T
   const int ngroups = (ntiles + kArriveGroup - 1) / kArriveGroup + 1;
   Engine e;
   e.n_maps = e.caps.maps = 1;
-  e.total_px = e.caps.px = (long long)M * N;
+  e.caps.px = (long long)M * N;
   e.total_tiles = e.caps.tiles = ntiles;
-  e.max_n = N;
   e.total_strips = e.act_strips = wf_strips(M);
   e.th = th;
   e.grid = ctx->tune.grid;
