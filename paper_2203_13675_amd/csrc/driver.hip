@@ -84,7 +84,6 @@ static void engine_free(Engine& e) {
     if (p) (void)hipFree(p);
   if (e.hms) (void)hipHostFree(e.hms);
   if (e.hlist) (void)hipHostFree(e.hlist);
-  if (e.lost) (void)hipHostFree(e.lost);
   e = Engine();
 }
 
@@ -131,9 +130,10 @@ static bool engine_allocate(Engine& e, const EngineCaps& c) {
   for (void** p : tv) A(p, (size_t)c.vec);
   A((void**)&e.iso, px);
   A((void**)&e.P, 8 * (size_t)kNumSlots * pst);
-  if (ok && hipHostMalloc((void**)&e.hms, sizeof(MapState) * c.maps) != hipSuccess) ok = false;
+  // (the sweeps' lost word follows the states)
+  if (ok && hipHostMalloc((void**)&e.hms, sizeof(MapState) * c.maps + sizeof(int)) != hipSuccess) ok = false;
+  if (ok) e.lost = reinterpret_cast<int*>(e.hms + c.maps);
   if (ok && hipHostMalloc((void**)&e.hlist, 4 * list_ints) != hipSuccess) ok = false;
-  if (ok && hipHostMalloc((void**)&e.lost, sizeof(int)) != hipSuccess) ok = false;
   if (!ok) {
     engine_free(e);
     return false;
