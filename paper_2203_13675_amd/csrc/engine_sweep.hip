@@ -142,7 +142,7 @@ __device__ __forceinline__ double fma_t(double a, double b, double c) { return _
 //    between kPivotFloor times the least and four times the largest, and squares,
 //    quotients, reciprocals and residuals are normal numbers.  A strip that meets
 //    another coupling, or a pivot above it outside that range, divides by the operator
-//    from there on (840 x 1120: 280 us for the pivots where the reciprocals take 226).
+//    from there on (840 x 1120: 313 us for the pivots where the reciprocals take 260).
 __device__ __forceinline__ double rcp_full(double b) {
   double r = __builtin_amdgcn_rcp(b);
   r = __builtin_fma(__builtin_fma(-b, r, 1.0), r, r);
