@@ -349,11 +349,11 @@ int lpu_precond_apply_noalloc(lp_unwrap_ctx* ctx, int M, int N, int precision, i
 int lpu_debug_force_breakdown(lp_unwrap_ctx* ctx, long long iteration);
 
 /* Testing hook for the bounded wait of the natural-order sweeps, whose strips of
- * 64 rows pass their last row on: from the next call on, a strip polls for a value
- * at most max_polls times (< 0: the default, about a second) before it gives up and
- * goes on with NaN.  Every kernel still runs to completion.  Errors:
- * LPU_ERR_INVALID_ARG for a null context, LPU_ERR_HIP. */
-int lpu_debug_sweep_polls(lp_unwrap_ctx* ctx, int max_polls);
+ * 64 rows pass their last row on: with on != 0, from the next call on a strip gives up
+ * at the first value that is not there yet (instead of after about a second) and goes
+ * on with NaN.  Every kernel still runs to completion.  Errors: LPU_ERR_INVALID_ARG
+ * for a null context, LPU_ERR_HIP. */
+int lpu_debug_sweep_no_wait(lp_unwrap_ctx* ctx, int on);
 
 #ifdef __cplusplus
 }

@@ -70,7 +70,7 @@ EXPORTED = ["lpu_default_options", "lp_unwrap_create", "lp_unwrap_destroy", "lp_
             "lpu_wrapped_differences", "lpu_weights", "lpu_apply_A", "lpu_rhs",
             "lpu_precond_apply", "lpu_ilu_pivots", "lpu_kernel_timing", "lpu_kernel_timing_get",
             "lpu_default_tuning", "lp_unwrap_set_tuning", "lp_unwrap_get_tuning",
-            "lp_unwrap_autotune", "lpu_debug_force_breakdown", "lpu_debug_sweep_polls",
+            "lp_unwrap_autotune", "lpu_debug_force_breakdown", "lpu_debug_sweep_no_wait",
             "lpu_precond_apply_noalloc"]
 
 # kernel classes of the instrumentation (lpu_kernel_class)
@@ -132,8 +132,8 @@ def load_library(path: str = LIB_PATH) -> ctypes.CDLL:
     lib.lpu_precond_apply_noalloc.restype = ip
     lib.lpu_debug_force_breakdown.argtypes = [vp, ctypes.c_longlong]
     lib.lpu_debug_force_breakdown.restype = ip
-    lib.lpu_debug_sweep_polls.argtypes = [vp, ip]
-    lib.lpu_debug_sweep_polls.restype = ip
+    lib.lpu_debug_sweep_no_wait.argtypes = [vp, ip]
+    lib.lpu_debug_sweep_no_wait.restype = ip
     return lib
 
 
@@ -409,10 +409,10 @@ class Context:
         reports a breakdown (0 switches it off)."""
         self._raise(self._lib.lpu_debug_force_breakdown(self._h, int(iteration)))
 
-    def debug_sweep_polls(self, max_polls: int):
-        """Testing hook: a strip of a natural-order sweep gives up waiting after
-        max_polls polls (-1: the default)."""
-        self._raise(self._lib.lpu_debug_sweep_polls(self._h, int(max_polls)))
+    def debug_sweep_no_wait(self, on: bool):
+        """Testing hook: a strip of a natural-order sweep gives up at the first value
+        that is not there yet."""
+        self._raise(self._lib.lpu_debug_sweep_no_wait(self._h, int(on)))
 
     def precond_apply(self, U, V, r, preconditioner, *, precision="fp64", dct_mode="split_bf16",
                       omega=1.0):

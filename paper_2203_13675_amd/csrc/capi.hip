@@ -190,11 +190,11 @@ int lpu_debug_force_breakdown(lp_unwrap_ctx* ctx, long long iteration) {
   return LPU_OK;
 }
 
-int lpu_debug_sweep_polls(lp_unwrap_ctx* ctx, int max_polls) {
+int lpu_debug_sweep_no_wait(lp_unwrap_ctx* ctx, int on) {
   if (!ctx) return LPU_ERR_INVALID_ARG;
   if (hipSetDevice(ctx->device) != hipSuccess) return LPU_ERR_HIP;
-  release_graphs(ctx);  // (the bound is a launch argument)
-  ctx->debug_sweep_polls = max_polls < 0 ? -1 : max_polls;
+  release_graphs(ctx);  // (it is a launch argument)
+  ctx->debug_no_wait = on != 0;
   return LPU_OK;
 }
 

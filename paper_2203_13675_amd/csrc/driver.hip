@@ -256,6 +256,8 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
       return set_error(ctx, LPU_ERR_HIP, "hipMemset");
     // no launch's tag (launches count from 1) is in a fresh edge buffer
     if (hipMemsetAsync(e.wctl, 0, 256, ctx->stream) != hipSuccess ||
+        hipMemcpyAsync(e.wctl + kSweepLostAt, &e.lost, sizeof(e.lost), hipMemcpyHostToDevice,
+                       ctx->stream) != hipSuccess ||
         hipMemsetAsync(e.wedge, 0, 8 * (size_t)e.caps.edges, ctx->stream) != hipSuccess)
       return set_error(ctx, LPU_ERR_HIP, "hipMemsetAsync");
   }
@@ -269,7 +271,7 @@ static int engine_setup(lp_unwrap_ctx* ctx, int n, const lpu_map* maps, int elem
   e.total_tiles = tiles;
   e.total_dtiles = dtiles;
   e.total_strips = strips;
-  e.max_polls = ctx->debug_sweep_polls >= 0 ? ctx->debug_sweep_polls : kSweepPolls;
+  e.no_wait = ctx->debug_no_wait;
   *e.lost = 0;  // (no earlier call's launch is still running)
   e.th = ctx->tune.tile_rows;
   e.grid = ctx->tune.grid;

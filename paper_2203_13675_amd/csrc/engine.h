@@ -34,6 +34,7 @@ constexpr int kListHead = 16;      // ints of counts[] ahead of the active-map l
 // polls of one wait of the sweeps: about a second, where a wait on a running predecessor
 // takes microseconds
 constexpr int kSweepPolls = 1 << 20;
+constexpr int kSweepLostAt = 8;    // word of wctl where the address of Engine::lost lies
 
 // DCT tables of one size n as seen by the FP32 FMA kernel.
 struct DctTabDev {
@@ -134,8 +135,8 @@ struct Engine {
   bool dct_tile64 = false;   // a map takes FP64 or dense MFMA DCT tiles of 64 x 64
   int* mact = nullptr;       // active maps (sweep kernels)
   int* slist = nullptr;      // (map, strip) pairs of the active maps' strips, strip by strip
-  int max_polls = kSweepPolls;  // sweeps: polls of a wait before it is given up
-  int* lost = nullptr;          // sweeps: pinned word, set when one was given up
+  bool no_wait = false;      // sweeps: give up every wait at its first poll (tests)
+  int* lost = nullptr;       // sweeps: pinned word, set when a wait was given up
   unsigned int* wctl = nullptr;        // sweeps: ticket, workgroups done, launches so far
   unsigned long long* wedge = nullptr; // sweeps: tagged last rows of the strips
   int* fcnt = nullptr;       // per-map arrival counters of the fused finishers (zero between launches)

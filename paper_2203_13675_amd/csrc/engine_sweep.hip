@@ -46,7 +46,7 @@
 // whatever the number of resident workgroups.  The wait is bounded all the
 // same; a strip whose wait runs out goes on with NaN, which ends that map's
 // solve as a breakdown, and says so in a word that the calls that wait for the
-// device read (WArgs::lost).
+// device read (WArgs::ctl).
 //
 // Measured (960 x 1280 FP64; 840 x 1120 FP32): a forward solve 143 and 105 us,
 // a backward one 148 and 112 us, the pivots 286 and 213 us, where one launch
@@ -76,6 +76,9 @@ constexpr int kWHeld = 3;    // chunks a loader or storer wave holds in register
 constexpr int kWPitch = kWT + 1;  // LDS entries per step (an element's row + 1 is a valid entry)
 constexpr int kWMaxGrid = 512;
 
+// flags of a launch: SSOR's scale 2 - omega; give up every wait at its first poll (tests)
+enum : int { kWSsor = 1, kWNoWait = 2 };
+
 enum SweepMode : int { kWPivots = 0, kWForward = 1, kWBackward = 2 };
 
 struct WArgs {
@@ -88,7 +91,8 @@ struct WArgs {
   long long pstride;
   const void *U, *V, *piv, *r;
   void *s, *y;
-  unsigned int* ctl;         // ticket, workgroups done, launches so far
+  unsigned int* ctl;         // ticket, workgroups done, launches so far; from kSweepLostAt on the
+                             // address of the host word to set when a wait is given up, or null
   unsigned long long* edge;  // tagged last rows of the strips
   int *fcnt, *gcnt;          // arrival counters of the fused finisher
   double* gsum;
@@ -96,10 +100,8 @@ struct WArgs {
   int expect;    // state of the maps to work on (-1: every active map)
   int fin_mode;  // backward: FinishMode of the fused finisher of r^T s (0: none)
   int recip;     // pivots: store 1 / p (what the solves read) instead of p
-  int max_polls; // of one wait before it is given up
-  int* lost;     // host word set when that happens, or null
   double omega;
-  int ssor;
+  int flags;     // kWSsor, kWNoWait
 };
 
 // DPP whole-wave shift with a fill: lane l receives lane l-1's v, lane 0 keeps
@@ -562,6 +564,7 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
         const unsigned long long* above = edge - (size_t)N * 2;
         const T* Va = reinterpret_cast<const T*>(a.V) + base - N;
         bool lost = false;
+        const int k0 = (a.flags & kWNoWait) ? kSweepPolls : 0;
         Edge<T> ew;
         T vn = T(0);
         // the column of this lane in chunk q, or a valid one (whose values are
@@ -578,13 +581,11 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
           T v = kOff;
           if (strip > 0) {
             bool need = mine;
-            for (int k = 0;; ++k) {
+            for (int k = k0;; ++k) {
               if (need && ew.ready(tag)) v = ew.value(), need = false;
               if (__builtin_amdgcn_ballot_w64(need) == 0) break;
-              if (lost || k >= a.max_polls) {
+              if (lost || k >= kSweepPolls) {
                 if (need) v = T(__builtin_nanf(""));
-                if (!lost && a.lost)
-                  __hip_atomic_store(a.lost, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
                 lost = true;
                 break;
               }
@@ -616,6 +617,10 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
           }
           wf_barrier();
         }
+        if (lost) {
+          int* const word = *reinterpret_cast<int* const*>(a.ctl + kSweepLostAt);
+          if (word) __hip_atomic_store(word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
       } else {
         const int l = wf_lane(), st = wv - 6;
         struct Held {
@@ -625,7 +630,7 @@ __global__ void __launch_bounds__(kWThreads, sizeof(T) == 8 ? 2 : 4) k_wf_sweep(
         const T* R = reinterpret_cast<const T*>(a.r) + base;
         T* out = reinterpret_cast<T*>(MODE == kWPivots ? const_cast<void*>(a.piv)
                                                        : (kRev ? a.s : a.y)) + base;
-        const T scale = a.ssor ? (T)(2.0 - a.omega) : T(1);
+        const T scale = (a.flags & kWSsor) ? (T)(2.0 - a.omega) : T(1);
         WLanes<T, kRev, kGS> ln(l, st * kGS, rows, N, base);
         auto load_r = [&](auto fast, int q, Held& h) {
           if (!kRev) return;
@@ -800,10 +805,8 @@ static WArgs make_wargs(const Engine& e, int expect, bool ssor, double omega, co
   a.expect = expect;
   a.fin_mode = 0;
   a.recip = 1;
-  a.max_polls = e.max_polls;
-  a.lost = e.lost;
   a.omega = omega;
-  a.ssor = ssor ? 1 : 0;
+  a.flags = (ssor ? kWSsor : 0) | (e.no_wait ? kWNoWait : 0);
   return a;
 }
 

@@ -128,7 +128,7 @@ struct lp_unwrap_ctx {
   bool list_event_live = false;
   lpu::KTimer kt;
   long long debug_breakdown_at = 0;  // lpu_debug_force_breakdown (0: off)
-  int debug_sweep_polls = -1;        // lpu_debug_sweep_polls (< 0: the default)
+  bool debug_no_wait = false;        // lpu_debug_sweep_no_wait
 };
 
 namespace lpu {

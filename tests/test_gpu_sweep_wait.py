@@ -1,6 +1,6 @@
-"""The bounded wait of the natural-order sweeps: with a bound of no polls at all the
-strips below the first give up (nothing hangs, every kernel ends), and each call
-says so; with the default bound back everything is as before."""
+"""The bounded wait of the natural-order sweeps: made to give up at the first value
+that is not there yet, the strips below the first do so (nothing hangs, every kernel
+ends), and each call says so; with the default bound back everything is as before."""
 import numpy as np
 import pytest
 
@@ -33,7 +33,7 @@ def test_a_lost_wait_is_reported(precision, pc):
         want = ctx.precond_apply(U, V, r, pc, precision=precision)
         phi = ctx.solve(psi, **kw)
         piv = ctx.ilu_pivots(U, V, precision=precision)
-        ctx.debug_sweep_polls(0)
+        ctx.debug_sweep_no_wait(True)
         with pytest.raises(binding.LpuError) as e:
             ctx.precond_apply(U, V, r, pc, precision=precision)
         assert e.value.code == binding.ERR_HIP and "gave up" in ctx.last_error()
@@ -42,7 +42,7 @@ def test_a_lost_wait_is_reported(precision, pc):
         assert "gave up" in ctx.last_error()
         lost = ctx.solve(psi, **kw)
         assert lost.status == binding.ERR_BREAKDOWN and "gave up" in ctx.last_error()
-        ctx.debug_sweep_polls(-1)
+        ctx.debug_sweep_no_wait(False)
         assert torch.equal(ctx.precond_apply(U, V, r, pc, precision=precision), want)
         assert torch.equal(ctx.ilu_pivots(U, V, precision=precision), piv)
         again = ctx.solve(psi, **kw)
